@@ -334,14 +334,13 @@ jko_status jko_time_iteration(const jko_grid* grid, const jko_energy* energy, co
  * 65536 cells this library builds xi~ once per (domain, gamma, L) as a dense
  * float32 matrix in the workspace (over the Nf free cells, the upper triangle
  * of 128 x 128 tiles, about Nf^2 * 2 bytes: 187 MB for the 9556 free cells of
- * a 100 x 100 room) by FP64 Chebyshev solves on the device, then runs every
+ * a 100 x 100 room) in FP64 on the device, then runs every
  * product of the scaling iteration as one pass over it.  Above 65536 cells
- * (or with per_product = 1) it applies xi~ the paper's way instead: each
- * product is L solves of (Id - (gamma/L) Delta_M) y = rhs on the grid, each a
- * Chebyshev iteration in FP64 (one five-point stencil sweep per iteration,
- * eight iterations per launch on tiles with a halo of eight cells, to 1e-13
- * of the right-hand side; linear in the grid's size), rounded to float32; no
- * operator is stored.  The flow uses the iteration and stop test
+ * (or with per_product = 1) it stores nothing: each
+ * product is the Chebyshev series of (Id - (gamma/L) Delta_M)^-L on the grid
+ * in FP64 (one five-point stencil sweep per degree, 16 sweeps per launch on
+ * tiles with a halo of 16 cells, to 1e-15 of the input's norm; linear in the
+ * grid's size), rounded to float32.  The flow uses the iteration and stop test
  * of jko_step with xi replaced by xi~; float32 only, no log domain, no
  * backward.
  * ------------------------------------------------------------------------ */
@@ -363,10 +362,10 @@ size_t jko_heat_workspace_bytes(const jko_heat_domain* domain);
 
 /* Builds xi~ for this domain and gamma into the workspace (which then holds
  * it for jko_heat_apply and jko_heat_flow with the same domain and gamma).
- * Each column is L solves of (Id - (gamma/L) Delta_M) x = rhs by Chebyshev
- * iteration in FP64 to 1e-14 of the right-hand side, rounded to float32.
- * Synchronous.  Cost: L * (about 3 sqrt(1 + 4 gamma (n0^2 + n1^2) / L) + 1)
- * stencil sweeps over N x min(N, 1024) doubles per 1024 columns. */
+ * Each column is the Chebyshev series of (Id - (gamma/L) Delta_M)^-L applied
+ * to a unit vector in FP64, to 1e-15, rounded to float32.
+ * Synchronous.  Cost: about 25 sqrt(1 + 4 gamma (n0^2 + n1^2) / L)
+ * stencil sweeps of the grid per column for L = 10. */
 jko_status jko_heat_build(const jko_heat_domain* domain, double gamma, void* workspace,
                           size_t workspace_bytes, void* stream);
 

@@ -1768,14 +1768,14 @@ jko_status heat_sums(const double* err, int64_t ne, const float* p, int64_t np, 
 }
 
 // One product of the iteration with the epilogue `ek`: a pass over the stored
-// operator, or the L solves of the per-product form (hs.X != NULL).
+// operator, or the series of the per-product form (hs.Y != NULL).
 jko_status heat_product(int ek, const HeatGemv& g, const HeatSolve& hs, hipStream_t st) {
-    if (hs.X) HIP_TRY(launch_heat_solve(ek, g, hs, st));
+    if (hs.Y) HIP_TRY(launch_heat_solve(ek, g, hs, st));
     else HIP_TRY(launch_heat_gemv(ek, g, st));
     return JKO_OK;
 }
 
-// The per-product solves' context of a domain (X = NULL for the stored operator).
+// The per-product form's context of a domain (Y = NULL for the stored operator).
 HeatSolve heat_solve_of(const HeatLayout& H, const jko_heat_domain* d, char* base, double gamma) {
     HeatSolve hs{};
     if (!H.solve) return hs;
@@ -1786,11 +1786,11 @@ HeatSolve heat_solve_of(const HeatLayout& H, const jko_heat_domain* d, char* bas
     hs.n1 = d->n1;
     hs.L = d->L;
     hs.gamma = gamma;
-    hs.X = sc;
-    hs.R = sc + H.N;
-    hs.R1 = sc + 2 * H.N;
-    hs.D0 = sc + 3 * H.N;
-    hs.D1 = sc + 4 * H.N;
+    hs.Y = sc;
+    hs.T0 = sc + H.N;
+    hs.T1 = sc + 2 * H.N;
+    hs.Q0 = sc + 3 * H.N;
+    hs.Q1 = sc + 4 * H.N;
     return hs;
 }
 

@@ -14,6 +14,8 @@
 // columns of the padding are zero.
 #pragma once
 
+#include <vector>
+
 #include "jko_internal.h"
 
 namespace jko {
@@ -65,39 +67,62 @@ hipError_t launch_heat_compact(const uint8_t* mask, int64_t N, int32_t* cidx, in
 hipError_t launch_heat_gather(float* x, const float* src, const int32_t* gidx, int64_t nf, int64_t ld,
                               hipStream_t st);
 
-// Chebyshev iterations per implicit step that bring the error of each solve
-// below tol of the right-hand side for the spectrum [1, beta].
-int heat_cheb_iters(double beta, double tol);
+// x^-L on [1, beta] as a Chebyshev series: x^-L = c_0 / 2 + sum_k c_k T_k(u),
+// x = theta + delta u, theta = (beta + 1) / 2, delta = (beta - 1) / 2, with an
+// error of at most tol (times x^-L's largest value, 1) anywhere on the interval.
+struct HeatSeries {
+    std::vector<double> c;
+};
+HeatSeries heat_series(double beta, int L, double tol);
 
-// Per-product form: the L solves of one product stop at this error relative
-// to the right-hand side's norm.  A product's far tail lies many orders below
-// its norm, and the scaling iteration divides by it (b = q / t), so the bound
-// sits far below float32 resolution.
-constexpr double kHeatSolveTol = 1e-13;
+// A product's far tail lies many orders below its norm, and the scaling
+// iteration divides by it (b = q / t), so the series' bound sits at the
+// resolution of its FP64 sums, far below float32's.
+constexpr double kHeatSeriesTol = 1e-15;
 
-// One product y = xi~ x by L solves on the grid (the paper's form of the
-// operator): x (free-cell vector of g) is scattered to the grid vector X,
-// solved in place, and each free row finished by the epilogue `ek` of g
-// (codes of launch_heat_gemv).  R, R1, D0, D1: grid scratch (N doubles
-// each; the residual and the direction alternate between their pairs).
+// One product y = xi~ x on the grid, nothing stored: x is g's free-cell vector
+// and each free row is finished by the epilogue `ek` of g (codes of
+// launch_heat_gemv).  T0, T1, Q0, Q1, Y: grid scratch (N doubles each).
 struct HeatSolve {
     const uint8_t* mask;     // NULL = no obstacle
     const int32_t* cidx;     // grid cell -> free index or -1
     int n0, n1, L;
     double gamma;
-    double* X;
-    double* R;
-    double* R1;
-    double* D0;
-    double* D1;
-};
-
-// Coefficients of up to 8 consecutive Chebyshev iterations (one launch).
-struct HeatChebSteps {
-    double c1[8], c2[8];
-    int steps;
+    double* T0;
+    double* T1;
+    double* Q0;
+    double* Q1;
+    double* Y;
 };
 hipError_t launch_heat_solve(int ek, const HeatGemv& g, const HeatSolve& h, hipStream_t st);
+
+// Sweeps of the series per launch.
+constexpr int kHeatSweeps = 16;
+
+// One launch of the series (kernel argument).
+struct HeatSeriesArgs {
+    int n0, n1;
+    double nu0, nu1, theta;
+    double scale;            // 2 / delta
+    double c0;               // c_0 / 2
+    double c[kHeatSweeps];   // the coefficients of this launch's sweeps
+    int steps;
+    int first;               // the start: T_0 from x, or from the unit column
+    int unit;                // columns of the operator: the vector of blockIdx.y is e_(j0 + blockIdx.y)
+    const uint8_t* mask;
+    const int32_t* cidx;
+    const int32_t* gidx;
+    const float* x;
+    const double* Tin;
+    const double* Qin;
+    double* Tout;
+    double* Qout;
+    double* Y;
+    int64_t stride;          // doubles between the grid vectors of two columns
+    int64_t j0;              // first column of the batch
+    float* A;                // the packed operator and its tiles per side
+    int64_t nT;
+};
 
 // Scratch doubles heat_build_operator needs for an N-cell grid (4 N C).
 int64_t heat_build_scratch(int64_t N);

@@ -12,20 +12,20 @@
 // room take 187 MB, which fits the device's 256 MB last-level cache.
 //
 // Grids of more than 2^16 cells (or on request) take the paper's own form
-// instead: each product is L successive solves of (Id - (gamma/L) Delta_M) y
-// = rhs on the grid, by the same Chebyshev iteration in FP64 with one vector
-// (a stencil sweep per iteration, linear in the grid's size), and its result
-// goes through the same epilogues.  No operator is stored.
+// instead, nothing stored: each product is (Id - (gamma/L) Delta_M)^-L on the
+// grid, as one Chebyshev series of the operator in FP64 (a stencil sweep per
+// degree, linear in the grid's size), and its result goes through the same
+// epilogues.
 //
-// Construction: the columns of xi~ are L successive solves of
-// M x = rhs, M = Id + nu_0 G_0 + nu_1 G_1, from unit vectors, all columns of
-// a chunk at once (C columns, element (cell i, column c) at i*C + c, so the
-// five-point stencil reads whole rows of C consecutive doubles).  M is
+// Construction: the columns of xi~ are the same series applied to unit
+// vectors, a chunk of columns per launch.  M = Id + nu_0 G_0 + nu_1 G_1 is
 // symmetric with spectrum in [1, 1 + 4 nu_0 + 4 nu_1] (Gershgorin; G_k is
-// positive semi-definite), so each solve is a Chebyshev iteration
-// (Saad, Iterative Methods for Sparse Linear Systems, 2nd ed., Alg. 12.1)
-// with no inner products: one stencil sweep per iteration, in FP64.
+// positive semi-definite).
+#include <math.h>
+
 #include <algorithm>
+#include <new>
+#include <vector>
 
 #include "heat.h"
 #include "epilogue.h"
@@ -40,165 +40,161 @@ namespace {
 
 __device__ __forceinline__ bool is_free(const uint8_t* mask, int64_t i) { return !mask || mask[i]; }
 
-// (M x)_(i, c) over a chunk: x_i + sum over free neighbours j of nu_k (x_i - x_j)
-// for a free cell; x_i (zero) for an obstacle.
-__device__ __forceinline__ double heat_mx(const double* __restrict__ x, const uint8_t* __restrict__ mask,
-                                          int64_t i, int64_t e, int C, int n0, int n1, double nu0, double nu1) {
-    const double xi = x[e];
-    if (!is_free(mask, i)) return xi;
-    const int r = (int)(i / n1), col = (int)(i - (int64_t)r * n1);
-    double acc = xi;
-    if (r > 0 && is_free(mask, i - n1)) acc += nu0 * (xi - x[e - (int64_t)n1 * C]);
-    if (r + 1 < n0 && is_free(mask, i + n1)) acc += nu0 * (xi - x[e + (int64_t)n1 * C]);
-    if (col > 0 && is_free(mask, i - 1)) acc += nu1 * (xi - x[e - C]);
-    if (col + 1 < n1 && is_free(mask, i + 1)) acc += nu1 * (xi - x[e + C]);
-    return acc;
+// One product (or one column of the stored operator) as a Chebyshev series.
+// M has its spectrum in [1, beta], so with u = (x - theta) / delta,
+//   x^-L = c_0 / 2 + sum_k c_k T_k(u) + O(tol)          (heat_series)
+// and xi~ v = M^-L v takes K sweeps of the recurrence
+//   T_0 = v,  T_1 = Mh v,  T_{k+1} = 2 Mh T_k - T_{k-1},   Mh = (M - theta) / delta,
+// each one five-point stencil, where L successive solves take L times a
+// solve's iterations: 75 sweeps instead of 450 for L = 10 and nu = 1
+// (beta = 9).  FP64 throughout.
+//
+// k_heat_series runs up to kPS sweeps per launch, blocked in time: a block
+// holds T_k and T_{k-1} of a kPTileH x kPTileW tile and a halo of kPS cells
+// in registers (a wave: one row of 64 cells per register, kPRows rows), and
+// the exact region shrinks by one cell per sweep, so that after kPS sweeps
+// the tile is still exact.  Left and right neighbours come from the
+// neighbouring lanes, the rows above and below from the wave's own registers
+// or, at its edge rows, from LDS (double-buffered, one barrier per sweep).
+// A cell outside the domain holds zeros in every T_k, so the neighbours'
+// weights are the same everywhere and only the diagonal differs by cell.
+// 300 x 300 room, one product: 754 us as L solves (60 launches of 11.9 us, eight
+// sweeps each through LDS, and 10 of 4.8 us), 64 us as five launches of this.
+// Bound: launch and load latency (about 4 us of a launch), then FP64 issue:
+// 7 FP64 operations and 4 lane moves per cell and sweep, 12 rows per SIMD.
+constexpr int kPS = kHeatSweeps;           // sweeps per launch = halo width
+constexpr int kPWaves = 16;
+constexpr int kPRows = 3;                  // rows per wave
+constexpr int kPTileW = 64 - 2 * kPS;      // 32
+constexpr int kPTileH = kPWaves * kPRows - 2 * kPS;   // 16
+static_assert(kPTileW > 0 && kPTileH > 0, "tile");
+constexpr int HEAT_DST_CONT = -1;          // the series goes on in the next launch
+constexpr int HEAT_DST_OPERATOR = -2;      // the last launch stores a row of the operator
+
+// The value of the lane to the left (lane - 1) or right (lane + 1); 0 past the ends.
+__device__ __forceinline__ double lane_left(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)b, 0x138, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(b >> 32), 0x138, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double lane_right(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)b, 0x130, 0xf, 0xf, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(b >> 32), 0x130, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// X = the unit columns of free cells j0 .. j0+C-1 (grid cell gidx[j]; none
-// at or beyond nf).
-__global__ void k_heat_unit(double* __restrict__ X, const int32_t* __restrict__ gidx, int64_t nf, int64_t N,
-                            int logC, int64_t j0) {
-    const int64_t n = N << logC;
-    const int C = 1 << logC;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e >> logC;
-        const int64_t j = j0 + (e & (C - 1));
-        X[e] = (j < nf && i == gidx[j]) ? 1.0 : 0.0;
-    }
-}
+template <int EK>
+__device__ __forceinline__ void heat_epilogue(const HeatGemv& g, int64_t r, float v);
+__host__ __device__ __forceinline__ int64_t tile_index(int64_t I, int64_t J, int64_t nT);
 
-// Start of one solve with right-hand side and first guess X:
-// R = X - M X, D = R / theta.
-__global__ void k_heat_cheb_init(const double* __restrict__ X, double* __restrict__ R, double* __restrict__ D,
-                                 const uint8_t* __restrict__ mask, int64_t N, int logC, int n0, int n1,
-                                 double nu0, double nu1, double inv_theta) {
-    const int64_t n = N << logC;
-    const int C = 1 << logC;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e >> logC;
-        const double r = X[e] - heat_mx(X, mask, i, e, C, n0, n1, nu0, nu1);
-        R[e] = r;
-        D[e] = r * inv_theta;
-    }
-}
-
-// One Chebyshev iteration: X += D, R -= M D, Dn = c1 D + c2 R (new R).
-// D is only read (at the cell and its neighbours); X, R, Dn only at the cell.
-__global__ void k_heat_cheb_step(double* __restrict__ X, double* __restrict__ R, const double* __restrict__ D,
-                                 double* __restrict__ Dn, const uint8_t* __restrict__ mask, int64_t N, int logC,
-                                 int n0, int n1, double nu0, double nu1, double c1, double c2) {
-    const int64_t n = N << logC;
-    const int C = 1 << logC;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e >> logC;
-        const double d = D[e];
-        const double md = heat_mx(D, mask, i, e, C, n0, n1, nu0, nu1);
-        X[e] += d;
-        const double r = R[e] - md;
-        R[e] = r;
-        Dn[e] = c1 * d + c2 * r;
-    }
-}
-
-// Several Chebyshev iterations per launch for one grid vector (the
-// per-product solves), blocked in time: a block owns a kHB x kHB tile,
-// stages R and D over the tile and a halo of kHS cells in LDS, and runs up
-// to kHS iterations there; each iteration reads D at the neighbours, so the
-// cells it can update shrink by one per iteration, and after kHS of them the
-// tile is still exact.  It then writes X, R and the new D of its tile (R and
-// D to the other buffers of a pair: other blocks still read the old ones as
-// their halos).  Per cell the arithmetic is k_heat_cheb_step's, in the same
-// order (absent neighbour terms add exact zeros).
-constexpr int kHB = 16;                  // tile edge
-constexpr int kHS = 8;                   // iterations per launch (halo width)
-constexpr int kHR = kHB + 2 * kHS;       // staged region edge
-constexpr int kHBThr = 256;
-static_assert(kHR * kHR % kHBThr == 0, "whole cells per thread");
-
-__global__ void __launch_bounds__(kHBThr)
-k_heat_cheb_block(double* __restrict__ X, const double* __restrict__ Rin, const double* __restrict__ Din,
-                  double* __restrict__ Rout, double* __restrict__ Dout, const uint8_t* __restrict__ mask, int n0,
-                  int n1, double nu0, double nu1, HeatChebSteps cf) {
-    constexpr int PER = kHR * kHR / kHBThr;
-    __shared__ double sR[kHR * kHR];
-    __shared__ double sD[2][kHR * kHR];
-    __shared__ uint8_t sM[kHR * kHR];   // 1 free cell, 0 obstacle or outside the grid
-    const int tiles_j = (n1 + kHB - 1) / kHB;
-    const int gi0 = (int)(blockIdx.x / tiles_j) * kHB - kHS;
-    const int gj0 = (int)(blockIdx.x % tiles_j) * kHB - kHS;
-    const int tid = threadIdx.x;
-    double xr[PER];
+// DST: an epilogue code (the last launch of a product), HEAT_DST_CONT or
+// HEAT_DST_OPERATOR (the last launch of an operator column; blockIdx.y is the
+// column of the batch).
+template <int DST>
+__global__ void __launch_bounds__(64 * kPWaves)
+k_heat_series(HeatSeriesArgs P, HeatGemv G) {
+    __shared__ double rowTop[2][kPWaves][64];
+    __shared__ double rowBot[2][kPWaves][64];
+    const int n0 = P.n0, n1 = P.n1;
+    const int tiles_j = (n1 + kPTileW - 1) / kPTileW;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int i0 = (int)(blockIdx.x / tiles_j) * kPTileH - kPS + kPRows * wave;   // grid row of this wave's first row
+    const int j = (int)(blockIdx.x % tiles_j) * kPTileW - kPS + lane;
+    const bool colin = j >= 0 && j < n1;
+    const int64_t col = (int64_t)blockIdx.y * P.stride;   // this column's grid vectors
+    double T[kPRows], Q[kPRows], y[kPRows], diag[kPRows], f[kPRows];
+    // free cells of the wave's rows and of the rows above and below
+    bool fr[kPRows + 2];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int c = tid + q * kHBThr;
-        const int li = c / kHR, lj = c % kHR, gi = gi0 + li, gj = gj0 + lj;
-        const bool in = gi >= 0 && gi < n0 && gj >= 0 && gj < n1;
-        const int64_t g = (int64_t)gi * n1 + gj;
-        sR[c] = in ? Rin[g] : 0.0;
-        sD[0][c] = in ? Din[g] : 0.0;
-        sM[c] = (in && is_free(mask, g)) ? 1 : 0;
-        const bool own = li >= kHS && li < kHS + kHB && lj >= kHS && lj < kHS + kHB;
-        xr[q] = (in && own) ? X[g] : 0.0;
+    for (int r = 0; r < kPRows + 2; ++r) {
+        const int i = i0 + r - 1;
+        fr[r] = colin && i >= 0 && i < n0 && is_free(P.mask, (int64_t)i * n1 + j);
     }
-    __syncthreads();
-    // Each cell's stencil once for the launch, branch-free: the weight of a
-    // neighbour is nu_k when both cells are free and 0 otherwise (an absent
-    // term adds an exact zero, so the sum is the same as skipping it; an
-    // obstacle's row is the identity).  Cells of the region's outer ring use
-    // themselves as neighbours: their values are never read by a cell that
-    // is still exact (the exact region shrinks by one cell per iteration).
-    int nb[PER][4];
-    double wt[PER][4];
-    double ownf[PER];
+    const bool owncol = lane >= kPS && lane < kPS + kPTileW;
+    bool own[kPRows];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int c = tid + q * kHBThr;
-        const int li = c / kHR, lj = c % kHR;
-        const bool ring = li == 0 || li == kHR - 1 || lj == 0 || lj == kHR - 1;
-        const bool f = sM[c] == 1 && !ring;
-        nb[q][0] = ring ? c : c - kHR;
-        nb[q][1] = ring ? c : c + kHR;
-        nb[q][2] = ring ? c : c - 1;
-        nb[q][3] = ring ? c : c + 1;
-        wt[q][0] = (f && sM[c - kHR] == 1) ? nu0 : 0.0;
-        wt[q][1] = (f && sM[c + kHR] == 1) ? nu0 : 0.0;
-        wt[q][2] = (f && sM[c - 1] == 1) ? nu1 : 0.0;
-        wt[q][3] = (f && sM[c + 1] == 1) ? nu1 : 0.0;
-        ownf[q] = (li >= kHS && li < kHS + kHB && lj >= kHS && lj < kHS + kHB) ? 1.0 : 0.0;
-    }
-    for (int st = 0; st < cf.steps; ++st) {
-        const double* D = sD[st & 1];
-        double* Dn = sD[(st + 1) & 1];
-        const double c1 = cf.c1[st], c2 = cf.c2[st];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            const int c = tid + q * kHBThr;
-            const double d = D[c];
-            const double du = D[nb[q][0]], dd = D[nb[q][1]], dl = D[nb[q][2]], dr = D[nb[q][3]];
-            double md = d;
-            md += wt[q][0] * (d - du);
-            md += wt[q][1] * (d - dd);
-            md += wt[q][2] * (d - dl);
-            md += wt[q][3] * (d - dr);
-            xr[q] += ownf[q] * d;
-            const double r = sR[c] - md;
-            sR[c] = r;
-            Dn[c] = c1 * d + c2 * r;
+    for (int r = 0; r < kPRows; ++r) {
+        const int i = i0 + r, li = kPRows * wave + r;
+        const int g = i * n1 + j;
+        const bool c = fr[r + 1];
+        own[r] = c && owncol && li >= kPS && li < kPS + kPTileH;
+        T[r] = Q[r] = y[r] = 0.0;
+        if (c) {
+            if (P.first) {
+                if (DST == HEAT_DST_OPERATOR || P.unit) T[r] = (P.gidx[P.j0 + blockIdx.y] == g) ? 1.0 : 0.0;
+                else {
+                    const int32_t x = P.cidx[g];
+                    T[r] = x >= 0 ? (double)P.x[x] : 0.0;
+                }
+                y[r] = P.c0 * T[r];
+            } else {
+                T[r] = P.Tin[col + g];
+                Q[r] = P.Qin[col + g];
+                if (own[r]) y[r] = P.Y[col + g];
+            }
         }
-        __syncthreads();
+        f[r] = c ? (P.first ? 0.5 : 1.0) : 0.0;
     }
-    const double* Df = sD[cf.steps & 1];
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-        const int c = tid + q * kHBThr;
-        const int li = c / kHR, lj = c % kHR, gi = gi0 + li, gj = gj0 + lj;
-        const bool own = li >= kHS && li < kHS + kHB && lj >= kHS && lj < kHS + kHB;
-        if (!own || gi >= n0 || gj >= n1) continue;
-        const int64_t g = (int64_t)gi * n1 + gj;
-        X[g] = xr[q];
-        Rout[g] = sR[c];
-        Dout[g] = Df[c];
+    for (int r = 0; r < kPRows; ++r) {
+        // neighbours in the domain, per axis
+        const int me = fr[r + 1] ? 1 : 0;
+        const int lf = __builtin_amdgcn_update_dpp(0, me, 0x138, 0xf, 0xf, true);
+        const int rt = __builtin_amdgcn_update_dpp(0, me, 0x130, 0xf, 0xf, true);
+        diag[r] = P.scale * ((1.0 - P.theta) + P.nu0 * (double)((fr[r] ? 1 : 0) + (fr[r + 2] ? 1 : 0)) +
+                             P.nu1 * (double)(lf + rt));
+    }
+    const double w0 = -P.scale * P.nu0, w1 = -P.scale * P.nu1;
+    for (int st = 0; st < P.steps; ++st) {
+        const int buf = st & 1;
+        rowTop[buf][wave][lane] = T[0];
+        rowBot[buf][wave][lane] = T[kPRows - 1];
+        __syncthreads();
+        const double up = wave > 0 ? rowBot[buf][wave - 1][lane] : 0.0;
+        const double dn = wave < kPWaves - 1 ? rowTop[buf][wave + 1][lane] : 0.0;
+        const double ck = P.c[st];
+#pragma unroll
+        for (int r = 0; r < kPRows; ++r) {
+            const double u = r > 0 ? T[r - 1] : up, d = r < kPRows - 1 ? T[r + 1] : dn;
+            double t = diag[r] * T[r];
+            t = __builtin_fma(w1, lane_left(T[r]) + lane_right(T[r]), t);
+            t = __builtin_fma(w0, u + d, t);
+            Q[r] = __builtin_fma(f[r], t, -Q[r]);   // T_{k+1}; swapped with T below
+            y[r] = __builtin_fma(ck, Q[r], y[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < kPRows; ++r) {
+            const double t = T[r];
+            T[r] = Q[r];
+            Q[r] = t;
+        }
+        if (P.first && st == 0)
+#pragma unroll
+            for (int r = 0; r < kPRows; ++r) f[r] += f[r];
+    }
+#pragma unroll
+    for (int r = 0; r < kPRows; ++r) {
+        if (!own[r]) continue;
+        const int g = (i0 + r) * n1 + j;
+        const int32_t cc = DST == HEAT_DST_CONT ? 0 : P.cidx[g];
+        if (cc < 0) continue;
+        if constexpr (DST == HEAT_DST_CONT) {
+            P.Tout[col + g] = T[r];
+            P.Qout[col + g] = Q[r];
+            P.Y[col + g] = y[r];
+        } else if constexpr (DST == HEAT_DST_OPERATOR) {
+            // row j of the operator (xi~ is symmetric: column j), its part in
+            // the upper triangle of tiles
+            const int64_t row = P.j0 + blockIdx.y;
+            const int64_t I = row / kHeatTile, J = cc / kHeatTile;
+            if (I <= J)
+                P.A[tile_index(I, J, P.nT) * kHeatTile * kHeatTile + (row - I * kHeatTile) * kHeatTile +
+                    (cc - J * kHeatTile)] = (float)y[r];
+        } else {
+            heat_epilogue<DST>(G, cc, (float)y[r]);
+        }
     }
 }
 
@@ -210,27 +206,6 @@ __global__ void k_heat_zero(float* __restrict__ A, int64_t n) {
 // Packed index of the upper-triangular tile (I, J), I <= J, of nT x nT.
 __host__ __device__ __forceinline__ int64_t tile_index(int64_t I, int64_t J, int64_t nT) {
     return I * nT - I * (I - 1) / 2 + (J - I);
-}
-
-// Element (free row cidx[i], free column j0 + c) of xi~ = X[i, c] rounded to
-// float32, stored where its tile lies in the upper triangle (xi~ is
-// symmetric: the solves give every column, the lower half is the
-// transpose).  Columns at or beyond nf are zero in X; padding rows are never
-// written and stay zero.
-__global__ void k_heat_store(const double* __restrict__ X, float* __restrict__ A, const int32_t* __restrict__ cidx,
-                             int64_t N, int logC, int64_t ld, int64_t j0) {
-    const int64_t n = N << logC;
-    const int C = 1 << logC;
-    const int64_t nT = ld / kHeatTile;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = e >> logC;
-        const int64_t r = cidx[i];
-        const int64_t j = j0 + (e & (C - 1));
-        const int64_t I = r / kHeatTile, J = j / kHeatTile;
-        if (r >= 0 && j < ld && I <= J)
-            A[tile_index(I, J, nT) * kHeatTile * kHeatTile + (r - I * kHeatTile) * kHeatTile + (j - J * kHeatTile)] =
-                (float)X[e];
-    }
 }
 
 // Free cells in row-major order: each of the 256 threads counts a contiguous
@@ -272,15 +247,6 @@ __global__ void k_heat_gather(float* __restrict__ x, const float* __restrict__ s
 }
 
 // ------------------------------------------------------------------ products
-
-// X (grid, FP64) = the free-cell vector x scattered to its cells, 0 on obstacles.
-__global__ void k_heat_scatter(double* __restrict__ X, const float* __restrict__ x, const int32_t* __restrict__ cidx,
-                               int64_t N) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < N; i += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = cidx[i];
-        X[i] = r >= 0 ? (double)x[r] : 0.0;
-    }
-}
 
 // Finish row r (free cell i = gidx[r]) of y = A x (value v): the epilogue of
 // the iteration's half-step.
@@ -407,30 +373,24 @@ __global__ void __launch_bounds__(256) k_heat_finish(HeatGemv g) {
     }
 }
 
-// Finish of a product computed by the solves: row r takes its cell's value of
-// X (rounded to float32) through the epilogue.
-template <int EK>
-__global__ void __launch_bounds__(256) k_heat_solve_finish(HeatGemv g, const double* __restrict__ X) {
-    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < g.N; r += (int64_t)gridDim.x * blockDim.x)
-        heat_epilogue<EK>(g, r, (float)X[g.gidx[r]]);
-}
-
 __global__ void k_heat_fill(float* __restrict__ x, float v, int64_t n, int64_t ld) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < ld; i += (int64_t)gridDim.x * blockDim.x)
         x[i] = i < n ? v : 0.f;
 }
 
-__global__ void __launch_bounds__(256) k_heat_sums(const double* __restrict__ errrow, int64_t ne,
+__global__ void __launch_bounds__(1024) k_heat_sums(const double* __restrict__ errrow, int64_t ne,
                                                    const float* __restrict__ p, int64_t np, double* __restrict__ out) {
-    __shared__ double sh[4];
+    __shared__ double sh[16];
     double e = 0.0, m = 0.0, bad = 0.0;
     if (errrow)
+#pragma unroll 4
         for (int64_t i = threadIdx.x; i < ne; i += blockDim.x) {
             const double v = errrow[i];
             if (isfinite(v)) e += v;
             else bad += 1.0;
         }
     if (p)
+#pragma unroll 4
         for (int64_t i = threadIdx.x; i < np; i += blockDim.x) m += (double)p[i];
     e = block_sum(e, sh);
     if (threadIdx.x == 0) out[0] = e;
@@ -440,11 +400,12 @@ __global__ void __launch_bounds__(256) k_heat_sums(const double* __restrict__ er
     if (threadIdx.x == 0) out[2] = bad;
 }
 
-__global__ void __launch_bounds__(256) k_heat_input(const float* __restrict__ p, const uint8_t* __restrict__ mask,
+__global__ void __launch_bounds__(1024) k_heat_input(const float* __restrict__ p, const uint8_t* __restrict__ mask,
                                                     const float* __restrict__ kappa, float kappa_s, int64_t N,
                                                     double* __restrict__ out) {
-    __shared__ double sh[4];
+    __shared__ double sh[16];
     double m = 0.0, cap = 0.0, bad = 0.0;
+#pragma unroll 4
     for (int64_t i = threadIdx.x; i < N; i += blockDim.x) {
         const float v = p[i];
         const bool fr = is_free(mask, i);
@@ -473,50 +434,67 @@ int chunk_log2(int64_t N) {
     return lg;                                    // at most 1024 columns per chunk
 }
 
-// L solves of M y = X in place on the grid vector X (obstacles stay zero),
-// each a Chebyshev iteration of K steps from the first guess X, kHS steps per
-// launch (k_heat_cheb_block; R and D alternate between their two buffers).
-void heat_solves(const HeatSolve& h, int K, hipStream_t st) {
-    const int64_t N = (int64_t)h.n0 * h.n1;
-    const double nu0 = h.n0 > 1 ? h.gamma * (double)h.n0 * h.n0 / h.L : 0.0;
-    const double nu1 = h.n1 > 1 ? h.gamma * (double)h.n1 * h.n1 / h.L : 0.0;
+// The stencil's constants and the series' coefficients for a domain.
+struct SeriesPlan {
+    HeatSeriesArgs a{};
+    HeatSeries s;
+    unsigned tiles = 0;
+};
+SeriesPlan series_plan(int n0, int n1, double gamma, int L) {
+    SeriesPlan p;
+    const double nu0 = n0 > 1 ? gamma * (double)n0 * n0 / L : 0.0;
+    const double nu1 = n1 > 1 ? gamma * (double)n1 * n1 / L : 0.0;
     const double beta = 1.0 + 4.0 * (nu0 + nu1);
-    const double theta = 0.5 * (beta + 1.0), delta = 0.5 * (beta - 1.0);
-    const int gb = grid_for(N);
-    const unsigned tiles = (unsigned)(((h.n0 + kHB - 1) / kHB) * ((h.n1 + kHB - 1) / kHB));
-    double* R[2] = {h.R, h.R1};
-    double* D[2] = {h.D0, h.D1};
-    for (int l = 0; l < h.L && K > 0; ++l) {
-        hipLaunchKernelGGL(k_heat_cheb_init, dim3(gb), dim3(256), 0, st, h.X, R[0], D[0], h.mask, N, 0, h.n0, h.n1,
-                           nu0, nu1, 1.0 / theta);
-        const double sigma1 = theta / delta;
-        double rho = 1.0 / sigma1;
-        int cur = 0;
-        for (int k = 0; k < K; k += kHS) {
-            HeatChebSteps cf{};
-            cf.steps = std::min(kHS, K - k);
-            for (int j = 0; j < cf.steps; ++j) {
-                const double rho_n = 1.0 / (2.0 * sigma1 - rho);
-                cf.c1[j] = rho_n * rho;
-                cf.c2[j] = 2.0 * rho_n / delta;
-                rho = rho_n;
-            }
-            hipLaunchKernelGGL(k_heat_cheb_block, dim3(tiles), dim3(kHBThr), 0, st, h.X, R[cur], D[cur], R[1 - cur],
-                               D[1 - cur], h.mask, h.n0, h.n1, nu0, nu1, cf);
-            cur = 1 - cur;
-        }
-    }
+    p.s = heat_series(beta, L, kHeatSeriesTol);
+    if (p.s.c.empty()) return p;
+    p.a.n0 = n0;
+    p.a.n1 = n1;
+    p.a.nu0 = nu0;
+    p.a.nu1 = nu1;
+    p.a.theta = 0.5 * (beta + 1.0);
+    p.a.scale = beta > 1.0 ? 4.0 / (beta - 1.0) : 0.0;   // 2 / delta
+    p.a.c0 = 0.5 * p.s.c[0];
+    p.tiles = (unsigned)(((n0 + kPTileH - 1) / kPTileH) * ((n1 + kPTileW - 1) / kPTileW));
+    return p;
+}
+
+// The launches of a series of degree K over `cols` columns; T and Q (T_{k-1})
+// alternate between their two buffers (other blocks still read the old ones
+// as their halos), the last launch finishes with DST.
+template <int DST>
+hipError_t run_series(SeriesPlan& p, double* const T[2], double* const Q[2], unsigned cols, const HeatGemv& g,
+                      hipStream_t st) {
+    const int K = (int)p.s.c.size() - 1;
+    if (K < 0) return hipErrorOutOfMemory;   // no series (an operator whose degree could not be run)
+    int cur = 0, k = 0;
+    do {
+        HeatSeriesArgs& a = p.a;
+        a.first = k == 0 ? 1 : 0;
+        a.steps = std::min(kPS, K - k);
+        for (int q = 0; q < a.steps; ++q) a.c[q] = p.s.c[k + 1 + q];
+        a.Tin = T[cur];
+        a.Qin = Q[cur];
+        a.Tout = T[1 - cur];
+        a.Qout = Q[1 - cur];
+        k += a.steps;
+        if (k < K) hipLaunchKernelGGL(k_heat_series<HEAT_DST_CONT>, dim3(p.tiles, cols), dim3(64 * kPWaves), 0, st, a, g);
+        else hipLaunchKernelGGL(k_heat_series<DST>, dim3(p.tiles, cols), dim3(64 * kPWaves), 0, st, a, g);
+        cur = 1 - cur;
+    } while (k < K);
+    return hipGetLastError();
 }
 
 template <int EK>
 hipError_t solve_as(const HeatGemv& g, const HeatSolve& h, hipStream_t st) {
-    const int64_t N = (int64_t)h.n0 * h.n1;
-    hipLaunchKernelGGL(k_heat_scatter, dim3(grid_for(N)), dim3(256), 0, st, h.X, g.x, h.cidx, N);
-    const double nu0 = h.n0 > 1 ? h.gamma * (double)h.n0 * h.n0 / h.L : 0.0;
-    const double nu1 = h.n1 > 1 ? h.gamma * (double)h.n1 * h.n1 / h.L : 0.0;
-    heat_solves(h, heat_cheb_iters(1.0 + 4.0 * (nu0 + nu1), kHeatSolveTol), st);
-    if (g.N > 0) hipLaunchKernelGGL(k_heat_solve_finish<EK>, dim3(grid_for(g.N)), dim3(256), 0, st, g, h.X);
-    return hipGetLastError();
+    if (g.N <= 0) return hipSuccess;   // no free cell
+    SeriesPlan p = series_plan(h.n0, h.n1, h.gamma, h.L);
+    p.a.mask = h.mask;
+    p.a.cidx = h.cidx;
+    p.a.x = g.x;
+    p.a.Y = h.Y;
+    double* T[2] = {h.T0, h.T1};
+    double* Q[2] = {h.Q0, h.Q1};
+    return run_series<EK>(p, T, Q, 1, g, st);
 }
 
 template <int EK>
@@ -530,11 +508,47 @@ hipError_t gemv_as(const HeatGemv& g, hipStream_t st) {
 
 }  // namespace
 
-int heat_cheb_iters(double beta, double tol) {
-    if (!(beta > 1.0)) return 0;
-    const double sk = sqrt(beta);
-    const double c = (sk - 1.0) / (sk + 1.0);
-    return (int)ceil(log(0.5 * tol) / log(c));
+// The Chebyshev coefficients of x^-L on [1, beta] (x = theta + delta u), down
+// to a tail of `tol` of the largest value f(1) = 1.  f' = -L f / x gives them
+// the three-term recurrence
+//   delta (k - 1 + L) c_{k-1} + 2 theta k c_k + delta (k + 1 - L) c_{k+1} = 0,
+// of which they are the decaying solution: they are run backwards from a
+// degree far in the tail (Miller's algorithm) and scaled so that the series
+// is 1 at x = 1, where its terms (-1)^k c_k are all positive.
+HeatSeries heat_series(double beta, int L, double tol) try {
+    HeatSeries out;
+    if (!(beta > 1.0)) {
+        out.c = {2.0};   // M is the identity
+        return out;
+    }
+    const double theta = 0.5 * (beta + 1.0), delta = 0.5 * (beta - 1.0);
+    const double rho = (sqrt(beta) + 1.0) / (sqrt(beta) - 1.0);   // the terms' final ratio
+    constexpr double kMost = (double)(1 << 28);   // far beyond a degree that could be run
+    if (!(45.0 / log(rho) < kMost)) return out;
+    int64_t K = (int64_t)(45.0 / log(rho)) + 16 + 4 * (int64_t)L;
+    std::vector<double> d;   // (-1)^k c_k
+    double sum = 0.0;
+    for (;;) {
+        d.assign((size_t)K + 2, 0.0);
+        d[(size_t)K] = 1e-200;
+        for (int64_t k = K; k > 0; --k) {
+            d[(size_t)k - 1] = (2.0 * theta * (double)k * d[(size_t)k] - delta * (double)(k + 1 - L) * d[(size_t)k + 1]) /
+                               (delta * (double)(k - 1 + L));
+            if (d[(size_t)k - 1] > 1e150)   // (what is scaled out of range is far below the tail)
+                for (int64_t q = k - 1; q <= K; ++q) d[(size_t)q] *= 1e-150;
+        }
+        sum = 0.5 * d[0];
+        for (int64_t k = 1; k <= K; ++k) sum += d[(size_t)k];
+        if (d[(size_t)K] <= 1e-25 * sum) break;
+        if ((K *= 2) > (int64_t)kMost) return out;
+    }
+    double tail = 0.0;
+    while (K > 0 && tail + d[(size_t)K] <= tol * sum) tail += d[(size_t)K--];
+    out.c.resize((size_t)K + 1);
+    for (int64_t k = 0; k <= K; ++k) out.c[(size_t)k] = ((k & 1) ? -d[(size_t)k] : d[(size_t)k]) / sum;
+    return out;
+} catch (const std::bad_alloc&) {
+    return HeatSeries{};   // (no exception leaves the C entry points)
 }
 
 int64_t heat_build_scratch(int64_t N) { return 4 * N * ((int64_t)1 << chunk_log2(N)); }
@@ -542,37 +556,24 @@ int64_t heat_build_scratch(int64_t N) { return 4 * N * ((int64_t)1 << chunk_log2
 hipError_t heat_build_operator(const uint8_t* mask, int n0, int n1, double gamma, int L, const int32_t* cidx,
                                const int32_t* gidx, int64_t nf, float* A, double* scratch, hipStream_t st) {
     const int64_t N = (int64_t)n0 * n1;
-    const int64_t ld = heat_ld(nf);
-    const int logC = chunk_log2(N);
-    const int64_t C = (int64_t)1 << logC;
-    const double nu0 = n0 > 1 ? gamma * (double)n0 * n0 / L : 0.0;
-    const double nu1 = n1 > 1 ? gamma * (double)n1 * n1 / L : 0.0;
-    const double beta = 1.0 + 4.0 * (nu0 + nu1);
-    const int K = heat_cheb_iters(beta, 1e-14);
-    const double theta = 0.5 * (beta + 1.0), delta = 0.5 * (beta - 1.0);
     hipLaunchKernelGGL(k_heat_zero, dim3(grid_for(heat_operator_floats(nf))), dim3(256), 0, st, A,
                        heat_operator_floats(nf));
-    double* X = scratch;
-    double* R = X + N * C;
-    double* D[2] = {R + N * C, R + 2 * N * C};
-    const int gb = grid_for(N * C);
-    for (int64_t j0 = 0; j0 < ld; j0 += C) {
-        hipLaunchKernelGGL(k_heat_unit, dim3(gb), dim3(256), 0, st, X, gidx, nf, N, logC, j0);
-        for (int l = 0; l < L && K > 0; ++l) {
-            // solve M x = X from the first guess X
-            hipLaunchKernelGGL(k_heat_cheb_init, dim3(gb), dim3(256), 0, st, X, R, D[0], mask, N, logC, n0, n1,
-                               nu0, nu1, 1.0 / theta);
-            const double sigma1 = theta / delta;
-            double rho = 1.0 / sigma1;
-            for (int k = 0; k < K; ++k) {
-                const double rho_n = 1.0 / (2.0 * sigma1 - rho);
-                hipLaunchKernelGGL(k_heat_cheb_step, dim3(gb), dim3(256), 0, st, X, R, D[k & 1], D[(k + 1) & 1],
-                                   mask, N, logC, n0, n1, nu0, nu1, rho_n * rho, 2.0 * rho_n / delta);
-                rho = rho_n;
-            }
-        }
-        hipLaunchKernelGGL(k_heat_store, dim3(gb), dim3(256), 0, st, X, A, cidx, N, logC, ld, j0);
-        const hipError_t e = hipGetLastError();
+    SeriesPlan p = series_plan(n0, n1, gamma, L);
+    // columns per chunk: T and Q twice each, and Y
+    const int64_t C = std::max<int64_t>(1, 4 * ((int64_t)1 << chunk_log2(N)) / 5);
+    p.a.mask = mask;
+    p.a.cidx = cidx;
+    p.a.gidx = gidx;
+    p.a.unit = 1;
+    p.a.A = A;
+    p.a.nT = heat_ntiles(nf);
+    p.a.stride = N;
+    p.a.Y = scratch;
+    double* T[2] = {scratch + N * C, scratch + 2 * N * C};
+    double* Q[2] = {scratch + 3 * N * C, scratch + 4 * N * C};
+    for (int64_t j0 = 0; j0 < nf; j0 += C) {
+        p.a.j0 = j0;
+        const hipError_t e = run_series<HEAT_DST_OPERATOR>(p, T, Q, (unsigned)std::min(C, nf - j0), HeatGemv{}, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -615,13 +616,13 @@ hipError_t launch_heat_fill(float* x, float v, int64_t n, int64_t ld, hipStream_
 
 hipError_t launch_heat_sums(const double* errrow, int64_t ne, const float* p, int64_t np, double* out,
                             hipStream_t st) {
-    hipLaunchKernelGGL(k_heat_sums, dim3(1), dim3(256), 0, st, errrow, ne, p, np, out);
+    hipLaunchKernelGGL(k_heat_sums, dim3(1), dim3(1024), 0, st, errrow, ne, p, np, out);
     return hipGetLastError();
 }
 
 hipError_t launch_heat_input(const float* p, const uint8_t* mask, const float* kappa, float kappa_s, int64_t N,
                              double* out, hipStream_t st) {
-    hipLaunchKernelGGL(k_heat_input, dim3(1), dim3(256), 0, st, p, mask, kappa, kappa_s, N, out);
+    hipLaunchKernelGGL(k_heat_input, dim3(1), dim3(1024), 0, st, p, mask, kappa, kappa_s, N, out);
     return hipGetLastError();
 }
 
