@@ -150,7 +150,7 @@ int part_cap_of(const Geo& g) {
         int64_t outer = 1, inner = 1;
         for (int j = 0; j < k; ++j) outer *= g.n[j];
         for (int j = k + 1; j < g.d; ++j) inner *= g.n[j];
-        cap = std::max<int64_t>(cap, log_pass_blocks(make_log_pass(outer, g.n[k], inner, 0, 1.0, nullptr)));
+        cap = std::max<int64_t>(cap, log_pass_blocks(make_log_pass(outer, g.n[k], inner, 1.0, nullptr)));
     }
     return (int)cap;
 }
@@ -405,7 +405,7 @@ jko_status apply_xi_log(const Plan& P, const float* x, EpiArgs epi, int* nblocks
         int64_t outer = 1, inner = 1;
         for (int j = 0; j < k; ++j) outer *= P.g.n[j];
         for (int j = k + 1; j < P.g.d; ++j) inner *= P.g.n[j];
-        const LogPass L = make_log_pass(outer, P.g.n[k], inner, P.W[k], P.gamma, in);
+        const LogPass L = make_log_pass(outer, P.g.n[k], inner, P.gamma, in);
         const bool last = i + 1 == na;
         EpiArgs e = epi;
         if (!last) {

@@ -12,16 +12,16 @@ namespace jko {
 struct LogPass {
     int64_t outer, inner;
     int n;
-    int W;                 // float32 band half-width of the factor (where the max search starts)
+    int R0;                // distance the max search starts with
     double alpha;
     const float* X;
-    int F;                 // fibres staged per block
-    int TI;                // outputs per block along the axis
-    int chunks;            // blocks per fibre group
-    int64_t fibre_blocks;  // fibre groups
+    int OI, OF;            // outputs along the axis and fibres of a work item
+    int T;                 // contiguous axis: threads staging a fibre
+    int chunks;            // items per group of fibres
+    int64_t items;
 };
 
-LogPass make_log_pass(int64_t outer, int n, int64_t inner, int W, double gamma, const float* X);
+LogPass make_log_pass(int64_t outer, int n, int64_t inner, double gamma, const float* X);
 int64_t log_pass_blocks(const LogPass& L);
 // Every epilogue but the adjoint's; partial sums go to slot blockIdx (at most epi.part.cap blocks).
 hipError_t launch_log_pass(const LogPass& L, const EpiArgs& epi, int* nblocks, hipStream_t st);
