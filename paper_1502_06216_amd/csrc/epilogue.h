@@ -339,9 +339,11 @@ __device__ __forceinline__ EpiIn epi_prefetch(const EpiArgs& E, int idx, int cnt
 // Log domain: the same with b, a held as log b, log a.
 // COH: b (b-update) and a (prox) are stored with device-scope stores.
 // NE: elements of `val` computed (cnt <= NE); 1 for one output per lane.
-template <int EK, bool COH = false, int NE = 4>
+// LDS (NE = 1): the b-update's b or the proximal step's a goes to *lds instead.
+template <int EK, bool COH = false, int NE = 4, bool LDS = false>
 __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4 val, bool logx,
-                                          const EpiIn& in, EpiAcc& acc) {
+                                          const EpiIn& in, EpiAcc& acc, float* lds = nullptr) {
+    static_assert(!LDS || NE == 1, "one output per lane");
     if (cnt <= 0) return;
     const bool vec = E.vec_ok && ((idx & 3) == 0);
     if (EK == EK_STORE) {
@@ -365,7 +367,8 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
                 }
             }
         }
-        if (COH) st4_coh(E.b, idx, cnt, vec, bn);
+        if (LDS) *lds = bn[0];
+        else if (COH) st4_coh(E.b, idx, cnt, vec, bn);
         else st4(E.b, idx, cnt, vec, bn);
         if (E.t_out) st4(E.t_out, idx, cnt, vec, val);
     } else if (EK == EK_ADJ_B) {
@@ -435,7 +438,8 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
             }
             if (E.check && e < cnt) acc.mass += (double)pn[e];
         }
-        if (COH) st4_coh(E.a, idx, cnt, vec, an);
+        if (LDS) *lds = an[0];
+        else if (COH) st4_coh(E.a, idx, cnt, vec, an);
         else st4(E.a, idx, cnt, vec, an);
         if (E.write_p) st4(E.p_out, idx, cnt, vec, pn);
         if (E.s_out) st4(E.s_out, idx, cnt, vec, val);

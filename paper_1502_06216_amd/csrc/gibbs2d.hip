@@ -38,6 +38,7 @@
 #include "control.h"
 #include "epilogue.h"
 #include "resident_sync.h"
+#include "tilefrag.h"
 
 namespace jko {
 
@@ -337,48 +338,11 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     // ---- Z = X K1_1^T over the halo rows
     const int F = LIp / 16;
     // one 16 x 16 fragment of Z: halo rows 16 f.., output columns 16 c..
+    const int k8 = SPLIT ? 8 * (lane >> 4) : koff;   // the lane's first k
     auto zfrag = [&](int f, int c) -> f4 {
-        if (SPLIT) {
-            const int k8 = 8 * (lane >> 4);
-            f4 acc = f4{0.f, 0.f, 0.f, 0.f};
-            const float* xr = &S.Xs[(16 * f + (lane & 15)) * kS + k8];
-            const uint16_t* khr = &S.Kjh[(16 * c + (lane & 15)) * kS2 + k8];
-            const uint16_t* klr = &S.Kjl[(16 * c + (lane & 15)) * kS2 + k8];
-            for (int c0 = 0; c0 < LJp; c0 += 32) {
-                bf8 ah, al;
-                split_bf16(*reinterpret_cast<const f4*>(xr + c0), *reinterpret_cast<const f4*>(xr + c0 + 4), ah, al);
-                const bf8 bh = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(khr + c0));
-                const bf8 bl = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(klr + c0));
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
-            }
-            return acc;
-        } else {
-            // even and odd k-chunks go to two accumulators (independent MFMA chains)
-            f4 acc0 = f4{0.f, 0.f, 0.f, 0.f}, acc1 = f4{0.f, 0.f, 0.f, 0.f};
-            const float* xr = &S.Xs[(16 * f + (lane & 15)) * kS + koff];
-            const float* kr = &S.Kj[(16 * c + (lane & 15)) * kS + koff];
-            int c0 = 0;
-            for (; c0 + 16 < LJp; c0 += 32) {
-                const f4 a0 = *reinterpret_cast<const f4*>(xr + c0);
-                const f4 b0 = *reinterpret_cast<const f4*>(kr + c0);
-                const f4 a1 = *reinterpret_cast<const f4*>(xr + c0 + 16);
-                const f4 b1 = *reinterpret_cast<const f4*>(kr + c0 + 16);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], b0[s], acc0, 0, 0, 0);
-                    acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[s], b1[s], acc1, 0, 0, 0);
-                }
-            }
-            if (c0 < LJp) {
-                const f4 a0 = *reinterpret_cast<const f4*>(xr + c0);
-                const f4 b0 = *reinterpret_cast<const f4*>(kr + c0);
-#pragma unroll
-                for (int s = 0; s < 4; ++s) acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[s], b0[s], acc0, 0, 0, 0);
-            }
-            return acc0 + acc1;
-        }
+        const int kc = 16 * c + (lane & 15);
+        return z_frag<SPLIT>(&S.Xs[(16 * f + (lane & 15)) * kS + k8], SPLIT ? nullptr : &S.Kj[kc * kS + k8],
+                             SPLIT ? &S.Kjh[kc * kS2 + k8] : nullptr, SPLIT ? &S.Kjl[kc * kS2 + k8] : nullptr, LJp);
     };
     // acc holds Z[ib = 16 f + koff + e][j = 16 c + (lane & 15)]
     if (TT == 16) {
@@ -407,23 +371,9 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     // ---- Y^T = Z^T K1_0^T: each 16 x 16 output block (column fragment jf,
     // row fragment if) over its k-chunks
     auto yfrag = [&](int jf, int ifr, int c0, f4 acc) -> f4 {
-        if (SPLIT) {
-            const int k = c0 + 8 * (lane >> 4);
-            bf8 ah, al;
-            const float* zr = &Zs[(16 * jf + (lane & 15)) * kS + k];
-            split_bf16(*reinterpret_cast<const f4*>(zr), *reinterpret_cast<const f4*>(zr + 4), ah, al);
-            const bf8 bh = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(&S.Kih[(16 * ifr + (lane & 15)) * kS2 + k]));
-            const bf8 bl = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(&S.Kil[(16 * ifr + (lane & 15)) * kS2 + k]));
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
-        } else {
-            const f4 a = *reinterpret_cast<const f4*>(&Zs[(16 * jf + (lane & 15)) * kS + c0 + koff]);
-            const f4 b = *reinterpret_cast<const f4*>(&S.Ki[(16 * ifr + (lane & 15)) * kS + c0 + koff]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
-        }
-        return acc;
+        const int k = c0 + k8, ki = 16 * ifr + (lane & 15);
+        return y_chunk<SPLIT>(&Zs[(16 * jf + (lane & 15)) * kS + k], SPLIT ? nullptr : &S.Ki[ki * kS + k],
+                              SPLIT ? &S.Kih[ki * kS2 + k] : nullptr, SPLIT ? &S.Kil[ki * kS2 + k] : nullptr, acc);
     };
     constexpr int KC = SPLIT ? 32 : 16;   // k per chunk
     f4 acc = f4{0.f, 0.f, 0.f, 0.f};
@@ -877,6 +827,7 @@ bool resident2d_fits(int n0, int n1, int W0, int W1, int prox_kind, int32_t prec
 }
 
 hipError_t launch_resident2d(const Resident2D& r, hipStream_t stream) {
+    if (r.B.tile == 16 && small2d_fits(r.B.n0, r.B.n1, r.B.W0, r.B.W1, r.split != 0)) return launch_small2d(r, stream);
     const int64_t nb = gibbs2d_blocks(r.B.n0, r.B.n1, r.B.tile);
     Resident2D arg = r;
     void* args[] = {&arg};

@@ -225,6 +225,10 @@ hipError_t launch_resident_adj(const ResidentAdj& r, hipStream_t stream);
 bool resident2d_fits(int n0, int n1, int W0, int W1, int prox_kind, int32_t precision, int tile);
 hipError_t launch_resident2d(const Resident2D& r, hipStream_t stream);
 
+// The same on a small grid in one block (small2d.hip): no other block to wait for.
+bool small2d_fits(int n0, int n1, int W0, int W1, bool split);
+hipError_t launch_small2d(const Resident2D& r, hipStream_t stream);
+
 // A whole 2D step in one cooperative launch with every application of xi
 // as the two rotating panel passes (axis 1 into the transposed intermediate
 // u, then axis 0 with the epilogue), for bands up to seven 32-k panels: block

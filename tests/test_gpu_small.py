@@ -1,0 +1,37 @@
+"""The one-block form of the resident 2D kernel (grids of at most 16 tiles of
+16 x 16) against the launch-per-application path: the same tile arithmetic and
+order of sums, so the same bits, on grids at the edges of its tiles, chunks and
+selection (the last two are beyond it in FP32)."""
+import pytest
+import torch
+
+import paper_1502_06216_amd as jk
+from workloads import small_case
+
+from _util import banner, dev, energies
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("iters", "absorptions", "stop", "status", "marginal_l1", "mass", "max_abs_log_a", "max_abs_log_b")
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("shape,width", [((16, 16), 2.0), ((15, 7), 2.0), ((17, 33), 3.0), ((1, 250), 3.0),
+                                         ((250, 1), 3.0), ((64, 64), 1.4), ((48, 63), 4.0), ((64, 64), 5.0),
+                                         ((16, 256), 6.0)])
+def test_step_and_gradient_same_bits(shape, width, precision):
+    banner(f"small grid {shape} width={width} {precision}")
+    gamma = (width / max(shape)) ** 2
+    wl = small_case(shape, "congestion", seed=6, gamma=gamma, tau=2.5 * gamma, n_boxes=0)
+    en, _ = energies(wl)
+    out = []
+    for resident in (True, False):
+        kw = dict(precision=precision, resident=resident)
+        p, st = jk.step(dev(wl.p0), en, wl.gamma, wl.tau, max_iters=23, check_every=4, absorb_threshold=60.0, **kw)
+        _, _, ck = jk.flow(dev(wl.p0), en, wl.gamma, wl.tau, 2, max_iters=5, checkpoints=True, **kw)
+        gw, gp = jk.backward(ck, [5, 5], dev(wl.w), en, wl.gamma, wl.tau, **kw)
+        out.append(((p, ck, gw, gp), st))
+    for a, b in zip(out[0][0], out[1][0]):
+        assert torch.equal(a, b), f"max |diff| {float((a - b).abs().max()):.3e}"
+    for k in KEYS:
+        assert out[0][1][k] == out[1][1][k], k
