@@ -37,6 +37,7 @@
 
 #include "control.h"
 #include "epilogue.h"
+#include "panel.h"
 #include "resident_sync.h"
 #include "tilefrag.h"
 
@@ -70,7 +71,8 @@ struct Smem {
     // every array starts on a 16-byte boundary (the unused one-element arrays
     // of the other precision would otherwise shift the rest by 8 bytes and
     // split the 16-byte LDS accesses)
-    alignas(16) float Xs[H * S];                   // [ib][jb]
+    // [ib][jb], and room for the end of the halo's last 1 KiB copy
+    alignas(16) float Xs[(H * S + 255) / 256 * 256];
     alignas(16) float Kj[SPLIT ? 1 : TT * S];      // [j][jb]  = K1_1[j0+j][jb0+jb]
     alignas(16) float Ki[SPLIT ? 1 : TT * S];      // [i][ib]  = K1_0[i0+i][ib0+ib]
     alignas(16) uint16_t Kjh[SPLIT ? TT * S2 : 1];   // split: bfloat16 hi / lo of the bands
@@ -147,19 +149,12 @@ template <int TT> constexpr int band_units() {   // max factor-band units per th
     return (TT * (Geom<TT>::kHalo / 4) + kThr - 1) / kThr;
 }
 
-// Issue the loads of the X halo (zero outside the grid).  COH: device-scope
-// loads (buffer loads with scope bit SC1, range-checked by the descriptor) of
-// a field other blocks of the same launch wrote.
-constexpr int kCpolDevice = 16;   // SC1: device scope
-
-template <int TT, bool COH = false>
+// Issue the loads of the X halo (zero outside the grid).
+template <int TT>
 __device__ __forceinline__ void load_halo(const Band2D& B, const Tile<TT>& T, f4 (&bx)[halo_units<TT>()]) {
     const int tid = threadIdx.x;
     const int nux = T.LIp * (T.LJp / 4);
     const bool vec1 = (B.n1 & 3) == 0;
-    __amdgpu_buffer_rsrc_t rs;
-    if (COH)
-        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B.X), (short)0, B.n0 * B.n1 * 4, 0x00020000);
 #pragma unroll
     for (int u = 0; u < halo_units<TT>(); ++u) {
         const int unit = tid + u * kThr;
@@ -167,27 +162,58 @@ __device__ __forceinline__ void load_halo(const Band2D& B, const Tile<TT>& T, f4
         if (unit < nux) {
             const int r = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
             if (r < T.LI) {
-                const int off = (T.ib0 + r) * B.n1 + T.jb0 + c;
-                if (COH) {
-                    if (vec1 && c + 3 < T.LJ)
-                        v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs, 4 * off, 0, kCpolDevice));
-                    else
+                const float* src = B.X + (T.ib0 + r) * B.n1 + T.jb0 + c;
+                if (vec1 && c + 3 < T.LJ) v = *reinterpret_cast<const f4*>(src);
+                else
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            v[e] = (c + e < T.LJ) ? __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                                                                  rs, 4 * (off + e), 0, kCpolDevice))
-                                                  : 0.f;
-                } else {
-                    const float* src = B.X + off;
-                    if (vec1 && c + 3 < T.LJ) v = *reinterpret_cast<const f4*>(src);
-                    else
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = (c + e < T.LJ) ? src[e] : 0.f;
-                }
+                    for (int e = 0; e < 4; ++e) v[e] = (c + e < T.LJ) ? src[e] : 0.f;
             }
         }
         bx[u] = v;
     }
+}
+
+// The resident kernels' halo: buffer loads that write LDS directly (16 bytes
+// per lane, 1 KiB per wave), device-scope (SC1) because other blocks of the
+// launch wrote the field.  A row is LJp / 4 chunks and one chunk of padding,
+// so that consecutive chunks are consecutive in LDS and 16 rows read at once
+// fall in distinct banks.  Each lane's offsets are fixed for the launch:
+// beyond the halo, and in the padding, they lie past the buffer and read
+// zeros.  A 16-byte load needs dword alignment only, so rows of any length
+// are loaded whole; where the last chunk of a row reaches past the grid's edge
+// its last elements are the next row's first and meet exact zeros of the
+// factor.  256 x 256, cycles of a phase from the wait's end to the halo in
+// LDS: 3016 by way of registers (its addresses divided out anew, then written
+// to LDS), 1347 so; 201 x 161, whose rows were loaded float by float:
+// 4754, 1351 so.
+template <int TT> constexpr int halo_copies() {   // max 1 KiB copies per wave
+    return (Geom<TT>::kHalo * (Geom<TT>::kHalo / 4 + 1) + kThr - 1) / kThr;
+}
+constexpr int kPastBuffer = 0x7ffffff0;
+
+template <int TT>
+__device__ __forceinline__ void halo_offsets(const Band2D& B, const Tile<TT>& T, int (&off)[halo_copies<TT>()]) {
+    const int cols = T.LJp / 4 + 1;
+#pragma unroll
+    for (int u = 0; u < halo_copies<TT>(); ++u) {
+        const int unit = threadIdx.x + u * kThr;
+        const int r = unit / cols, c = 4 * (unit % cols);
+        off[u] = (r < T.LI && c < T.LJ) ? 4 * ((T.ib0 + r) * B.n1 + T.jb0 + c) : kPastBuffer;
+    }
+}
+
+template <int TT>
+__device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, const int (&off)[halo_copies<TT>()],
+                                          float* Xs) {
+    // (the field's own allocation is a multiple of 256 bytes long)
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B.X), (short)0, (B.n0 * B.n1 * 4 + 15) & ~15, kBufRsrcWord3);
+    const int wave = threadIdx.x >> 6;
+    const int units = T.LIp * (T.LJp / 4 + 1);
+#pragma unroll
+    for (int u = 0; u < halo_copies<TT>(); ++u)
+        if (wave * 64 + u * kThr < units) lds_copy16<kCpolCoherent>(rs, Xs + 4 * (wave * 64 + u * kThr), off[u]);
+    wait_vm_n<0>();
 }
 
 template <int TT, bool SPLIT>
@@ -325,8 +351,9 @@ __device__ __forceinline__ void stage_bands(const Band2D& B, const Tile<TT>& T, 
 // takes over.  The second contraction is one fragment per 16 x 16 output
 // block, its k range cut into 16-wide (FP32) or 32-wide (split) chunks spread
 // over the waves; the per-wave partial sums are added in a fixed order.
+// xs: floats per staged row of X.
 template <int TT, int EK, bool COH = false, bool SPLIT = false>
-__device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& T,
+__device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& T, int xs,
                                               const EpiIn (&ein)[Geom<TT>::kOut], Smem<TT, SPLIT>& S, int slot) {
     constexpr int kS = Smem<TT, SPLIT>::S, kS2 = Smem<TT, SPLIT>::S2;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -341,7 +368,7 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     const int k8 = SPLIT ? 8 * (lane >> 4) : koff;   // the lane's first k
     auto zfrag = [&](int f, int c) -> f4 {
         const int kc = 16 * c + (lane & 15);
-        return z_frag<SPLIT>(&S.Xs[(16 * f + (lane & 15)) * kS + k8], SPLIT ? nullptr : &S.Kj[kc * kS + k8],
+        return z_frag<SPLIT>(&S.Xs[(16 * f + (lane & 15)) * xs + k8], SPLIT ? nullptr : &S.Kj[kc * kS + k8],
                              SPLIT ? &S.Kjh[kc * kS2 + k8] : nullptr, SPLIT ? &S.Kjl[kc * kS2 + k8] : nullptr, LJp);
     };
     // acc holds Z[ib = 16 f + koff + e][j = 16 c + (lane & 15)]
@@ -444,7 +471,7 @@ gibbs2d_kernel(Band2D B, EpiArgs E) {
     stage_bands<TT>(B, T, S);
     store_halo<TT, SPLIT>(S, T, bx);
     if (done) return;   // the step has stopped: nothing to compute (uniform)
-    contract_tile<TT, EK, false, SPLIT>(E, T, ein, S, (int)blockIdx.x);
+    contract_tile<TT, EK, false, SPLIT>(E, T, Smem<TT, SPLIT>::S, ein, S, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------ resident kernel
@@ -507,6 +534,8 @@ resident2d(Resident2D R) {
 
     // factor bands: staged once for the whole launch
     stage_bands<TT>(B, T, S);
+    int off[halo_copies<TT>()];
+    halo_offsets<TT>(B, T, off);
     // epilogue inputs that do not change over the iteration (q; the energy's fields)
     EpiIn inq[NO], inp[NO];
 #pragma unroll
@@ -529,10 +558,8 @@ resident2d(Resident2D R) {
         E.check = CHK ? 1 : 0;
         if (EKv >= EK_PROX) E.write_p = CHK ? 1 : 0;
         B.X = X;
-        f4 bx[halo_units<TT>()];
-        load_halo<TT, true>(B, T, bx);
-        store_halo<TT, SPLIT>(S, T, bx);
-        contract_tile<TT, EKv, true, SPLIT>(E, T, in, S, slot);
+        copy_halo<TT>(B, T, off, S.Xs);
+        contract_tile<TT, EKv, true, SPLIT>(E, T, T.LJp + 4, in, S, slot);
     };
     const std::integral_constant<int, EK_BUPDATE> ekb;
     const std::integral_constant<int, PK> ekp;
@@ -643,6 +670,8 @@ resident_adj(ResidentAdj R) {
     const Tile<TT> T = tile_of<TT, SPLIT>(B, logical, lane);
     if (tid == 0) n_nbr = neighbours_of<TT>(B, logical, nb, nbr);
     stage_bands<TT>(B, T, S);
+    int off[halo_copies<TT>()];
+    halo_offsets<TT>(B, T, off);
     EpiArgs eb{};
     eb.kind = EpiKind::ADJ_B;
     eb.q = R.q;
@@ -665,13 +694,9 @@ resident_adj(ResidentAdj R) {
 #pragma unroll
         for (int u = 0; u < NO; ++u) ia[u] = epi_prefetch<EK_ADJ_B, true>(eb, T.eidx[u], T.ecnt[u]);
         if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
-        {
-            B.X = R.sbar;
-            f4 bx[halo_units<TT>()];
-            load_halo<TT, true>(B, T, bx);
-            store_halo<TT, SPLIT>(S, T, bx);
-        }
-        contract_tile<TT, EK_ADJ_B, true, SPLIT>(eb, T, ia, S, slot);
+        B.X = R.sbar;
+        copy_halo<TT>(B, T, off, S.Xs);
+        contract_tile<TT, EK_ADJ_B, true, SPLIT>(eb, T, T.LJp + 4, ia, S, slot);
         publish(R.sync, slot, ++count);
         if (k == 1) break;
         ep.hin = R.hist + (2 * (int64_t)(k - 2) + 1) * R.hist_stride;
@@ -679,13 +704,9 @@ resident_adj(ResidentAdj R) {
 #pragma unroll
         for (int u = 0; u < NO; ++u) ip[u] = epi_prefetch<AK, true>(ep, T.eidx[u], T.ecnt[u]);
         if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
-        {
-            B.X = R.tbar;
-            f4 bx[halo_units<TT>()];
-            load_halo<TT, true>(B, T, bx);
-            store_halo<TT, SPLIT>(S, T, bx);
-        }
-        contract_tile<TT, AK, true, SPLIT>(ep, T, ip, S, slot);
+        B.X = R.tbar;
+        copy_halo<TT>(B, T, off, S.Xs);
+        contract_tile<TT, AK, true, SPLIT>(ep, T, T.LJp + 4, ip, S, slot);
         publish(R.sync, slot, ++count);
     }
 }
