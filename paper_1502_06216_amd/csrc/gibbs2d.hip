@@ -80,6 +80,7 @@ struct Smem {
     alignas(16) uint16_t Kih[SPLIT ? TT * S2 : 1];
     alignas(16) uint16_t Kil[SPLIT ? TT * S2 : 1];
     alignas(16) float Zown[Geom<TT>::kAliasZ ? 1 : TT * S];   // [j][ib]
+    alignas(16) float Zodd[Geom<TT>::kAliasZ || SPLIT ? 1 : TT * S];   // FP32: the odd k-chunks' share of Z
     alignas(16) float red[8 * 4 * kRS];            // [wave][element][lane] partial sums of the second contraction
     double shd[8];
     __device__ float* Z() { return Geom<TT>::kAliasZ ? Xs : Zown; }
@@ -208,7 +209,7 @@ __device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, co
     // (the field's own allocation is a multiple of 256 bytes long)
     const __amdgpu_buffer_rsrc_t rs =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B.X), (short)0, (B.n0 * B.n1 * 4 + 15) & ~15, kBufRsrcWord3);
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int units = T.LIp * (T.LJp / 4 + 1);
 #pragma unroll
     for (int u = 0; u < halo_copies<TT>(); ++u)
@@ -356,7 +357,7 @@ template <int TT, int EK, bool COH = false, bool SPLIT = false>
 __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& T, int xs,
                                               const EpiIn (&ein)[Geom<TT>::kOut], Smem<TT, SPLIT>& S, int slot) {
     constexpr int kS = Smem<TT, SPLIT>::S, kS2 = Smem<TT, SPLIT>::S2;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int koff = 4 * (lane >> 4);
     const int LIp = T.LIp, LJp = T.LJp;
     float* const Zs = S.Z();
@@ -372,7 +373,22 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
                              SPLIT ? &S.Kjh[kc * kS2 + k8] : nullptr, SPLIT ? &S.Kjl[kc * kS2 + k8] : nullptr, LJp);
     };
     // acc holds Z[ib = 16 f + koff + e][j = 16 c + (lane & 15)]
-    if (TT == 16) {
+    constexpr bool HALVES = TT == 16 && !SPLIT;
+    if constexpr (HALVES) {
+        // FP32: the even and the odd k-chunks of each fragment are units of
+        // their own, so that the four SIMDs carry the same share (12 units for
+        // a halo of 96 rows, where six whole fragments leave two SIMDs half
+        // idle); the second contraction adds the two as it reads them
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int u = wave + 8 * m, half = u >= F ? 1 : 0, f = u - (half ? F : 0);
+            if (u < 2 * F) {
+                const f4 acc = z_half(&S.Xs[(16 * f + (lane & 15)) * xs + k8], &S.Kj[(lane & 15) * kS + k8], 16 * half,
+                                      LJp);
+                *reinterpret_cast<f4*>(&(half ? S.Zodd : Zs)[(lane & 15) * kS + 16 * f + koff]) = acc;
+            }
+        }
+    } else if (TT == 16) {
         if (wave < F) {
             const f4 acc = zfrag(wave, 0);
             *reinterpret_cast<f4*>(&Zs[(lane & 15) * kS + 16 * wave + koff]) = acc;
@@ -400,7 +416,8 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     auto yfrag = [&](int jf, int ifr, int c0, f4 acc) -> f4 {
         const int k = c0 + k8, ki = 16 * ifr + (lane & 15);
         return y_chunk<SPLIT>(&Zs[(16 * jf + (lane & 15)) * kS + k], SPLIT ? nullptr : &S.Ki[ki * kS + k],
-                              SPLIT ? &S.Kih[ki * kS2 + k] : nullptr, SPLIT ? &S.Kil[ki * kS2 + k] : nullptr, acc);
+                              SPLIT ? &S.Kih[ki * kS2 + k] : nullptr, SPLIT ? &S.Kil[ki * kS2 + k] : nullptr, acc,
+                              HALVES ? &S.Zodd[(16 * jf + (lane & 15)) * kS + k] : nullptr);
     };
     constexpr int KC = SPLIT ? 32 : 16;   // k per chunk
     f4 acc = f4{0.f, 0.f, 0.f, 0.f};
@@ -503,7 +520,7 @@ resident2d(Resident2D R) {
     __shared__ int nbr[kMaxNeighbours];
     __shared__ int all[kFusedMaxBlocks];
     __shared__ int n_nbr;
-    __shared__ uint32_t okw, word;
+    __shared__ uint32_t okw, word, failed;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int nb = (int)gridDim.x;
@@ -515,6 +532,7 @@ resident2d(Resident2D R) {
     if (tid == 0) {
         n_nbr = neighbours_of<TT>(B, logical, nb, nbr);
         C = *R.ctl;
+        failed = 0;
     }
     for (int t = tid; t < nb; t += kThr) all[t] = t;
 
@@ -574,7 +592,7 @@ resident2d(Resident2D R) {
             ia[u] = inq[u];
             if (chk) ia[u].v = ld4_coh(R.b, T.eidx[u], T.ecnt[u], 0.f);
         }
-        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         if (chk) phase(ekb, yes(), eb, ia, R.a);
         else phase(ekb, no(), eb, ia, R.a);
         publish(R.sync, slot, ++count);
@@ -591,7 +609,7 @@ resident2d(Resident2D R) {
         uint32_t decision = 0;
         if (chk) {
             if (slot == 0) {
-                if (!wait_for(R.sync, nb, all, count, R.spin_limit)) return;
+                if (!wait_for(R.sync, nb, all, count, R.spin_limit, &failed)) return;
                 if ((tid >> 6) == 0) ctl_update<true>(&C, R.part, nb, k, R.tol, 1, R.absorb, R.a_only);
                 __syncthreads();
                 if (tid == 0) {
@@ -625,7 +643,7 @@ resident2d(Resident2D R) {
         // ---- s = xi b, p = prox(s), a = p / s (p kept at candidate iterations)
         const bool cand = (R.checks && k % R.ce == 0) || k == R.K;
         ep.s_out = R.hist ? R.hist + (2 * (int64_t)(k - 1) + 1) * R.hist_stride : nullptr;
-        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         if (cand) phase(ekp, yes(), ep, inp, R.b);
         else phase(ekp, no(), ep, inp, R.b);
         publish(R.sync, slot, ++count);
@@ -661,6 +679,7 @@ resident_adj(ResidentAdj R) {
     __shared__ __attribute__((aligned(16))) Smem<TT, SPLIT> S;
     __shared__ int nbr[kMaxNeighbours];
     __shared__ int n_nbr;
+    __shared__ uint32_t failed;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int nb = (int)gridDim.x;
@@ -668,7 +687,10 @@ resident_adj(ResidentAdj R) {
     Band2D B = R.B;
     const int logical = xcd_block();
     const Tile<TT> T = tile_of<TT, SPLIT>(B, logical, lane);
-    if (tid == 0) n_nbr = neighbours_of<TT>(B, logical, nb, nbr);
+    if (tid == 0) {
+        n_nbr = neighbours_of<TT>(B, logical, nb, nbr);
+        failed = 0;
+    }
     stage_bands<TT>(B, T, S);
     int off[halo_copies<TT>()];
     halo_offsets<TT>(B, T, off);
@@ -693,7 +715,7 @@ resident_adj(ResidentAdj R) {
         EpiIn ia[NO];
 #pragma unroll
         for (int u = 0; u < NO; ++u) ia[u] = epi_prefetch<EK_ADJ_B, true>(eb, T.eidx[u], T.ecnt[u]);
-        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         B.X = R.sbar;
         copy_halo<TT>(B, T, off, S.Xs);
         contract_tile<TT, EK_ADJ_B, true, SPLIT>(eb, T, T.LJp + 4, ia, S, slot);
@@ -703,7 +725,7 @@ resident_adj(ResidentAdj R) {
         EpiIn ip[NO];
 #pragma unroll
         for (int u = 0; u < NO; ++u) ip[u] = epi_prefetch<AK, true>(ep, T.eidx[u], T.ecnt[u]);
-        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         B.X = R.tbar;
         copy_halo<TT>(B, T, off, S.Xs);
         contract_tile<TT, AK, true, SPLIT>(ep, T, T.LJp + 4, ip, S, slot);

@@ -42,26 +42,28 @@ __device__ __forceinline__ void publish(uint32_t* sync, int slot, uint32_t count
 
 // Wait until blocks list[0 .. n) (one per thread) have published >= count.
 // Returns false (in every thread) if the wait ran out or another block aborted.
-__device__ __forceinline__ bool wait_for(uint32_t* sync, int n, const int* list, uint32_t count, int spin_limit) {
-    int ok = 1;
+// *failed: a word of the block's LDS, zero until a wait fails.
+__device__ __forceinline__ bool wait_for(uint32_t* sync, int n, const int* list, uint32_t count, int spin_limit,
+                                         uint32_t* failed) {
     const int t = threadIdx.x;
     if (t < n) {
         const uint32_t* f = flag_of(sync, list[t]);
         for (int spins = 0; __hip_atomic_load(f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < count; ++spins) {
             if ((spins & 31) == 31 &&
                 __hip_atomic_load(sync, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                ok = 0;
+                *failed = 1;
                 break;
             }
             if (spins >= spin_limit) {
                 __hip_atomic_store(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ok = 0;
+                *failed = 1;
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
         }
     }
-    return __syncthreads_and(ok) != 0;
+    __syncthreads();
+    return *failed == 0;
 }
 
 // All stores of this block completed, then store `value` to `word`.

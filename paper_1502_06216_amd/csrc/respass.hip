@@ -132,7 +132,7 @@ resident_pass2d(ResidentPass2D R) {
     __shared__ int nbr[2][kRMaxNbr];
     __shared__ int n_nbr[2];
     __shared__ int all[kFusedMaxBlocks];
-    __shared__ uint32_t okw, word;
+    __shared__ uint32_t okw, word, failed;
     __shared__ double shd[8];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -155,6 +155,7 @@ resident_pass2d(ResidentPass2D R) {
         np[s] = (panel_k1(i0[s], TI, W[s], nlen[s]) - kb0[s]) >> 5;
     }
     if (tid == 0) {
+        failed = 0;
         n_nbr[0] = wait_list(g, t, 0, nb, nbr[0]);
         n_nbr[1] = wait_list(g, t, 1, nb, nbr[1]);
         C = *R.ctl;
@@ -306,10 +307,10 @@ resident_pass2d(ResidentPass2D R) {
                 ia[f][u] = inq[f][u];
                 if (chk) ia[f][u].v = ld4_coh(R.b, eidx[1][u] + f * (int)N, ecnt[1][u], 0.f);
             }
-        if (!wait_for(R.sync, nn0, nbr[0], count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn0, nbr[0], count, R.spin_limit, &failed)) return;
         run_pass(p0, eks, no(), R.a, R.u0, eb, ia);
         publish(R.sync, slot, ++count);
-        if (!wait_for(R.sync, nn1, nbr[1], count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn1, nbr[1], count, R.spin_limit, &failed)) return;
         if (chk) run_pass(p1, ekb, yes(), R.u0, nullptr, eb, ia);
         else run_pass(p1, ekb, no(), R.u0, nullptr, eb, ia);
         publish(R.sync, slot, ++count);
@@ -321,7 +322,7 @@ resident_pass2d(ResidentPass2D R) {
         uint32_t decision = 0;
         if (chk) {
             if (slot == 0) {
-                if (!wait_for(R.sync, nb, all, count, R.spin_limit)) return;
+                if (!wait_for(R.sync, nb, all, count, R.spin_limit, &failed)) return;
                 if ((tid >> 6) == 0) ctl_update<true>(&C, R.part, nb, k, R.tol, R.check_mass, R.absorb, R.a_only);
                 __syncthreads();
                 if (tid == 0) {
@@ -354,10 +355,10 @@ resident_pass2d(ResidentPass2D R) {
 
         // ---- s = xi b, p = prox(s), a = p / s (p kept at candidate iterations)
         const bool cand = (R.checks && k % R.ce == 0) || k == R.K;
-        if (!wait_for(R.sync, nn0, nbr[0], count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn0, nbr[0], count, R.spin_limit, &failed)) return;
         run_pass(p0, eks, no(), R.b, R.u1, ep, inpp);
         publish(R.sync, slot, ++count);
-        if (!wait_for(R.sync, nn1, nbr[1], count, R.spin_limit)) return;
+        if (!wait_for(R.sync, nn1, nbr[1], count, R.spin_limit, &failed)) return;
         if (cand) run_pass(p1, ekp, yes(), R.u1, nullptr, ep, inpp);
         else run_pass(p1, ekp, no(), R.u1, nullptr, ep, inpp);
         publish(R.sync, slot, ++count);

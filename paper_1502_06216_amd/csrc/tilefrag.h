@@ -51,11 +51,25 @@ __device__ __forceinline__ f4 z_frag(const float* xr, const float* kr, const uin
     }
 }
 
+// One of the two accumulators of an FP32 fragment alone: the chunks c0 = first,
+// first + 32, ...; z_frag is the sum of the one from 0 and the one from 16.
+__device__ __forceinline__ f4 z_half(const float* xr, const float* kr, int first, int L) {
+    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+    for (int c0 = first; c0 < L; c0 += 32) {
+        const f4 a = *reinterpret_cast<const f4*>(xr + c0);
+        const f4 b = *reinterpret_cast<const f4*>(kr + c0);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
+    }
+    return acc;
+}
+
 // One k-chunk (16 in FP32, 32 split) of a 16 x 16 fragment of Y^T = Z^T K1_0^T,
-// added to acc; the pointers as above, already at the chunk.
+// added to acc; the pointers as above, already at the chunk.  Z is zr, or zr +
+// z2 (the two accumulators of an FP32 fragment).
 template <bool SPLIT>
 __device__ __forceinline__ f4 y_chunk(const float* zr, const float* kr, const uint16_t* khr, const uint16_t* klr,
-                                      f4 acc) {
+                                      f4 acc, const float* z2 = nullptr) {
     if constexpr (SPLIT) {
         bf8 ah, al;
         split_bf16(*reinterpret_cast<const f4*>(zr), *reinterpret_cast<const f4*>(zr + 4), ah, al);
@@ -65,7 +79,8 @@ __device__ __forceinline__ f4 y_chunk(const float* zr, const float* kr, const ui
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
     } else {
-        const f4 a = *reinterpret_cast<const f4*>(zr);
+        f4 a = *reinterpret_cast<const f4*>(zr);
+        if (z2) a += *reinterpret_cast<const f4*>(z2);
         const f4 b = *reinterpret_cast<const f4*>(kr);
 #pragma unroll
         for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], b[s], acc, 0, 0, 0);
