@@ -1681,7 +1681,7 @@ struct HeatLayout {
     int64_t N = 0, ld = 0;
     bool solve = false;      // products by L solves on the grid, no stored operator
     size_t hdr = 0, A = 0, part = 0, scratch = 0, cidx = 0, gidx = 0, a = 0, b = 0, x = 0, p0 = 0, p1 = 0, g = 0,
-           kf = 0, err = 0, out = 0;
+           kf = 0, err = 0, out = 0, sync = 0;
     size_t total = 0;
 };
 
@@ -1713,6 +1713,7 @@ HeatLayout heat_layout(int n0, int n1, bool solve) {
     H.kf = take(H.N * sizeof(float));
     H.err = take(H.N * sizeof(double));
     H.out = take(8 * sizeof(double));
+    H.sync = take(solve ? 0 : (size_t)heat_resident_sync_words() * sizeof(uint32_t));
     H.total = o;
     return H;
 }
@@ -1831,7 +1832,53 @@ jko_status heat_step(const HeatLayout& H, char* base, int64_t nf, const HeatSolv
     int iters = pr->max_iters;
     bool bytol = false;
     double h[3] = {0.0, 0.0, 0.0};
-    for (int k = 1; k <= pr->max_iters; ++k) {
+    int k0 = 1;   // first iteration left to one launch per product
+    if (!H.solve && heat_resident_fits(gt.nT, kind)) {
+        // the resident kernel, in one launch or, in tolerance mode, in one
+        // launch up to each check's t = A a
+        HeatResident r{};
+        r.t = gt;
+        r.s = gs;
+        r.spin_limit = kBarrierSpinLimit;
+        r.sync = reinterpret_cast<uint32_t*>(base + H.sync);
+        const int64_t total = 2 * (int64_t)pr->max_iters;
+        if (total < INT32_MAX) {
+            k0 = pr->max_iters + 1;
+            int64_t next_check = tolmode ? 2 * (int64_t)pr->check_every : total;   // product of the next check
+            for (int64_t done = 0; done < total;) {
+                const int64_t last = std::min(total, tolmode ? next_check + 1 : total);
+                r.first = (int32_t)done;
+                r.last = (int32_t)last;
+                r.check = tolmode && last == next_check + 1 ? 1 : 0;
+                HIP_TRY(launch_fill(reinterpret_cast<float*>(r.sync), 0.f, heat_resident_sync_words(), st));
+                const hipError_t e = launch_heat_resident(r, kind, st);
+                if (e == hipErrorCooperativeLaunchTooLarge && done == 0) {
+                    (void)hipGetLastError();
+                    k0 = 1;
+                    break;
+                }
+                HIP_TRY(e);
+                uint32_t w = 0;
+                HIP_TRY(hipMemcpyAsync(rb().host, r.sync, sizeof w, hipMemcpyDeviceToHost, st));
+                HIP_TRY(hipStreamSynchronize(st));
+                memcpy(&w, rb().host, sizeof w);
+                if (w) return fail(JKO_ERR_HIP, "resident heat kernel: a wait for another block timed out");
+                done = last;
+                if (r.check) {
+                    jko_status s = heat_sums(err, nf, nullptr, 0, dout, st, h);
+                    if (s) return s;
+                    if (h[2] > 0.0) break;
+                    if (h[0] <= pr->tol_l1) {
+                        iters = (int)(next_check / 2);
+                        bytol = true;
+                        break;
+                    }
+                    next_check += 2 * (int64_t)pr->check_every;
+                }
+            }
+        }
+    }
+    for (int k = k0; k <= pr->max_iters; ++k) {
         gt.check = tolmode && k > 1 && (k - 1) % pr->check_every == 0;
         jko_status s = heat_product(HEAT_EK_BUPDATE, gt, hs, st);
         if (s) return s;

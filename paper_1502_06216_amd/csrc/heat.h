@@ -10,7 +10,8 @@
 // those Nf indices.  xi~ is symmetric; the library stores its upper triangle
 // of kHeatTile x kHeatTile float32 tiles: tile (I, J), I <= J, of the ld x ld
 // matrix (ld = Nf rounded up to the tile) at
-// packed index I*nT - I*(I-1)/2 + (J - I), each tile row-major.  Rows and
+// packed index I*nT - I*(I-1)/2 + (J - I), each tile in the order of
+// heat_tile_offset (heat_tile.h).  Rows and
 // columns of the padding are zero.
 #pragma once
 
@@ -137,6 +138,22 @@ hipError_t heat_build_operator(const uint8_t* mask, int n0, int n1, double gamma
 enum : int { HEAT_EK_STORE = 0, HEAT_EK_BUPDATE = 1, HEAT_EK_MONITOR = 2, HEAT_EK_PROX = 3 };
 
 hipError_t launch_heat_gemv(int ek, const HeatGemv& g, hipStream_t st);
+
+// Products [first, last) of a step's iteration with the stored operator in one
+// cooperative launch (heatres.hip): product 2 (k - 1) is t = A a with the
+// b-update of iteration k (record t), product 2 (k - 1) + 1 is s = A b with the
+// proximal update (record s, whose p is written by the launch's last one).
+struct HeatResident {
+    HeatGemv t, s;
+    int32_t first, last;
+    int32_t check;           // the last product, a t = A a, writes errrow
+    int32_t spin_limit;      // polls before a wait gives up
+    uint32_t* sync;          // heat_resident_sync_words() words, zeroed before the launch; [0] != 0
+                             // afterwards: a wait ran out
+};
+int64_t heat_resident_sync_words();
+bool heat_resident_fits(int nT, int kind);
+hipError_t launch_heat_resident(const HeatResident& r, int kind, hipStream_t st);
 
 // x[0..n) = v, x[n..ld) = 0
 hipError_t launch_heat_fill(float* x, float v, int64_t n, int64_t ld, hipStream_t st);

@@ -27,8 +27,7 @@
 #include <new>
 #include <vector>
 
-#include "heat.h"
-#include "epilogue.h"
+#include "heat_tile.h"
 
 namespace jko {
 
@@ -85,8 +84,6 @@ __device__ __forceinline__ double lane_right(double v) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-template <int EK>
-__device__ __forceinline__ void heat_epilogue(const HeatGemv& g, int64_t r, float v);
 __host__ __device__ __forceinline__ int64_t tile_index(int64_t I, int64_t J, int64_t nT);
 
 // DST: an epilogue code (the last launch of a product), HEAT_DST_CONT or
@@ -190,8 +187,8 @@ k_heat_series(HeatSeriesArgs P, HeatGemv G) {
             const int64_t row = P.j0 + blockIdx.y;
             const int64_t I = row / kHeatTile, J = cc / kHeatTile;
             if (I <= J)
-                P.A[tile_index(I, J, P.nT) * kHeatTile * kHeatTile + (row - I * kHeatTile) * kHeatTile +
-                    (cc - J * kHeatTile)] = (float)y[r];
+                P.A[tile_index(I, J, P.nT) * kHeatTileFloats +
+                    heat_tile_offset((int)(row - I * kHeatTile), (int)(cc - J * kHeatTile))] = (float)y[r];
         } else {
             heat_epilogue<DST>(G, cc, (float)y[r]);
         }
@@ -248,102 +245,51 @@ __global__ void k_heat_gather(float* __restrict__ x, const float* __restrict__ s
 
 // ------------------------------------------------------------------ products
 
-// Finish row r (free cell i = gidx[r]) of y = A x (value v): the epilogue of
-// the iteration's half-step.
-template <int EK>
-__device__ __forceinline__ void heat_epilogue(const HeatGemv& g, int64_t r, float v) {
-    const int64_t i = g.gidx[r];
-    if constexpr (EK == EK_STORE) {
-        g.y[i] = v;
-    } else if constexpr (EK == EK_BUPDATE || EK == EK_MONITOR) {
-        const float q = g.q[i];
-        if (EK == EK_MONITOR || g.check) g.errrow[r] = fabs((double)g.b[r] * (double)v - (double)q);
-        if (EK == EK_BUPDATE) g.b[r] = q == 0.f ? 0.f : q / v;
-    } else {
-        constexpr int KIND = EK - EK_PROX;
-        const ProxArgs& px = g.px;
-        float pu = 1.f, pv = 0.f;
-        if (KIND == JKO_F_CONGESTION || KIND == JKO_F_CONGESTION_BINARY) {
-            pu = px.g ? px.g[i] : 1.f;
-            pv = px.kappa ? px.kappa[i] : px.kappa_s;
-        } else if (KIND == JKO_F_ENTROPY || KIND == JKO_F_POROUS) {
-            pu = px.kf ? px.kf[i] : px.kf_s;
-        } else if (KIND == JKO_F_GEN_ENTROPY) {
-            pu = px.kf ? px.kf[i] : px.kf_s;
-            pv = px.g ? px.g[i] : px.eps_s;
-        }
-        const float p = prox_val<KIND>(px, v, pu, pv);
-        g.a[r] = p == 0.f ? 0.f : p / v;
-        g.p[i] = p;
-    }
-}
-
-// Plain loads: the packed operator of a 100 x 100 room stays largely
-// resident in the last-level cache between passes; with the non-temporal
-// hint the room's flow ran 12 % slower (measured on the full-grid operator:
-// 11.8 K against 13.4 K iterations/s).
-#ifndef JKO_HEAT_NT
-#define JKO_HEAT_NT 0
-#endif
-// One float4 of an operator tile, with the non-temporal hint when JKO_HEAT_NT.
-__device__ __forceinline__ f4 ld_nt(const f4* p) {
-#if JKO_HEAT_NT
-    return __builtin_nontemporal_load(p);
-#else
-    return *p;
-#endif
-}
-
 // Tile pass: block b takes the packed tile (I, J), I <= J, and writes
 //   part[I][J] = A_IJ x_J             (its row sums, the tile's share of y_I)
 //   part[J][I] = A_IJ^T x_I  (I < J)  (its column sums, the share of y_J
 //                                      from the transposed lower tile)
-// so that every (row block, tile) slot of part is written exactly once.  A
-// tile row is 32 float4s: thread (group g, lane c) takes float4 c of rows
-// g, g + 8, ..., g + 120 (plain loads, see ld_nt), keeps one partial row sum per
-// row and four column sums in registers; the row partials are then summed
-// through LDS (one row per thread), the column sums over the 8 groups.
-__global__ void __launch_bounds__(256) k_heat_tiles(const float* __restrict__ A, const float* __restrict__ x,
-                                                    float* __restrict__ part, int nT) {
-    constexpr int T = kHeatTile, R = T / 8;
+// so that every (row block, tile) slot of part is written exactly once.  The
+// loads are plain: the operator of a 100 x 100 room stays largely in the
+// last-level cache between passes (with the non-temporal hint the room's flow
+// ran 12 % slower).  A step runs on the resident kernel (heatres.hip) where
+// the operator suits it; this pass serves single products and larger operators.
+__global__ void __launch_bounds__(kHeatThr) k_heat_tiles(const float* __restrict__ A, const float* __restrict__ x,
+                                                         float* __restrict__ part, int nT) {
+    constexpr int T = kHeatTile;
+    __shared__ float rows[kHeatWaves][T];
     const int b = blockIdx.x;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rg = lane >> 2;
+    HeatTileRegs a;
+    heat_load_tile(a, A, b, wave, lane);
     int I = 0, start = 0;
     while (start + (nT - I) <= b) {    // uniform over the block; at most nT steps
         start += nT - I;
         ++I;
     }
     const int J = I + (b - start);
-    const f4* __restrict__ tile = reinterpret_cast<const f4*>(A + (int64_t)b * T * T);
-    const int t = threadIdx.x, cl = t & 31, rg = t >> 5;
-    const f4 xj = reinterpret_cast<const f4*>(x + (int64_t)J * T)[cl];
-    const float* __restrict__ xi = x + (int64_t)I * T;
-    const bool off = I != J;
-    __shared__ float red[T][33];      // row partials, padded against bank conflicts
-    __shared__ f4 cols[8][32];
-    float rp[R];
-    f4 cacc = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const int r = rg + 8 * k;
-        const f4 a = ld_nt(tile + r * 32 + cl);
-        rp[k] = (a.x * xj.x + a.y * xj.y) + (a.z * xj.z + a.w * xj.w);
-        if (off) cacc += a * xi[r];
+    const f4 xj = reinterpret_cast<const f4*>(x + (int64_t)J * T)[4 * wave + (lane & 3)];
+    const f4* xr = reinterpret_cast<const f4*>(x + (int64_t)I * T) + 2 * rg;
+    const f4 x0 = xr[0], x1 = xr[1];
+    const float xi[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+    float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    const f4 cs = heat_tile_fma([&](int q) { return a.v[q]; }, xj, xi, rs);
+    if (I != J) {
+        const float v = heat_column_sum(cs);
+        if ((lane & 12) == 0) part[((int64_t)J * nT + I) * T + 16 * wave + 4 * (lane & 3) + (lane >> 4)] = v;
     }
 #pragma unroll
-    for (int k = 0; k < R; ++k) red[rg + 8 * k][cl] = rp[k];
-    if (off) cols[rg][cl] = cacc;
+    for (int q = 0; q < 8; ++q) {
+        const float v = heat_row_sum(rs[q]);
+        if ((lane & 3) == 0) rows[wave][8 * rg + q] = v;
+    }
     __syncthreads();
+    const int t = threadIdx.x;
     if (t < T) {
-        float y = 0.f;
+        float y = rows[0][t];
 #pragma unroll
-        for (int c = 0; c < 32; ++c) y += red[t][c];
+        for (int w = 1; w < kHeatWaves; ++w) y += rows[w][t];
         part[((int64_t)I * nT + J) * T + t] = y;
-    } else if (off && t < T + 32) {
-        const int c = t - T;
-        f4 v = cols[0][c];
-#pragma unroll
-        for (int g = 1; g < 8; ++g) v += cols[g][c];
-        reinterpret_cast<f4*>(part + ((int64_t)J * nT + I) * T)[c] = v;
     }
 }
 
@@ -501,7 +447,7 @@ template <int EK>
 hipError_t gemv_as(const HeatGemv& g, hipStream_t st) {
     if (g.nT == 0) return hipSuccess;   // no free cell
     const int64_t tiles = (int64_t)g.nT * (g.nT + 1) / 2;
-    hipLaunchKernelGGL(k_heat_tiles, dim3((unsigned)tiles), dim3(256), 0, st, g.A, g.x, g.part, g.nT);
+    hipLaunchKernelGGL(k_heat_tiles, dim3((unsigned)tiles), dim3(kHeatThr), 0, st, g.A, g.x, g.part, g.nT);
     hipLaunchKernelGGL(k_heat_finish<EK>, dim3((unsigned)((g.N + 31) / 32)), dim3(256), 0, st, g);
     return hipGetLastError();
 }
