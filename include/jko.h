@@ -186,10 +186,12 @@ typedef struct {
  * passes' shapes.
  * JKO_FLAG_NO_RESIDENT: one launch per Gibbs application (per pass) instead
  *   of the resident kernels.  Both paths give the same bits.
- * JKO_FLAG_AXIS_PASSES: on 3D grids whose axes are multiples of 32 (the
- *   second at most 128), an application of xi normally runs as a plane pass
- *   (axes 1 and 2 of each plane, the intermediate kept on chip) and an axis-0
- *   pass; this flag runs three axis passes instead.  Both give the same bits.
+ * JKO_FLAG_AXIS_PASSES: on 3D grids (axes of at least 16 cells, the second at
+ *   most 128, bands of a few 32-cell panels), an application of xi normally
+ *   runs as a plane pass (axes 1 and 2 of each plane, the intermediate kept on
+ *   chip) and an axis-0 pass; this flag runs three axis passes instead.  Both
+ *   give the same bits where every axis is a multiple of 32, and the same
+ *   values to rounding on others.
  *   On 2D grids it runs every application as per-axis passes instead of the
  *   fused tile kernel (and a step on the resident pass kernel where its
  *   shape allows).

@@ -229,6 +229,11 @@ struct Plan {
     bool plane3d = false;        // 3D applications run as a plane pass and a slow-axis pass
 
     float* F(int i) const { return field[i]; }
+    // x is one of the workspace's fields, each a multiple of 256 bytes long
+    bool owns(const float* x) const {
+        const char* c = reinterpret_cast<const char*>(x);
+        return c >= base && c < base + L.total;
+    }
     float* hist(int64_t i) const {
         return reinterpret_cast<float*>(base + L.hist + (size_t)i * align_up((size_t)g.N * sizeof(float)));
     }
@@ -272,7 +277,7 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
     P.gamma = gamma;
     for (int k = 0; k < P.g.d; ++k) P.W[k] = band_halfwidth(P.g.n[k], gamma);
     P.plane3d = P.g.d == 3 && !(flags & JKO_FLAG_AXIS_PASSES) &&
-                plane3d_fits(P.g.n[0], P.g.n[1], P.g.n[2], P.W[0], P.W[1], P.W[2]);
+                plane3d_fits(P.g.n[0], P.g.n[1], P.g.n[2], P.W[0], P.W[1], P.W[2], P.prec);
     // A 2D application runs as the fused tile kernel, which trades redundant
     // halo work for one launch, with 16 x 16 tiles where at most one block
     // per CU covers the grid.  Otherwise, for axes of a multiple of 32 whose
@@ -296,12 +301,23 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
     P.resident = P.fused2d;
     P.respass = !P.fused2d && passes2d;
     for (int k = 0; k < P.g.d; ++k) {
+        if (P.plane3d && plane3d_stride(P.g.n[k]) != P.g.n[k]) {
+            // padded rows: only the form that this precision reads, over the
+            // bytes of the two square ones (plane3d_fits: the rows at most double)
+            char* f = P.base + P.L.factor_off[k];
+            const bool split = P.prec == JKO_SPLIT_BF16;
+            P.K1[k] = split ? nullptr : reinterpret_cast<const float*>(f);
+            P.K1hi[k] = split ? reinterpret_cast<const uint16_t*>(f) : nullptr;
+            P.K1lo[k] = split ? reinterpret_cast<const uint16_t*>(
+                                    f + align_up((size_t)P.g.n[k] * P.g.n[k] * sizeof(float))) : nullptr;
+        }
         bool done = false;
         for (int j = 0; j < k; ++j)
             if (P.g.n[j] == P.g.n[k]) done = true;
         if (done) continue;
         HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[k]), const_cast<uint16_t*>(P.K1hi[k]),
-                                    const_cast<uint16_t*>(P.K1lo[k]), P.g.n[k], gamma, P.st));
+                                    const_cast<uint16_t*>(P.K1lo[k]), P.g.n[k],
+                                    P.plane3d ? plane3d_stride(P.g.n[k]) : P.g.n[k], gamma, P.st));
     }
     return JKO_OK;
 }
@@ -320,7 +336,7 @@ void set_vec(EpiArgs& e) {
 // The plane pass of a 3D application (x -> z1) and its slow-axis pass (z1 -> epilogue).
 Plane3D plane_of(const Plan& P, const float* x, const Ctl* ctl) {
     return Plane3D{P.g.n[0], P.g.n[1], P.g.n[2], P.W[1], P.W[2], P.K1[1], P.K1hi[1], P.K1lo[1],
-                   P.K1[2], P.K1hi[2], P.K1lo[2], x, P.F(F_Z1), ctl};
+                   P.K1[2], P.K1hi[2], P.K1lo[2], x, P.F(F_Z1), ctl, P.owns(x)};
 }
 Pass slow_of(const Plan& P) {
     Pass s{};
@@ -1156,7 +1172,7 @@ jko_status attraction_flow(const Geo& g, const jko_energy* en, const jko_params*
     if ((s = build_factors(P, pr->gamma, pr->flags))) return s;
     // the stacking axis: gamma -> 0 rounds every off-diagonal entry to zero
     HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[0]), const_cast<uint16_t*>(P.K1hi[0]),
-                                const_cast<uint16_t*>(P.K1lo[0]), 2, 1e-30, P.st));
+                                const_cast<uint16_t*>(P.K1lo[0]), 2, 2, 1e-30, P.st));
     P.ident[0] = true;
     // 2D grids: both couplings in one launch of the fused 2D kernel per
     // application (axis 0 of the stacked field is the identity)

@@ -25,10 +25,11 @@
 // These passes run the plain domain only: after an absorption switch every
 // product runs on the exact log-sum-exp passes of logpass.hip.
 //
-// 3D grids whose axes are multiples of 32 use two other kernels defined here,
-// which keep the layout: a plane pass (axes 2 and 1 of each plane, the
+// 3D grids of moderate bands use two other kernels defined here, which keep the
+// layout: a plane pass (axes 2 and 1 of each plane, the
 // intermediate in LDS) and a slow-axis pass (axis 0, X staged transposed),
-// with the same arithmetic in the same order as the three axis passes.
+// with the same arithmetic, for axes of multiples of 32 in the same order, as
+// the three axis passes.
 #include <math.h>
 
 #include <algorithm>
@@ -519,16 +520,27 @@ hipError_t launch_ek(int ek, int cfg, int64_t nb, const Pass& p, const EpiArgs& 
 // A 3D application of xi as a plane pass (axes 2 and 1 of each plane a, the
 // intermediate kept in LDS) and a slow-axis pass (axis 0, with the epilogue),
 // both keeping the layout [a][b][c].  The arithmetic is that of the three
-// axis passes, in the same order: the plane pass's first stage is the axis-2
-// pass (rows b, outputs c' in 32-wide chunks over their 32-aligned bands), its
-// second stage the axis-1 pass on the staged intermediate (outputs b' in
-// 32-wide chunks, one per wave, each over its own band), and the slow-axis
-// pass is the axis-0 pass with X staged transposed.  Two launches per application instead of three, and one trip
-// of the field through memory fewer.
+// axis passes, on axes of multiples of 32 in the same order: the plane pass's
+// first stage is the axis-2 pass (rows b, outputs c' in 32-wide chunks over
+// their 32-aligned bands), its second stage the axis-1 pass on the staged
+// intermediate (outputs b' in 32-wide chunks, one per wave, each over its own
+// band), and the slow-axis pass is the axis-0 pass with X staged transposed.
+// Two launches per application instead of three, and one trip of the field
+// through memory fewer.
+//
+// Other axes (RAG) are taken as rounded up to whole panels: the factors' rows
+// are stored that long, zero past the axis's end; rows of X past its end are
+// read as zeros by way of an offset past the buffer; a chunk across a row's
+// end is loaded whole (16-byte copies need dword alignment only), its further
+// values cut to zero in the plane pass and confined to unwritten outputs in the
+// slow-axis pass.  Copying such rows float by float instead: 45 x 38 x 51,
+// split, 24.8 us an iteration against 22.2.
 
 constexpr int kPlaneMaxN1 = 128;             // one 16-row fragment of b per wave in the first stage
+constexpr int kPlaneMinN = 16;               // a factor's padded rows fit where its square copies lie (round32(n) <= 2 n)
 constexpr int kPlaneQ = kPlaneMaxN1 / 32;    // band panels of a b' chunk
 
+__host__ __device__ inline int round32(int n) { return (n + 31) & ~31; }
 __host__ __device__ inline int band_lo32(int i0, int W) { return (i0 - W > 0 ? i0 - W : 0) & ~31; }
 __host__ __device__ inline int band_hi32(int i0, int W, int n) {
     const int h = (i0 + 32 + W + 31) & ~31;
@@ -542,7 +554,10 @@ int plane_lds_bytes(int n1, int NP) { return std::max(NP * (n1 + 32) * 128, 32 *
 constexpr int kPlaneWaves = 8;                 // 512 threads: two waves per SIMD per block
 constexpr int kPlaneThr = 64 * kPlaneWaves;
 
-template <bool SPLIT>
+// A byte offset past every buffer of these kernels: the copy reads as zero.
+constexpr int kPastEnd = 0x7ffffffc;
+
+template <bool SPLIT, bool RAG>
 __global__ void __launch_bounds__(kPlaneThr)
 plane_pass(Plane3D P) {
     extern __shared__ __attribute__((aligned(16))) float dyn[];
@@ -550,17 +565,19 @@ plane_pass(Plane3D P) {
     int done = 0;
     if (P.ctl) done = P.ctl->done | P.ctl->logmode;
     const int n1 = P.n1, n2 = P.n2;
-    const int chunks = n2 >> 5;
+    // RAG: the axes' lengths rounded up to whole panels, and so the factors' row strides
+    const int m1 = RAG ? round32(n1) : n1, m2 = RAG ? round32(n2) : n2;
+    const int chunks = m2 >> 5;
     const int logical = xcd_logical_block();
     const int a = logical / chunks, c0 = (logical % chunks) * 32;
-    const int kb0 = band_lo32(c0, P.W2), kb1 = band_hi32(c0, P.W2, n2);
+    const int kb0 = band_lo32(c0, P.W2), kb1 = band_hi32(c0, P.W2, m2);
     const int NP = (kb1 - kb0) >> 5;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
-    float* Xs = dyn;                                                   // [NP][n1][32]
-    float* K2f = dyn + NP * n1 * 32;                                   // [NP][32][32]
-    uint16_t* K2h = reinterpret_cast<uint16_t*>(dyn + NP * n1 * 32);   // [NP][32][32] bf16
+    float* Xs = dyn;                                                   // [NP][m1][32]
+    float* K2f = dyn + NP * m1 * 32;                                   // [NP][32][32]
+    uint16_t* K2h = reinterpret_cast<uint16_t*>(dyn + NP * m1 * 32);   // [NP][32][32] bf16
     uint16_t* K2l = K2h + NP * 32 * 32;
-    const int ZS = n1 + 4;
+    const int ZS = m1 + 4;
     float* Zt = dyn;                                                   // [32][ZS] after the first stage
 
     // Second stage: waves 2q and 2q + 1 share the 32-row chunk q of b', one
@@ -570,21 +587,21 @@ plane_pass(Plane3D P) {
     const int bt = bq0 + 16 * (wave & 1);   // first b' of this wave's fragment
     const bool s2 = bq0 < n1;
     const int qb0 = s2 ? band_lo32(bq0, P.W1) : 0;
-    const int NQ = s2 ? (band_hi32(bq0, P.W1, n1) - qb0) >> 5 : 0;
+    const int NQ = s2 ? (band_hi32(bq0, P.W1, m1) - qb0) >> 5 : 0;
     f4 kq[kPlaneQ][2];
     bf8 kqh[kPlaneQ], kql[kPlaneQ];
 #pragma unroll
     for (int q = 0; q < kPlaneQ; ++q) {
         if (q >= NQ) continue;
-        const int row = bt + (lane & 15);
+        const int row = RAG ? min(bt + (lane & 15), n1 - 1) : bt + (lane & 15);   // rows past the end: not stored
         const int kb = qb0 + 32 * q;
         if (SPLIT) {
-            kqh[q] = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(P.K1hi + row * n1 + kb + 8 * g));
-            kql[q] = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(P.K1lo + row * n1 + kb + 8 * g));
+            kqh[q] = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(P.K1hi + row * m1 + kb + 8 * g));
+            kql[q] = __builtin_bit_cast(bf8, *reinterpret_cast<const u16x8*>(P.K1lo + row * m1 + kb + 8 * g));
         } else {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
-                kq[q][h] = *reinterpret_cast<const f4*>(P.K1 + row * n1 + kb + 4 * (4 * h + g));
+                kq[q][h] = *reinterpret_cast<const f4*>(P.K1 + row * m1 + kb + 4 * (4 * h + g));
         }
     }
 
@@ -592,33 +609,47 @@ plane_pass(Plane3D P) {
     // the chunk (layout and swizzle of the panel form).
     {
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(P.X), (short)0, P.n0 * n1 * n2 * 4, kBufRsrcWord3);
+            const_cast<float*>(P.X), (short)0, RAG && P.padded ? (P.n0 * n1 * n2 * 4 + 15) & ~15 : P.n0 * n1 * n2 * 4,
+            kBufRsrcWord3);
         const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
             SPLIT ? (void*)const_cast<uint16_t*>(P.K2hi) : (void*)const_cast<float*>(P.K2), (short)0,
-            SPLIT ? n2 * n2 * 2 : n2 * n2 * 4, kBufRsrcWord3);
+            SPLIT ? n2 * m2 * 2 : n2 * m2 * 4, kBufRsrcWord3);
         const __amdgpu_buffer_rsrc_t rkl = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint16_t*>(SPLIT ? P.K2lo : P.K2hi), (short)0, n2 * n2 * 2, kBufRsrcWord3);
+            const_cast<uint16_t*>(SPLIT ? P.K2lo : P.K2hi), (short)0, n2 * m2 * 2, kBufRsrcWord3);
         const int xrow = lane >> 3, xch = lane & 7;
         const int krow = lane >> 2, kch = lane & 3;
-        const int XC = n1 / 8;   // 8-row X copies per panel
-        for (int j = wave; j < NP * XC; j += kPlaneWaves) {
-            const int pnl = j / XC, row = (j % XC) * 8 + xrow;
-            const int col = kb0 + 32 * pnl + 4 * (xch ^ ((row >> 1) & 7));
-            lds_copy16(rx, Xs + j * 256, 4 * ((a * n1 + row) * n2 + col));
+        if (RAG && (n2 & 3) != 0 && !P.padded) {
+            // no word past the field may be read: copies of single floats, two
+            // rows each, those past a row's or the plane's end reading as zeros
+            const int XC = m1 / 2;
+            for (int j = wave; j < NP * XC; j += kPlaneWaves) {
+                const int pnl = j / XC, row = (j % XC) * 2 + (lane >> 5);
+                const int col = kb0 + 32 * pnl + 4 * (((lane & 31) >> 2) ^ ((row >> 1) & 7)) + (lane & 3);
+                lds_copy4(rx, Xs + j * 64, row < n1 && col < n2 ? 4 * ((a * n1 + row) * n2 + col) : kPastEnd);
+            }
+        } else {
+            const int XC = m1 / 8;   // 8-row X copies per panel
+            for (int j = wave; j < NP * XC; j += kPlaneWaves) {
+                const int pnl = j / XC, row = (j % XC) * 8 + xrow;
+                const int col = kb0 + 32 * pnl + 4 * (xch ^ ((row >> 1) & 7));
+                const int voff = 4 * ((a * n1 + row) * n2 + col);
+                lds_copy16(rx, Xs + j * 256, RAG && (row >= n1 || col >= n2) ? kPastEnd : voff);
+            }
         }
-        // K2: four copies per panel (FP32: 8 rows each; split: 16 rows of hi, then lo)
+        // K2: four copies per panel (FP32: 8 rows each; split: 16 rows of hi, then
+        // lo); rows past the factor's end read as zeros
         for (int j = wave; j < NP * 4; j += kPlaneWaves) {
             const int pnl = j >> 2, q = j & 3;
             if (SPLIT) {
                 const int qq = q & 1, row = qq * 16 + krow;
                 const int col = kb0 + 32 * pnl + 8 * (kch ^ ((row >> 2) & 3));
-                const int voff = 2 * ((c0 + row) * n2 + col);
+                const int voff = 2 * ((c0 + row) * m2 + col);
                 if (q < 2) lds_copy16(rk, K2h + (pnl * 2 + qq) * 512, voff);
                 else lds_copy16(rkl, K2l + (pnl * 2 + qq) * 512, voff);
             } else {
                 const int row = q * 8 + xrow;
                 const int col = kb0 + 32 * pnl + 4 * (xch ^ ((row >> 1) & 7));
-                lds_copy16(rk, K2f + j * 256, 4 * ((c0 + row) * n2 + col));
+                lds_copy16(rk, K2f + j * 256, 4 * ((c0 + row) * m2 + col));
             }
         }
     }
@@ -629,17 +660,25 @@ plane_pass(Plane3D P) {
     // ---- first stage: Z[b][c'] = sum_c X[b][c] K2[c'][c]; wave w owns the
     // 16-row fragment w of b and both 16-column fragments of c'
     const int fb = wave;
-    const bool s1 = fb < (n1 >> 4);
+    const bool s1 = fb < (m1 >> 4);
     const int s8 = (lane >> 1) & 7;
     f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
     if (s1) {
         for (int pnl = 0; pnl < NP; ++pnl) {
-            const float* xr = Xs + (pnl * n1 + fb * 16 + (lane & 15)) * 32;
+            const float* xr = Xs + (pnl * m1 + fb * 16 + (lane & 15)) * 32;
+            // a row's last chunk may hold the next row's first values
+            auto cut = [&](f4 v, int col) {
+                if (RAG)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = col + e < n2 ? v[e] : 0.f;
+                return v;
+            };
+            const int kc = kb0 + 32 * pnl;
             if (SPLIT) {
                 const int s4 = (lane >> 2) & 3;
                 bf8 ah, al, bh[2], bl[2];
-                const f4 v0 = *reinterpret_cast<const f4*>(xr + 4 * ((2 * g) ^ s8));
-                const f4 v1 = *reinterpret_cast<const f4*>(xr + 4 * ((2 * g + 1) ^ s8));
+                const f4 v0 = cut(*reinterpret_cast<const f4*>(xr + 4 * ((2 * g) ^ s8)), kc + 8 * g);
+                const f4 v1 = cut(*reinterpret_cast<const f4*>(xr + 4 * ((2 * g + 1) ^ s8)), kc + 8 * g + 4);
                 split_bf16(v0, v1, ah, al);
 #pragma unroll
                 for (int f = 0; f < 2; ++f) {
@@ -657,7 +696,7 @@ plane_pass(Plane3D P) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int ch = 4 * ((4 * h + g) ^ s8);
-                    const f4 av = *reinterpret_cast<const f4*>(xr + ch);
+                    const f4 av = cut(*reinterpret_cast<const f4*>(xr + ch), kc + 4 * (4 * h + g));
                     f4 bv[2];
 #pragma unroll
                     for (int f = 0; f < 2; ++f)
@@ -722,7 +761,9 @@ plane_pass(Plane3D P) {
     for (int f = 0; f < 2; ++f) {
         const int cl = f * 16 + 4 * g;
         const int bp = bt + (lane & 15);
-        __builtin_nontemporal_store(acc2[f], reinterpret_cast<f4*>(P.Y + ((int64_t)a * n1 + bp) * n2 + c0 + cl));
+        float* y = P.Y + ((int64_t)a * n1 + bp) * n2 + c0 + cl;
+        if (RAG) st4(y, 0, bp < n1 ? min(4, n2 - c0 - cl) : 0, false, acc2[f]);
+        else __builtin_nontemporal_store(acc2[f], reinterpret_cast<f4*>(y));
     }
 }
 
@@ -733,7 +774,7 @@ plane_pass(Plane3D P) {
 // reads of four k at once fall in distinct banks.
 __device__ __forceinline__ int slow_pos(int k, int r) { return (((r >> 2) ^ (4 * ((k >> 2) & 3))) << 2) | (r & 3); }
 
-template <bool SPLIT, int EK>
+template <bool SPLIT, int EK, bool RAG>
 __global__ void __launch_bounds__(kThreads)
 contract_slow(Pass P, EpiArgs E) {
     constexpr int TR = 64, TI = 32, WR = 2, WI = 2;
@@ -746,11 +787,12 @@ contract_slow(Pass P, EpiArgs E) {
     if (E.ctl) done = E.ctl->done | E.ctl->logmode;
     const int n = P.n;
     const int R = (int)P.R;
-    const int IT = n / TI;
+    const int m = RAG ? round32(n) : n;   // n in whole panels: the factor's row stride
+    const int IT = m / TI;
     const int logical = xcd_logical_block();
     const int r0 = (logical / IT) * TR;
     const int i0 = (logical % IT) * TI;
-    const int kb0 = band_lo32(i0, P.W), kb1 = band_hi32(i0, P.W, n);
+    const int kb0 = band_lo32(i0, P.W), kb1 = band_hi32(i0, P.W, m);
     const int NP = (kb1 - kb0) >> 5;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wr = wave % WR, wi = wave / WR;
@@ -762,6 +804,7 @@ contract_slow(Pass P, EpiArgs E) {
     constexpr int UE = (TI * TR / 4 + kThreads - 1) / kThreads;
     EpiIn ein[UE];
     int eidx[UE], ecnt[UE];
+    const int last4 = n * R - 4;   // RAG: the last index with four values from it on
 #pragma unroll
     for (int u = 0; u < UE; ++u) {
         const int unit = tid + u * kThreads;
@@ -769,15 +812,18 @@ contract_slow(Pass P, EpiArgs E) {
         const int i = i0 + il, r = r0 + rl;
         ecnt[u] = (unit < TI * TR / 4 && i < n) ? max(0, min(4, R - r)) : 0;
         eidx[u] = i * R + r;
-        ein[u] = epi_prefetch<EK, false, true>(E, eidx[u], ecnt[u]);   // whole tiles
+        // four values in any case; a group that the field's end cuts is read
+        // from its last four and moved down before it is used
+        ein[u] = epi_prefetch<EK, false, true>(E, RAG ? min(eidx[u], last4) : eidx[u], 4);
     }
     {
-        // copies issued untracked, K first, then X panel by panel: each
-        // wave issues two X copies per panel, so panel p has landed for this
-        // wave once at most 2 (NP - 1 - p) copies are outstanding
+        // copies issued untracked, K first (rows past the factor's end read as
+        // zeros), then X panel by panel: each wave issues two X copies per
+        // panel, so panel p has landed for this wave once at most
+        // 2 (NP - 1 - p) copies are outstanding
         const int xrow = lane >> 3, xch = lane & 7;
         if (SPLIT) {
-            const i4v rh = buffer_desc(P.K1hi, n * n * 2), rl = buffer_desc(P.K1lo, n * n * 2);
+            const i4v rh = buffer_desc(P.K1hi, n * m * 2), rl = buffer_desc(P.K1lo, n * m * 2);
             constexpr int KPP = TI / 16;
             const int nK = NP * KPP;
             const int kr = lane >> 2, kch = lane & 3;
@@ -785,27 +831,29 @@ contract_slow(Pass P, EpiArgs E) {
                 const int jj = j < nK ? j : j - nK;
                 const int pnl = jj / KPP, row = (jj % KPP) * 16 + kr;
                 const int col = kb0 + 32 * pnl + 8 * (kch ^ ((row >> 2) & 3));
-                const int voff = 2 * ((i0 + row) * n + col);
+                const int voff = 2 * ((i0 + row) * m + col);
                 if (j < nK) lds_copy16_untracked(rh, Kh + jj * 512, voff);
                 else lds_copy16_untracked(rl, Kl + jj * 512, voff);
             }
         } else {
-            const i4v rk = buffer_desc(P.K1, n * n * 4);
+            const i4v rk = buffer_desc(P.K1, n * m * 4);
             constexpr int KPP = TI / 8;
             for (int j = wave; j < NP * KPP; j += kThreads / 64) {
                 const int pnl = j / KPP, row = (j % KPP) * 8 + xrow;
                 const int col = kb0 + 32 * pnl + 4 * (xch ^ ((row >> 1) & 7));
-                lds_copy16_untracked(rk, Kf + j * 256, 4 * ((i0 + row) * n + col));
+                lds_copy16_untracked(rk, Kf + j * 256, 4 * ((i0 + row) * m + col));
             }
         }
         // X: 4 rows of 64 r per wave-wide copy; lane L fills position L & 15 of
         // row 4 j + (L >> 4) with the chunk that the swizzle puts there
-        const i4v rx = buffer_desc(P.X, R * n * 4);
+        // (RAG: the last chunk of a row may hold the next row's first values, which
+        // reach only outputs past r = R; X's allocation is a multiple of 16 bytes)
+        const i4v rx = buffer_desc(P.X, RAG ? (R * n * 4 + 15) & ~15 : R * n * 4);
         const int krow = lane >> 4, pos = lane & 15;
         for (int j = wave; j < NP * 8; j += kThreads / 64) {
             const int pnl = j / 8, k = (j % 8) * 4 + krow;
-            const int c = pos ^ (4 * ((k >> 2) & 3));
-            lds_copy16_untracked(rx, Xs + j * 256, 4 * ((kb0 + 32 * pnl + k) * R + r0 + 4 * c));
+            const int kk = kb0 + 32 * pnl + k, r = r0 + 4 * (pos ^ (4 * ((k >> 2) & 3)));
+            lds_copy16_untracked(rx, Xs + j * 256, RAG && (kk >= n || r >= R) ? kPastEnd : 4 * (kk * R + r));
         }
     }
     if (done) {   // the step has stopped: nothing to compute (uniform)
@@ -906,15 +954,16 @@ contract_slow(Pass P, EpiArgs E) {
         const int il = unit / (TR / 4), rl = 4 * (unit % (TR / 4));
         if (ecnt[u] == 0) continue;
         const f4 v = *reinterpret_cast<const f4*>(&tile[il * TS + rl]);
+        if (RAG && eidx[u] > last4) epi_shift(ein[u], eidx[u] - last4);
         epi_apply<EK>(E, eidx[u], ecnt[u], v, false, ein[u], ea);
     }
     epi_finish(E, ea, (int)blockIdx.x, shd);
 }
 
-template <bool SPLIT>
+template <bool SPLIT, bool RAG>
 hipError_t launch_slow_ek(int ek, int64_t nb, const Pass& p, const EpiArgs& e, int lds, hipStream_t st) {
     const dim3 grid((unsigned)nb), block(kThreads);
-#define JKO_SLOW(EKV) hipLaunchKernelGGL((contract_slow<SPLIT, EKV>), grid, block, lds, st, p, e); break
+#define JKO_SLOW(EKV) hipLaunchKernelGGL((contract_slow<SPLIT, EKV, RAG>), grid, block, lds, st, p, e); break
     switch (ek) {
         case EK_STORE: JKO_SLOW(EK_STORE);
         case EK_BUPDATE: JKO_SLOW(EK_BUPDATE);
@@ -936,49 +985,76 @@ hipError_t launch_slow_ek(int ek, int64_t nb, const Pass& p, const EpiArgs& e, i
     return hipGetLastError();
 }
 
-// Widest band (in 32-panels) of the 32-chunks of an axis of length n.
+// Widest band (in 32-panels) of the 32-chunks of an axis of length n, rounded up.
 int band_panels(int n, int W) {
+    n = round32(n);
     int np = 0;
     for (int i0 = 0; i0 < n; i0 += 32) np = std::max(np, (band_hi32(i0, W, n) - band_lo32(i0, W)) >> 5);
     return np;
+}
+
+// Ragged axes (rounded up to whole panels) keep this form: an iteration is four
+// launches, not six, and the axis passes read ragged rows float by float.
+// Microseconds an iteration, zero energy, axis passes -> these: 45 x 38 x 51
+// FP32 28 -> 23, split 34 -> 22; 63 x 65 x 67 FP32 35 -> 27, split 43 -> 25;
+// 125 x 127 x 123 FP32 74 -> 53, split 92 -> 47.  The exception is a large FP32
+// volume whose axis passes read whole 16-byte runs over two 32-wide chunks and
+// which the rounding up makes 1.3 times as large: 100^3 42 -> 45, 116^3
+// 48 -> 50 (but 92^3 40 -> 38; 124^3, 1.1 times, 54 -> 50; three chunks, 100^3,
+// 50 -> 45).
+bool plane3d_pays(int n0, int n1, int n2, int W0, int W1, int W2, int32_t precision) {
+    const int64_t N = (int64_t)n0 * n1 * n2, M = (int64_t)round32(n0) * round32(n1) * round32(n2);
+    const bool runs = n0 % 4 == 0 && n1 % 4 == 0 && n2 % 4 == 0;
+    return precision == JKO_SPLIT_BF16 || !runs || std::max({W0, W1, W2}) > 16 || N < 900000 || 10 * M <= 13 * N;
 }
 
 }  // namespace
 
 int64_t contract_max_blocks(const Pass& pass, int32_t /*precision*/) { return tiles_of(pass, pick_cfg(pass)); }
 
-bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2) {
-    if (n0 % 32 != 0 || n1 % 32 != 0 || n2 % 32 != 0 || n1 > kPlaneMaxN1) return false;
-    if ((int64_t)n0 * n1 * n2 * 4 >= ((int64_t)1 << 31)) return false;
+bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2, int32_t precision) {
+    if (!plane3d_pays(n0, n1, n2, W0, W1, W2, precision)) return false;
+    if (n0 < kPlaneMinN || n1 < kPlaneMinN || n2 < kPlaneMinN || n1 > kPlaneMaxN1) return false;
+    if ((int64_t)n0 * n1 * n2 * 4 >= kPastEnd) return false;
     const int np2 = band_panels(n2, W2), np0 = band_panels(n0, W0);
     if (np2 > kPanelMax || np0 > kPanelMax || band_panels(n1, W1) > kPlaneQ) return false;
     // dynamic LDS within 64 KiB with the static arrays beside it
-    return plane_lds_bytes(n1, np2) <= 65536 - 2048 && panel_lds_bytes(64, 32, np0) <= 65536 - 2048;
+    return plane_lds_bytes(round32(n1), np2) <= 65536 - 2048 && panel_lds_bytes(64, 32, np0) <= 65536 - 2048;
 }
 
+int plane3d_stride(int n) { return round32(n); }
+
 hipError_t launch_plane3d(const Plane3D& p, int32_t precision, int* nblocks, hipStream_t stream) {
-    const int64_t nb = (int64_t)p.n0 * (p.n2 / 32);
+    const int64_t nb = (int64_t)p.n0 * (round32(p.n2) / 32);
     if (nblocks) *nblocks = (int)nb;
-    const int lds = plane_lds_bytes(p.n1, band_panels(p.n2, p.W2));
-    if (precision == JKO_SPLIT_BF16)
-        hipLaunchKernelGGL(plane_pass<true>, dim3((unsigned)nb), dim3(kPlaneThr), lds, stream, p);
-    else
-        hipLaunchKernelGGL(plane_pass<false>, dim3((unsigned)nb), dim3(kPlaneThr), lds, stream, p);
+    const int lds = plane_lds_bytes(round32(p.n1), band_panels(p.n2, p.W2));
+    const bool rag = p.n1 % 32 != 0 || p.n2 % 32 != 0;
+    const dim3 grid((unsigned)nb), block(kPlaneThr);
+    if (precision == JKO_SPLIT_BF16) {
+        if (rag) hipLaunchKernelGGL((plane_pass<true, true>), grid, block, lds, stream, p);
+        else hipLaunchKernelGGL((plane_pass<true, false>), grid, block, lds, stream, p);
+    } else {
+        if (rag) hipLaunchKernelGGL((plane_pass<false, true>), grid, block, lds, stream, p);
+        else hipLaunchKernelGGL((plane_pass<false, false>), grid, block, lds, stream, p);
+    }
     return hipGetLastError();
 }
 
-int64_t contract_slow_blocks(const Pass& pass) { return (pass.R / 64) * (int64_t)(pass.n / 32); }
+int64_t contract_slow_blocks(const Pass& pass) { return (pass.R + 63) / 64 * (int64_t)((pass.n + 31) / 32); }
 
 hipError_t launch_contract_slow(const Pass& pass, int32_t precision, const EpiArgs& epi, int* nblocks,
                                 hipStream_t stream) {
-    // whole tiles only: every output group of four is complete
-    if (pass.R % 64 != 0 || pass.n % 32 != 0) return hipErrorInvalidValue;
     const int64_t nb = contract_slow_blocks(pass);
     if (nblocks) *nblocks = (int)nb;
     if (nb <= 0) return hipSuccess;
     const int lds = panel_lds_bytes(64, 32, band_panels(pass.n, pass.W));
-    if (precision == JKO_SPLIT_BF16) return launch_slow_ek<true>(ek_of(epi), nb, pass, epi, lds, stream);
-    return launch_slow_ek<false>(ek_of(epi), nb, pass, epi, lds, stream);
+    const bool rag = pass.R % 64 != 0 || pass.n % 32 != 0;
+    const int ek = ek_of(epi);
+    if (precision == JKO_SPLIT_BF16)
+        return rag ? launch_slow_ek<true, true>(ek, nb, pass, epi, lds, stream)
+                   : launch_slow_ek<true, false>(ek, nb, pass, epi, lds, stream);
+    return rag ? launch_slow_ek<false, true>(ek, nb, pass, epi, lds, stream)
+               : launch_slow_ek<false, false>(ek, nb, pass, epi, lds, stream);
 }
 
 hipError_t launch_contract(const Pass& pass, int32_t precision, const EpiArgs& epi, int* nblocks,

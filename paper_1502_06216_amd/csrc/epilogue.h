@@ -233,6 +233,10 @@ __device__ __forceinline__ void st4(float* __restrict__ p, int idx, int cnt, boo
         __builtin_nontemporal_store(v, reinterpret_cast<f4*>(p + idx));
         return;
     }
+    if (cnt == 4) {   // whole, but aligned to a dword only
+        __builtin_nontemporal_store(v, reinterpret_cast<f4_dw*>(p + idx));
+        return;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         if (e < cnt) __builtin_nontemporal_store(v[e], p + idx + e);
@@ -328,6 +332,16 @@ __device__ __forceinline__ EpiIn epi_prefetch(const EpiArgs& E, int idx, int cnt
         }
     }
     return in;
+}
+
+// The inputs moved down by sh elements (1 .. 3), for a group read that many too early.
+__device__ __forceinline__ void epi_shift(EpiIn& in, int sh) {
+    auto down = [&](f4 v) {
+        return sh == 1 ? f4{v[1], v[2], v[3], v[3]} : sh == 2 ? f4{v[2], v[3], v[3], v[3]} : f4{v[3], v[3], v[3], v[3]};
+    };
+    in.u = down(in.u);
+    in.v = down(in.v);
+    in.w = down(in.w);
 }
 
 // Finish `cnt` consecutive outputs idx .. idx+cnt-1 of a contraction whose

@@ -122,23 +122,26 @@ int64_t contract_max_blocks(const Pass& pass, int32_t precision);
 // 3D application in two launches that keep the layout [a][b][c] (c contiguous):
 //   plane pass:  Y[a][b'][c'] = sum_b K1_1[b'][b] sum_c K1_2[c'][c] X[a][b][c]
 //   slow pass:   Y[a'][r] = sum_a K1_0[a'][a] X[a][r]   (r = b n2 + c), + epilogue
-// Same arithmetic, in the same order, as the three axis passes.
+// Same arithmetic as the three axis passes, and in the same order where every axis is a multiple of 32.
 struct Plane3D {
     int n0, n1, n2;        // grid
     int W1, W2;            // band half-widths of the axis-1 and axis-2 factors
-    const float* K1;       // n1 x n1 axis-1 factor (and its bfloat16 split)
+    const float* K1;       // axis-1 factor (and its bfloat16 split), rows of plane3d_stride(n1)
     const uint16_t* K1hi;
     const uint16_t* K1lo;
-    const float* K2;       // n2 x n2 axis-2 factor
+    const float* K2;       // axis-2 factor, rows of plane3d_stride(n2)
     const uint16_t* K2hi;
     const uint16_t* K2lo;
     const float* X;        // input field
     float* Y;              // output field (not X)
     const Ctl* ctl;        // kernels return early when ctl->done
+    bool padded;           // X's allocation is a multiple of 16 bytes long
 };
-bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2);
+int plane3d_stride(int n);   // the factors' row stride: n in whole panels, the columns past n zero
+bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2, int32_t precision);
 hipError_t launch_plane3d(const Plane3D& p, int32_t precision, int* nblocks, hipStream_t stream);
-// Slow-axis pass: Pass.R = n1 n2 columns, Pass.n = n0, X is n0 x R (rows contiguous in r).
+// Slow-axis pass: Pass.R = n1 n2 columns, Pass.n = n0, X is n0 x R (rows contiguous in r), in an
+// allocation of a multiple of 16 bytes; the factor's rows are plane3d_stride(n0) long.
 hipError_t launch_contract_slow(const Pass& pass, int32_t precision, const EpiArgs& epi, int* nblocks,
                                 hipStream_t stream);
 int64_t contract_slow_blocks(const Pass& pass);
@@ -279,7 +282,7 @@ hipError_t launch_resident_pass2d(const ResidentPass2D& r, hipStream_t stream);
 int band_halfwidth(int n, double gamma);
 
 // ----------------------------------------------------------------- pointwise
-hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, double gamma,
+hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int stride, double gamma,
                                hipStream_t s);
 hipError_t launch_fill(float* x, float v, int64_t n, hipStream_t s);
 hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t s);

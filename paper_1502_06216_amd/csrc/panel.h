@@ -173,7 +173,12 @@ __device__ __forceinline__ void lds_copy16(__amdgpu_buffer_rsrc_t rs, void* lds,
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 16, voff, 0, 0, CPOL);
 }
 
-// The same copy as an instruction the compiler does not track.  The compiler
+// A copy of one float per lane, for sources aligned to nothing more.
+__device__ __forceinline__ void lds_copy4(__amdgpu_buffer_rsrc_t rs, void* lds, int voff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void*)lds, 4, voff, 0, 0, 0);
+}
+
+// The 16-byte copy as an instruction the compiler does not track.  The compiler
 // makes every LDS read wait for all the LDS copies it knows to be in flight
 // (it cannot tell which LDS they write), so with tracked copies a read of a
 // landed panel still waits for the whole band; issued this way, the caller

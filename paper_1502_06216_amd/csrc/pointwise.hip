@@ -37,13 +37,14 @@ unsigned blocks_for(int64_t n, int per = 256) {
     return (unsigned)b;
 }
 
-__global__ void k_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, double gamma) {
+// n rows of `stride` >= n columns, those from n on zero; K1 or hi and lo may be NULL.
+__global__ void k_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int stride, double gamma) {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n * n) return;
-    const int i = (int)(idx / n), j = (int)(idx % n);
+    if (idx >= (int64_t)n * stride) return;
+    const int i = (int)(idx / stride), j = (int)(idx % stride);
     const double d = (double)(i - j) / (double)n;
-    const double kd = exp(-(d * d) / gamma);
-    K1[idx] = (float)kd;
+    const double kd = j < n ? exp(-(d * d) / gamma) : 0.0;
+    if (K1) K1[idx] = (float)kd;
     if (hi) {
         const uint16_t h = f2bf_rne((float)kd);
         hi[idx] = h;
@@ -277,10 +278,10 @@ __global__ void k_axpy(float* __restrict__ y, const float* __restrict__ x, int64
 
 }  // namespace
 
-hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, double gamma,
+hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int stride, double gamma,
                                hipStream_t s) {
-    const int64_t nn = (int64_t)n * n;
-    hipLaunchKernelGGL(k_build_factor, dim3(blocks_for(nn)), dim3(256), 0, s, K1, hi, lo, n, gamma);
+    const int64_t nn = (int64_t)n * stride;
+    hipLaunchKernelGGL(k_build_factor, dim3(blocks_for(nn)), dim3(256), 0, s, K1, hi, lo, n, stride, gamma);
     return hipGetLastError();
 }
 
