@@ -224,6 +224,7 @@ struct Plan {
     bool batch2d = false;        // stacked (2, n0, n1) applications: the fused kernel on both fields
     bool batch_pass = false;     // stacked (2, n0, n1) applications: per-field rotating passes, no pass over
                                  // the identity axis
+    bool own_bands = false;      // ... whose blocks compute their factor bands
     bool resident = false;       // ... and a step may run in one resident launch
     bool respass = false;        // a step may run in one launch of the resident pass kernel
     bool plane3d = false;        // 3D applications run as a plane pass and a slow-axis pass
@@ -273,7 +274,9 @@ jko_status carve(Plan* P, const Geo& g, int op, int64_t extra, void* ws, size_t 
     return JKO_OK;
 }
 
-jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
+// once: the caller makes a single product, whose tile kernel computes its own
+// bands (own_bands), so that no factor is stored.
+jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool once = false) {
     P.gamma = gamma;
     for (int k = 0; k < P.g.d; ++k) P.W[k] = band_halfwidth(P.g.n[k], gamma);
     P.plane3d = P.g.d == 3 && !(flags & JKO_FLAG_AXIS_PASSES) &&
@@ -300,6 +303,8 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
     P.fused2d = P.tile != 0;
     P.resident = P.fused2d;
     P.respass = !P.fused2d && passes2d;
+    P.own_bands = once && P.fused2d;
+    if (P.own_bands) return JKO_OK;
     for (int k = 0; k < P.g.d; ++k) {
         if (P.plane3d && plane3d_stride(P.g.n[k]) != P.g.n[k]) {
             // padded rows: only the form that this precision reads, over the
@@ -365,6 +370,7 @@ jko_status apply_xi(const Plan& P, const float* x, EpiArgs epi, int* nblocks) {
     if (P.fused2d) {
         Band2D b{P.g.n[0], P.g.n[1], P.W[0],   P.W[1],   P.K1[0], P.K1[1],
                  x,        P.K1hi[0], P.K1lo[0], P.K1hi[1], P.K1lo[1], P.tile};
+        if (P.own_bands) b.gamma = P.gamma;
         int nb = 0;
         HIP_TRY(launch_gibbs2d(b, P.prec, epi, &nb, P.st));
         if (nblocks) *nblocks = nb;
@@ -1316,7 +1322,7 @@ jko_status jko_gibbs_apply(const jko_grid* grid, double gamma, int32_t precision
     Plan P;
     s = carve(&P, g, OP_GIBBS, 0, ws, ws_bytes, precision, static_cast<hipStream_t>(stream));
     if (s) return s;
-    s = build_factors(P, gamma);
+    s = build_factors(P, gamma, 0, true);
     if (s) return s;
     EpiArgs e{};
     e.kind = EpiKind::STORE;

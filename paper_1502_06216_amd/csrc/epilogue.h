@@ -6,6 +6,7 @@
 #include <math.h>
 
 #include "adjoint.h"
+#include "factor.h"
 #include "jko_internal.h"
 
 namespace jko {
@@ -19,14 +20,6 @@ typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
 constexpr int kThreads = 256;
 
 // ----------------------------------------------------------------- helpers
-
-__device__ __forceinline__ uint16_t f2bf_rne(float x) {
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 // Block-wide FP64 reductions; every thread of the block must call them.
 __device__ inline double block_sum(double v, double* sh) {

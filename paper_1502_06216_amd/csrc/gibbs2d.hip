@@ -336,6 +336,56 @@ __device__ __forceinline__ void stage_bands(const Band2D& B, const Tile<TT>& T, 
     }
 }
 
+// The tile's factor bands from the kernel itself, for a product on its own: an
+// entry depends on |i - k| alone, so a band has fewer distinct entries than a
+// halo edge, and each takes one thread one exponential, which runs while the
+// halo's loads are in flight.  32 x 32: a product is one launch of 4.8 us, not
+// two of 5.8 (the factors) and 5.0 us, and a call among others takes 9.6 us
+// (11.7 before), which the host's share now bounds.
+template <int TT, bool SPLIT>
+__device__ __forceinline__ void build_bands(const Band2D& B, const Tile<TT>& T, Smem<TT, SPLIT>& S) {
+    constexpr int H = Geom<TT>::kHalo;
+    static_assert(kThr >= 512 && H <= 256 && 2 * H <= 8 * 4 * kRS, "one thread per entry, in the partial sums' LDS");
+    constexpr int kS = Smem<TT, SPLIT>::S, kS2 = Smem<TT, SPLIT>::S2;
+    const int tid = threadIdx.x;
+    uint32_t* tab = reinterpret_cast<uint32_t*>(S.red);   // [axis][|i - k|]: a float, or hi and lo
+    const int ax = tid >> 8, diff = tid & 255;
+    if (diff < H) {
+        const double kd = gibbs_entry(diff, ax ? B.n0 : B.n1, B.gamma);
+        if (SPLIT) {
+            uint16_t h, l;
+            gibbs_split(kd, &h, &l);
+            tab[ax * H + diff] = h | ((uint32_t)l << 16);
+        } else {
+            tab[ax * H + diff] = __float_as_uint((float)kd);
+        }
+    }
+    __syncthreads();
+    // axis 1: rows j, then axis 0: rows i (zero outside the grid)
+    auto fill = [&](int axis, int n, int r0, int kb, int L, int Lp, float* kf, uint16_t* kh, uint16_t* kl) {
+        for (int unit = tid; unit < TT * (Lp / 4); unit += kThr) {
+            const int r = unit / (Lp / 4), c = 4 * (unit % (Lp / 4));
+            u32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool in = r0 + r < n && c + e < L;
+                v[e] = in ? tab[axis * H + abs(r0 + r - (kb + c + e))] : 0u;
+            }
+            if (SPLIT) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    kh[r * kS2 + c + e] = (uint16_t)v[e];
+                    kl[r * kS2 + c + e] = (uint16_t)(v[e] >> 16);
+                }
+            } else {
+                *reinterpret_cast<f4*>(&kf[r * kS + c]) = __builtin_bit_cast(f4, v);
+            }
+        }
+    };
+    fill(0, B.n1, T.j0, T.jb0, T.LJ, T.LJp, S.Kj, S.Kjh, S.Kjl);
+    fill(1, B.n0, T.i0, T.ib0, T.LI, T.LIp, S.Ki, S.Kih, S.Kil);
+}
+
 // Both contractions of the staged tile and its epilogue, then the block's
 // partials into slot `slot`.  Xs and the factor bands are staged, not yet
 // synced.  COH: the scalings and partials the epilogue writes use
@@ -463,7 +513,8 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     epi_finish<COH>(E, ea, slot, S.shd);
 }
 
-template <int TT, int EK, bool SPLIT>
+// BUILD: the block computes its factor bands (B.gamma) instead of loading them.
+template <int TT, int EK, bool SPLIT, bool BUILD = false>
 __global__ void __launch_bounds__(kThr)
 gibbs2d_kernel(Band2D B, EpiArgs E) {
     __shared__ __attribute__((aligned(16))) Smem<TT, SPLIT> S;
@@ -485,7 +536,8 @@ gibbs2d_kernel(Band2D B, EpiArgs E) {
     // the staging loads are issued before the LDS stores
     f4 bx[halo_units<TT>()];
     load_halo<TT>(B, T, bx);
-    stage_bands<TT>(B, T, S);
+    if (BUILD) build_bands<TT, SPLIT>(B, T, S);
+    else stage_bands<TT>(B, T, S);
     store_halo<TT, SPLIT>(S, T, bx);
     if (done) return;   // the step has stopped: nothing to compute (uniform)
     contract_tile<TT, EK, false, SPLIT>(E, T, Smem<TT, SPLIT>::S, ein, S, (int)blockIdx.x);
@@ -773,6 +825,10 @@ const void* resident_kernel(int tile, int prox_kind, bool split) {
 
 template <int TT, bool SPLIT>
 void launch_g2(int ek, dim3 grid, dim3 block, const Band2D& b, const EpiArgs& epi, hipStream_t stream) {
+    if (b.gamma > 0.0 && ek == EK_STORE) {
+        hipLaunchKernelGGL((gibbs2d_kernel<TT, EK_STORE, SPLIT, true>), grid, block, 0, stream, b, epi);
+        return;
+    }
 #define JKO_G2(EKV) hipLaunchKernelGGL((gibbs2d_kernel<TT, EKV, SPLIT>), grid, block, 0, stream, b, epi); break
     switch (ek) {
         case EK_STORE: JKO_G2(EK_STORE);

@@ -162,6 +162,8 @@ struct Band2D {
     int tile;              // output tile edge: 16 or 32
     int batch;             // per-application kernel only: this many n0 x n1 fields stacked in X and in
                            // the epilogue's fields, one block per (field, tile); 0 or 1: one field
+    double gamma;          // per-application kernel, STORE epilogue: > 0 and each block computes its
+                           // factor bands from it (K0 .. K1lo are not read)
 };
 // The tile's halo (tile + 2 W, aligned) fits the kernel's LDS.
 bool gibbs2d_fits(int n0, int n1, int W0, int W1, int32_t precision, int tile);

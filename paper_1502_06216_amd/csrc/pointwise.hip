@@ -16,19 +16,12 @@
 
 #include "adjoint.h"
 #include "control.h"
+#include "factor.h"
 #include "jko_internal.h"
 
 namespace jko {
 
 namespace {
-
-__device__ __forceinline__ uint16_t f2bf_rne(float x) {
-    uint32_t u = __float_as_uint(x);
-    if ((u & 0x7f800000u) == 0x7f800000u) return (uint16_t)((u >> 16) | ((u & 0xffffu) ? 0x40u : 0u));
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
-__device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 
 unsigned blocks_for(int64_t n, int per = 256) {
     int64_t b = (n + per - 1) / per;
@@ -42,14 +35,9 @@ __global__ void k_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)n * stride) return;
     const int i = (int)(idx / stride), j = (int)(idx % stride);
-    const double d = (double)(i - j) / (double)n;
-    const double kd = j < n ? exp(-(d * d) / gamma) : 0.0;
+    const double kd = j < n ? gibbs_entry(i - j, n, gamma) : 0.0;
     if (K1) K1[idx] = (float)kd;
-    if (hi) {
-        const uint16_t h = f2bf_rne((float)kd);
-        hi[idx] = h;
-        lo[idx] = f2bf_rne((float)(kd - (double)bf2f(h)));
-    }
+    if (hi) gibbs_split(kd, &hi[idx], &lo[idx]);
 }
 
 __global__ void k_fill(float* x, float v, int64_t n) {

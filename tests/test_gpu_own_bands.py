@@ -1,0 +1,29 @@
+"""A 2D product whose tile blocks compute their factor bands themselves, against
+the same product from stored factors: one iteration of a step under the zero
+energy from a = 1 is b = q / (xi 1), p = xi b, so two products give the step's
+density bit for bit.  Grids at the edges of the tiles of both sizes, narrow and
+wide bands, and bands cut by both edges of the grid."""
+import pytest
+import torch
+
+import paper_1502_06216_amd as jk
+
+from _util import banner, dev
+from workloads import small_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("shape,cells", [((16, 16), 2.0), ((1, 250), 3.0), ((17, 33), 1.0), ((45, 70), 3.0),
+                                         ((201, 161), 3.0), ((256, 256), 4.0), ((64, 48), 5.0), ((300, 270), 2.5),
+                                         ((511, 500), 4.0)])
+def test_same_bits_as_stored_factors(shape, cells, precision):
+    banner(f"own bands {shape} {cells} {precision}")
+    gamma = (cells / max(shape)) ** 2
+    q = dev(small_case(shape, "zero", seed=2).p0)
+    p, _ = jk.step(q, jk.EnergySpec(kind="zero"), gamma, 2.5 * gamma, max_iters=1, precision=precision,
+                   resident=False)
+    t = jk.gibbs_apply(torch.ones_like(q), gamma, precision)
+    b = torch.where(q == 0, torch.zeros_like(q), q / t)
+    assert torch.equal(jk.gibbs_apply(b, gamma, precision), p)
