@@ -224,7 +224,6 @@ struct Plan {
     bool batch2d = false;        // stacked (2, n0, n1) applications: the fused kernel on both fields
     bool batch_pass = false;     // stacked (2, n0, n1) applications: per-field rotating passes, no pass over
                                  // the identity axis
-    bool own_bands = false;      // ... whose blocks compute their factor bands
     bool resident = false;       // ... and a step may run in one resident launch
     bool respass = false;        // a step may run in one launch of the resident pass kernel
     bool plane3d = false;        // 3D applications run as a plane pass and a slow-axis pass
@@ -274,9 +273,9 @@ jko_status carve(Plan* P, const Geo& g, int op, int64_t extra, void* ws, size_t 
     return JKO_OK;
 }
 
-// once: the caller makes a single product, whose tile kernel computes its own
-// bands (own_bands), so that no factor is stored.
-jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool once = false) {
+// The plan's paths, and the stored factors of those that read them (the tile
+// kernels make their own bands).
+jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
     P.gamma = gamma;
     for (int k = 0; k < P.g.d; ++k) P.W[k] = band_halfwidth(P.g.n[k], gamma);
     P.plane3d = P.g.d == 3 && !(flags & JKO_FLAG_AXIS_PASSES) &&
@@ -303,8 +302,7 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool once = f
     P.fused2d = P.tile != 0;
     P.resident = P.fused2d;
     P.respass = !P.fused2d && passes2d;
-    P.own_bands = once && P.fused2d;
-    if (P.own_bands) return JKO_OK;
+    if (P.fused2d) return JKO_OK;
     for (int k = 0; k < P.g.d; ++k) {
         if (P.plane3d && plane3d_stride(P.g.n[k]) != P.g.n[k]) {
             // padded rows: only the form that this precision reads, over the
@@ -360,17 +358,14 @@ Pass slow_of(const Plan& P) {
 jko_status apply_xi(const Plan& P, const float* x, EpiArgs epi, int* nblocks) {
     set_vec(epi);
     if (P.batch2d) {
-        Band2D b{P.g.n[1], P.g.n[2], P.W[1],   P.W[2],   P.K1[1], P.K1[2],
-                 x,        P.K1hi[1], P.K1lo[1], P.K1hi[2], P.K1lo[2], P.tile, P.g.n[0]};
+        Band2D b{P.g.n[1], P.g.n[2], P.W[1], P.W[2], P.gamma, x, P.tile, P.g.n[0], P.owns(x)};
         int nb = 0;
         HIP_TRY(launch_gibbs2d(b, P.prec, epi, &nb, P.st));
         if (nblocks) *nblocks = nb;
         return JKO_OK;
     }
     if (P.fused2d) {
-        Band2D b{P.g.n[0], P.g.n[1], P.W[0],   P.W[1],   P.K1[0], P.K1[1],
-                 x,        P.K1hi[0], P.K1lo[0], P.K1hi[1], P.K1lo[1], P.tile};
-        if (P.own_bands) b.gamma = P.gamma;
+        Band2D b{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.gamma, x, P.tile, 1, P.owns(x)};
         int nb = 0;
         HIP_TRY(launch_gibbs2d(b, P.prec, epi, &nb, P.st));
         if (nblocks) *nblocks = nb;
@@ -740,8 +735,7 @@ jko_status launch_resident(const Plan& P, const float* q, float* p_out, const Pr
                            bool checks, double tol, double absorb, int a_only, bool record_hist, bool* launched) {
     *launched = false;
     Resident2D r{};
-    r.B = Band2D{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.K1[0], P.K1[1], nullptr,
-                 P.K1hi[0], P.K1lo[0], P.K1hi[1], P.K1lo[1], P.tile};
+    r.B = Band2D{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.gamma, nullptr, P.tile};
     r.split = P.prec == JKO_SPLIT_BF16 ? 1 : 0;
     r.q = q;
     r.a = P.F(F_A);
@@ -1322,7 +1316,7 @@ jko_status jko_gibbs_apply(const jko_grid* grid, double gamma, int32_t precision
     Plan P;
     s = carve(&P, g, OP_GIBBS, 0, ws, ws_bytes, precision, static_cast<hipStream_t>(stream));
     if (s) return s;
-    s = build_factors(P, gamma, 0, true);
+    s = build_factors(P, gamma);
     if (s) return s;
     EpiArgs e{};
     e.kind = EpiKind::STORE;
@@ -1619,8 +1613,7 @@ jko_status jko_backward(const jko_grid* grid, const jko_energy* energy, const jk
         if (P.resident && !(params->flags & JKO_FLAG_NO_RESIDENT) &&
             resident_adj_fits(g.n[0], g.n[1], P.W[0], P.W[1], px.kind, P.prec, P.tile)) {
             ResidentAdj r{};
-            r.B = Band2D{g.n[0], g.n[1], P.W[0], P.W[1], P.K1[0], P.K1[1], nullptr,
-                         P.K1hi[0], P.K1lo[0], P.K1hi[1], P.K1lo[1], P.tile};
+            r.B = Band2D{g.n[0], g.n[1], P.W[0], P.W[1], P.gamma, nullptr, P.tile};
             r.q = q;
             r.hist = P.hist(0);
             r.hist_stride = (int64_t)(P.hist(1) - P.hist(0));

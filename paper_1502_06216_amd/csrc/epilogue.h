@@ -203,7 +203,10 @@ struct EpiIn {
     f4 u, v, w;
 };
 
+// NE = 1, here and below: cnt is at most one.
+template <int NE = 4>
 __device__ __forceinline__ f4 ld4(const float* __restrict__ p, int idx, int cnt, bool vec, float fill) {
+    if constexpr (NE == 1) return f4{cnt > 0 ? p[idx] : fill, fill, fill, fill};
     if (vec && cnt == 4) return *reinterpret_cast<const f4*>(p + idx);
     f4 r = f4{fill, fill, fill, fill};
 #pragma unroll
@@ -221,7 +224,12 @@ __device__ __forceinline__ f4 ld4_full(const float* __restrict__ p, int idx) {
 
 // Epilogue results are written with the non-temporal (streaming) hint: each
 // is read once, by the next kernel or pass, usually from another XCD.
+template <int NE = 4>
 __device__ __forceinline__ void st4(float* __restrict__ p, int idx, int cnt, bool vec, f4 v) {
+    if constexpr (NE == 1) {
+        if (cnt > 0) __builtin_nontemporal_store(v[0], p + idx);
+        return;
+    }
     if (vec && cnt == 4) {
         __builtin_nontemporal_store(v, reinterpret_cast<f4*>(p + idx));
         return;
@@ -257,7 +265,12 @@ __device__ __forceinline__ void split_bf16(f4 v0, f4 v1, bf8& hi, bf8& lo) {
 // block of the resident kernel writes and another reads within the launch.
 // A whole aligned run goes out as one 16-byte buffer store with the device
 // scope bit (SC1); the descriptor spans the 2^31 bytes a 32-bit offset reaches.
+template <int NE = 4>
 __device__ __forceinline__ void st4_coh(float* p, int idx, int cnt, bool vec, f4 v) {
+    if constexpr (NE == 1) {
+        if (cnt > 0) __hip_atomic_store(p + idx, v[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     if (vec && cnt == 4) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(p, (short)0, 0x7fffffff, 0x00020000);
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rs, 4 * idx, 0, 16);
@@ -267,8 +280,13 @@ __device__ __forceinline__ void st4_coh(float* p, int idx, int cnt, bool vec, f4
     for (int e = 0; e < 4; ++e)
         if (e < cnt) __hip_atomic_store(p + idx + e, v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <int NE = 4>
 __device__ __forceinline__ f4 ld4_coh(const float* p, int idx, int cnt, float fill) {
-    f4 r;
+    f4 r = f4{fill, fill, fill, fill};
+    if constexpr (NE == 1) {
+        if (cnt > 0) r[0] = __hip_atomic_load(p + idx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return r;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e)
         r[e] = (e < cnt) ? __hip_atomic_load(p + idx + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : fill;
@@ -277,7 +295,7 @@ __device__ __forceinline__ f4 ld4_coh(const float* p, int idx, int cnt, float fi
 
 // COH: accumulators of the adjoint epilogues are read with device-scope loads
 // (the resident reverse sweep writes them with device-scope stores).
-template <int EK, bool COH = false, bool FULL = false>
+template <int EK, bool COH = false, bool FULL = false, int NE = 4>
 __device__ __forceinline__ EpiIn epi_prefetch(const EpiArgs& E, int idx, int cnt) {
     EpiIn in;
     in.u = f4{0.f, 0.f, 0.f, 0.f};
@@ -289,7 +307,7 @@ __device__ __forceinline__ EpiIn epi_prefetch(const EpiArgs& E, int idx, int cnt
     // register copy at a join waits for the load to land
     auto ld4 = [&](const float* p, int i, int c, bool v, float fill) {
         if constexpr (FULL) return ld4_full(p, i);
-        else return jko::ld4(p, i, c, v, fill);
+        else return jko::ld4<NE>(p, i, c, v, fill);
     };
     if (EK == EK_BUPDATE || EK == EK_MONITOR) {
         in.u = ld4(E.q, idx, cnt, vec, 0.f);
@@ -297,7 +315,7 @@ __device__ __forceinline__ EpiIn epi_prefetch(const EpiArgs& E, int idx, int cnt
     } else if (EK == EK_ADJ_B) {
         in.u = ld4(E.hin, idx, cnt, vec, 0.f);
         in.v = ld4(E.q, idx, cnt, vec, 0.f);
-        in.w = COH ? ld4_coh(E.acc, idx, cnt, 0.f) : ld4(E.acc, idx, cnt, vec, 0.f);
+        in.w = COH ? ld4_coh<NE>(E.acc, idx, cnt, 0.f) : ld4(E.acc, idx, cnt, vec, 0.f);
     } else if (EK >= EK_ADJ_PROX) {
         const ProxArgs& px = E.prox;
         in.u = ld4(E.hin, idx, cnt, vec, 0.f);
@@ -354,7 +372,7 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
     if (cnt <= 0) return;
     const bool vec = E.vec_ok && ((idx & 3) == 0);
     if (EK == EK_STORE) {
-        st4(E.y, idx, cnt, vec, val);
+        st4<NE>(E.y, idx, cnt, vec, val);
     } else if (EK == EK_BUPDATE) {
         f4 bn;
 #pragma unroll
@@ -375,9 +393,9 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
             }
         }
         if (LDS) *lds = bn[0];
-        else if (COH) st4_coh(E.b, idx, cnt, vec, bn);
-        else st4(E.b, idx, cnt, vec, bn);
-        if (E.t_out) st4(E.t_out, idx, cnt, vec, val);
+        else if (COH) st4_coh<NE>(E.b, idx, cnt, vec, bn);
+        else st4<NE>(E.b, idx, cnt, vec, bn);
+        if (E.t_out) st4<NE>(E.t_out, idx, cnt, vec, val);
     } else if (EK == EK_ADJ_B) {
         f4 tb, qb;
 #pragma unroll
@@ -387,11 +405,11 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
             qb[e] = (dq != 0.f) ? in.w[e] + dq : in.w[e];
         }
         if (COH) {
-            st4_coh(E.y, idx, cnt, vec, tb);
-            st4_coh(E.acc, idx, cnt, vec, qb);
+            st4_coh<NE>(E.y, idx, cnt, vec, tb);
+            st4_coh<NE>(E.acc, idx, cnt, vec, qb);
         } else {
-            st4(E.y, idx, cnt, vec, tb);
-            st4(E.acc, idx, cnt, vec, qb);
+            st4<NE>(E.y, idx, cnt, vec, tb);
+            st4<NE>(E.acc, idx, cnt, vec, qb);
         }
     } else if (EK >= EK_ADJ_PROX) {
         constexpr int KIND = EK - EK_ADJ_PROX;
@@ -402,15 +420,15 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
             sb[e] = adj_prox_cell<KIND>(E.prox, E.sigma, in.u[e], 0.f, val[e], in.v[e], in.w[e], &d);
             dw[e] = d;
         }
-        if (COH) st4_coh(E.y, idx, cnt, vec, sb);
-        else st4(E.y, idx, cnt, vec, sb);
+        if (COH) st4_coh<NE>(E.y, idx, cnt, vec, sb);
+        else st4<NE>(E.y, idx, cnt, vec, sb);
         if ((KIND == JKO_F_CONGESTION || KIND == JKO_F_GEN_ENTROPY) && E.acc) {
-            f4 wb = COH ? ld4_coh(E.acc, idx, cnt, 0.f) : ld4(E.acc, idx, cnt, vec, 0.f);
+            f4 wb = COH ? ld4_coh<NE>(E.acc, idx, cnt, 0.f) : ld4<NE>(E.acc, idx, cnt, vec, 0.f);
 #pragma unroll
             for (int e = 0; e < NE; ++e)
                 if (dw[e] != 0.f) wb[e] += dw[e];
-            if (COH) st4_coh(E.acc, idx, cnt, vec, wb);
-            else st4(E.acc, idx, cnt, vec, wb);
+            if (COH) st4_coh<NE>(E.acc, idx, cnt, vec, wb);
+            else st4<NE>(E.acc, idx, cnt, vec, wb);
         }
     } else if (EK == EK_MONITOR) {
 #pragma unroll
@@ -446,10 +464,10 @@ __device__ __forceinline__ void epi_apply(const EpiArgs& E, int idx, int cnt, f4
             if (E.check && e < cnt) acc.mass += (double)pn[e];
         }
         if (LDS) *lds = an[0];
-        else if (COH) st4_coh(E.a, idx, cnt, vec, an);
-        else st4(E.a, idx, cnt, vec, an);
-        if (E.write_p) st4(E.p_out, idx, cnt, vec, pn);
-        if (E.s_out) st4(E.s_out, idx, cnt, vec, val);
+        else if (COH) st4_coh<NE>(E.a, idx, cnt, vec, an);
+        else st4<NE>(E.a, idx, cnt, vec, an);
+        if (E.write_p) st4<NE>(E.p_out, idx, cnt, vec, pn);
+        if (E.s_out) st4<NE>(E.s_out, idx, cnt, vec, val);
     }
 }
 

@@ -28,5 +28,14 @@ __device__ __forceinline__ void gibbs_split(double kd, uint16_t* hi, uint16_t* l
     *hi = h;
     *lo = f2bf_rne((float)(kd - (double)bf2f(h)));
 }
+// One entry as a kernel's table of them holds it: the float's bits, or hi and lo.
+template <bool SPLIT>
+__device__ __forceinline__ uint32_t gibbs_bits(int diff, int n, double gamma) {
+    const double kd = gibbs_entry(diff, n, gamma);
+    if (!SPLIT) return __float_as_uint((float)kd);
+    uint16_t h, l;
+    gibbs_split(kd, &h, &l);
+    return h | ((uint32_t)l << 16);
+}
 
 }  // namespace jko

@@ -143,205 +143,78 @@ __device__ __forceinline__ Tile<TT> tile_of(const Band2D& B, int logical, int la
     return T;
 }
 
-template <int TT> constexpr int halo_units() {   // max halo units (4 floats) per thread
-    return (Geom<TT>::kHalo * (Geom<TT>::kHalo / 4) + kThr - 1) / kThr;
-}
-template <int TT> constexpr int band_units() {   // max factor-band units per thread
-    return (TT * (Geom<TT>::kHalo / 4) + kThr - 1) / kThr;
-}
-
-// Issue the loads of the X halo (zero outside the grid).
-template <int TT>
-__device__ __forceinline__ void load_halo(const Band2D& B, const Tile<TT>& T, f4 (&bx)[halo_units<TT>()]) {
-    const int tid = threadIdx.x;
-    const int nux = T.LIp * (T.LJp / 4);
-    const bool vec1 = (B.n1 & 3) == 0;
-#pragma unroll
-    for (int u = 0; u < halo_units<TT>(); ++u) {
-        const int unit = tid + u * kThr;
-        f4 v = f4{0.f, 0.f, 0.f, 0.f};
-        if (unit < nux) {
-            const int r = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            if (r < T.LI) {
-                const float* src = B.X + (T.ib0 + r) * B.n1 + T.jb0 + c;
-                if (vec1 && c + 3 < T.LJ) v = *reinterpret_cast<const f4*>(src);
-                else
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (c + e < T.LJ) ? src[e] : 0.f;
-            }
-        }
-        bx[u] = v;
-    }
-}
-
-// The resident kernels' halo: buffer loads that write LDS directly (16 bytes
-// per lane, 1 KiB per wave), device-scope (SC1) because other blocks of the
-// launch wrote the field.  A row is LJp / 4 chunks and one chunk of padding,
+// The halo: buffer loads that write LDS directly (16 bytes per lane, 1 KiB per
+// wave), in the resident kernels device-scope (SC1) because other blocks of
+// the launch wrote the field.  A row is LJp / 4 chunks and one chunk of padding,
 // so that consecutive chunks are consecutive in LDS and 16 rows read at once
 // fall in distinct banks.  Each lane's offsets are fixed for the launch:
 // beyond the halo, and in the padding, they lie past the buffer and read
 // zeros.  A 16-byte load needs dword alignment only, so rows of any length
 // are loaded whole; where the last chunk of a row reaches past the grid's edge
-// its last elements are the next row's first and meet exact zeros of the
-// factor.  256 x 256, cycles of a phase from the wait's end to the halo in
-// LDS: 3016 by way of registers (its addresses divided out anew, then written
-// to LDS), 1347 so; 201 x 161, whose rows were loaded float by float:
+// its last elements are the next row's first, which the lane that copied them
+// puts to zero once they have landed (a value that isn't finite must not reach
+// the row before).  256 x 256, cycles of a phase from the wait's end to the
+// halo in LDS: 3016 by way of registers (its addresses divided out anew, then
+// written to LDS), 1347 so; 201 x 161, whose rows were loaded float by float:
 // 4754, 1351 so.
 template <int TT> constexpr int halo_copies() {   // max 1 KiB copies per wave
     return (Geom<TT>::kHalo * (Geom<TT>::kHalo / 4 + 1) + kThr - 1) / kThr;
 }
 constexpr int kPastBuffer = 0x7ffffff0;
 
+// Returns the copies (one bit each) whose chunk crosses the end of a grid row.
 template <int TT>
-__device__ __forceinline__ void halo_offsets(const Band2D& B, const Tile<TT>& T, int (&off)[halo_copies<TT>()]) {
+__device__ __forceinline__ uint32_t halo_offsets(const Band2D& B, const Tile<TT>& T, int (&off)[halo_copies<TT>()]) {
     const int cols = T.LJp / 4 + 1;
+    uint32_t cut = 0;
 #pragma unroll
     for (int u = 0; u < halo_copies<TT>(); ++u) {
         const int unit = threadIdx.x + u * kThr;
         const int r = unit / cols, c = 4 * (unit % cols);
         off[u] = (r < T.LI && c < T.LJ) ? 4 * ((T.ib0 + r) * B.n1 + T.jb0 + c) : kPastBuffer;
+        if (r < T.LI && c < T.LJ && T.jb0 + c + 4 > B.n1) cut |= 1u << u;
+    }
+    return cut;
+}
+
+// After the wait for this wave's copies: what came from the next row, to zero.
+template <int TT>
+__device__ __forceinline__ void cut_rows(const Band2D& B, uint32_t cut, float* Xs) {
+    static_assert(halo_copies<TT>() <= 32, "one bit per copy");
+    while (cut) {
+        const int u = __builtin_ctz(cut);
+        cut &= cut - 1;
+        for (int e = B.n1 & 3; e < 4; ++e) Xs[4 * (threadIdx.x + u * kThr) + e] = 0.f;
     }
 }
 
-template <int TT>
-__device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, const int (&off)[halo_copies<TT>()],
-                                          float* Xs) {
-    // (the field's own allocation is a multiple of 256 bytes long)
+template <int TT, int CPOL>
+__device__ __forceinline__ void issue_halo(const Band2D& B, const Tile<TT>& T, const int (&off)[halo_copies<TT>()],
+                                           float* Xs, int nbytes) {
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B.X), (short)0, (B.n0 * B.n1 * 4 + 15) & ~15, kBufRsrcWord3);
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B.X), (short)0, nbytes, kBufRsrcWord3);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int units = T.LIp * (T.LJp / 4 + 1);
 #pragma unroll
     for (int u = 0; u < halo_copies<TT>(); ++u)
-        if (wave * 64 + u * kThr < units) lds_copy16<kCpolCoherent>(rs, Xs + 4 * (wave * 64 + u * kThr), off[u]);
+        if (wave * 64 + u * kThr < units) lds_copy16<CPOL>(rs, Xs + 4 * (wave * 64 + u * kThr), off[u]);
+}
+
+template <int TT>
+__device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, const int (&off)[halo_copies<TT>()],
+                                          uint32_t cut, float* Xs) {
+    // (the field's own allocation is a multiple of 256 bytes long)
+    issue_halo<TT, kCpolCoherent>(B, T, off, Xs, (B.n0 * B.n1 * 4 + 15) & ~15);
     wait_vm_n<0>();
+    cut_rows<TT>(B, cut, Xs);
 }
 
-template <int TT, bool SPLIT>
-__device__ __forceinline__ void store_halo(Smem<TT, SPLIT>& S, const Tile<TT>& T,
-                                           const f4 (&bx)[halo_units<TT>()]) {
-    constexpr int kS = Smem<TT, SPLIT>::S;
-    const int tid = threadIdx.x;
-    const int nux = T.LIp * (T.LJp / 4);
-#pragma unroll
-    for (int u = 0; u < halo_units<TT>(); ++u) {
-        const int unit = tid + u * kThr;
-        if (unit < nux) {
-            const int r = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            *reinterpret_cast<f4*>(&S.Xs[r * kS + c]) = bx[u];
-        }
-    }
-}
-
-// Stage the two FP32 factor bands of the tile (zero outside the band).
-template <int TT>
-__device__ __forceinline__ void stage_bands(const Band2D& B, const Tile<TT>& T, Smem<TT, false>& S) {
-    constexpr int kS = Smem<TT, false>::S;
-    constexpr int UK = band_units<TT>();
-    const int tid = threadIdx.x;
-    const int nkj = TT * (T.LJp / 4), nki = TT * (T.LIp / 4);
-    const bool vec1 = (B.n1 & 3) == 0, vec0 = (B.n0 & 3) == 0;
-    f4 bj[UK], bi[UK];
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-        const int unit = tid + u * kThr;
-        f4 v = f4{0.f, 0.f, 0.f, 0.f};
-        if (unit < nkj) {
-            const int j = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            if (T.j0 + j < B.n1) {
-                const float* src = B.K1 + (int64_t)(T.j0 + j) * B.n1 + T.jb0 + c;
-                if (vec1 && c + 3 < T.LJ) v = *reinterpret_cast<const f4*>(src);
-                else
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (c + e < T.LJ) ? src[e] : 0.f;
-            }
-        }
-        bj[u] = v;
-        f4 w = f4{0.f, 0.f, 0.f, 0.f};
-        if (unit < nki) {
-            const int i = unit / (T.LIp / 4), c = 4 * (unit % (T.LIp / 4));
-            if (T.i0 + i < B.n0) {
-                const float* src = B.K0 + (int64_t)(T.i0 + i) * B.n0 + T.ib0 + c;
-                if (vec0 && c + 3 < T.LI) w = *reinterpret_cast<const f4*>(src);
-                else
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) w[e] = (c + e < T.LI) ? src[e] : 0.f;
-            }
-        }
-        bi[u] = w;
-    }
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-        const int unit = tid + u * kThr;
-        if (unit < nkj) {
-            const int j = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            *reinterpret_cast<f4*>(&S.Kj[j * kS + c]) = bj[u];
-        }
-        if (unit < nki) {
-            const int i = unit / (T.LIp / 4), c = 4 * (unit % (T.LIp / 4));
-            *reinterpret_cast<f4*>(&S.Ki[i * kS + c]) = bi[u];
-        }
-    }
-}
-
-// Split path: stage the bfloat16 hi / lo factor bands (built from the exact
-// factor in double precision), zero outside the band.
-template <int TT>
-__device__ __forceinline__ void stage_bands(const Band2D& B, const Tile<TT>& T, Smem<TT, true>& S) {
-    constexpr int kS2 = Smem<TT, true>::S2;
-    constexpr int UK = band_units<TT>();
-    const int tid = threadIdx.x;
-    const int nkj = TT * (T.LJp / 4), nki = TT * (T.LIp / 4);
-    u16x4 jh[UK], jl[UK], ih[UK], il[UK];
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-        const int unit = tid + u * kThr;
-        jh[u] = jl[u] = ih[u] = il[u] = u16x4{0, 0, 0, 0};
-        if (unit < nkj) {
-            const int j = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            if (T.j0 + j < B.n1) {
-                const int64_t off = (int64_t)(T.j0 + j) * B.n1 + T.jb0 + c;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    jh[u][e] = (c + e < T.LJ) ? B.K1hi[off + e] : (uint16_t)0;
-                    jl[u][e] = (c + e < T.LJ) ? B.K1lo[off + e] : (uint16_t)0;
-                }
-            }
-        }
-        if (unit < nki) {
-            const int i = unit / (T.LIp / 4), c = 4 * (unit % (T.LIp / 4));
-            if (T.i0 + i < B.n0) {
-                const int64_t off = (int64_t)(T.i0 + i) * B.n0 + T.ib0 + c;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ih[u][e] = (c + e < T.LI) ? B.K0hi[off + e] : (uint16_t)0;
-                    il[u][e] = (c + e < T.LI) ? B.K0lo[off + e] : (uint16_t)0;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < UK; ++u) {
-        const int unit = tid + u * kThr;
-        if (unit < nkj) {
-            const int j = unit / (T.LJp / 4), c = 4 * (unit % (T.LJp / 4));
-            *reinterpret_cast<u16x4*>(&S.Kjh[j * kS2 + c]) = jh[u];
-            *reinterpret_cast<u16x4*>(&S.Kjl[j * kS2 + c]) = jl[u];
-        }
-        if (unit < nki) {
-            const int i = unit / (T.LIp / 4), c = 4 * (unit % (T.LIp / 4));
-            *reinterpret_cast<u16x4*>(&S.Kih[i * kS2 + c]) = ih[u];
-            *reinterpret_cast<u16x4*>(&S.Kil[i * kS2 + c]) = il[u];
-        }
-    }
-}
-
-// The tile's factor bands from the kernel itself, for a product on its own: an
-// entry depends on |i - k| alone, so a band has fewer distinct entries than a
-// halo edge, and each takes one thread one exponential, which runs while the
-// halo's loads are in flight.  32 x 32: a product is one launch of 4.8 us, not
-// two of 5.8 (the factors) and 5.0 us, and a call among others takes 9.6 us
-// (11.7 before), which the host's share now bounds.
+// The tile's factor bands.  An entry depends on |i - k| alone, so a band has
+// fewer distinct entries than a halo edge; each takes one thread one
+// exponential (the value that would be stored for the launch otherwise), and
+// the launch path's run while the halo's loads are in flight.  32 x 32: a
+// product is one launch of 4.8 us, not two of 5.8 (storing the factors) and
+// 5.0 us (reading the bands back).
 template <int TT, bool SPLIT>
 __device__ __forceinline__ void build_bands(const Band2D& B, const Tile<TT>& T, Smem<TT, SPLIT>& S) {
     constexpr int H = Geom<TT>::kHalo;
@@ -350,16 +223,7 @@ __device__ __forceinline__ void build_bands(const Band2D& B, const Tile<TT>& T, 
     const int tid = threadIdx.x;
     uint32_t* tab = reinterpret_cast<uint32_t*>(S.red);   // [axis][|i - k|]: a float, or hi and lo
     const int ax = tid >> 8, diff = tid & 255;
-    if (diff < H) {
-        const double kd = gibbs_entry(diff, ax ? B.n0 : B.n1, B.gamma);
-        if (SPLIT) {
-            uint16_t h, l;
-            gibbs_split(kd, &h, &l);
-            tab[ax * H + diff] = h | ((uint32_t)l << 16);
-        } else {
-            tab[ax * H + diff] = __float_as_uint((float)kd);
-        }
-    }
+    if (diff < H) tab[ax * H + diff] = gibbs_bits<SPLIT>(diff, ax ? B.n0 : B.n1, B.gamma);
     __syncthreads();
     // axis 1: rows j, then axis 0: rows i (zero outside the grid)
     auto fill = [&](int axis, int n, int r0, int kb, int L, int Lp, float* kf, uint16_t* kh, uint16_t* kl) {
@@ -513,8 +377,7 @@ __device__ __forceinline__ void contract_tile(const EpiArgs& E, const Tile<TT>& 
     epi_finish<COH>(E, ea, slot, S.shd);
 }
 
-// BUILD: the block computes its factor bands (B.gamma) instead of loading them.
-template <int TT, int EK, bool SPLIT, bool BUILD = false>
+template <int TT, int EK, bool SPLIT>
 __global__ void __launch_bounds__(kThr)
 gibbs2d_kernel(Band2D B, EpiArgs E) {
     __shared__ __attribute__((aligned(16))) Smem<TT, SPLIT> S;
@@ -531,16 +394,28 @@ gibbs2d_kernel(Band2D B, EpiArgs E) {
     // contraction.
     EpiIn ein[Geom<TT>::kOut];
 #pragma unroll
-    for (int u = 0; u < Geom<TT>::kOut; ++u) ein[u] = epi_prefetch<EK>(E, T.eidx[u], T.ecnt[u]);
+    for (int u = 0; u < Geom<TT>::kOut; ++u) ein[u] = epi_prefetch<EK, false, false, 1>(E, T.eidx[u], T.ecnt[u]);
 
-    // the staging loads are issued before the LDS stores
-    f4 bx[halo_units<TT>()];
-    load_halo<TT>(B, T, bx);
-    if (BUILD) build_bands<TT, SPLIT>(B, T, S);
-    else stage_bands<TT>(B, T, S);
-    store_halo<TT, SPLIT>(S, T, bx);
+    // (every copy's LDS and the table's are distinct, so the copies land while
+    // the bands are made)
+    int off[halo_copies<TT>()];
+    const uint32_t cut = halo_offsets<TT>(B, T, off);
+    issue_halo<TT, 0>(B, T, off, S.Xs, B.padded ? (B.n0 * B.n1 * 4 + 15) & ~15 : B.n0 * B.n1 * 4);
+    build_bands<TT, SPLIT>(B, T, S);
+    wait_vm_n<0>();
+    cut_rows<TT>(B, cut, S.Xs);
+    const int xs = T.LJp + 4;
+    const int tail = B.n1 & 3;
+    if (!B.padded && tail && T.ib0 + T.LI == B.n0 && T.jb0 + T.LJ == B.n1) {
+        // the chunk across the buffer's end: its values one by one
+        __syncthreads();
+        if (threadIdx.x < tail) {
+            const int c = T.LJ - tail + threadIdx.x;
+            S.Xs[(T.LI - 1) * xs + c] = B.X[(int64_t)(B.n0 - 1) * B.n1 + T.jb0 + c];
+        }
+    }
     if (done) return;   // the step has stopped: nothing to compute (uniform)
-    contract_tile<TT, EK, false, SPLIT>(E, T, Smem<TT, SPLIT>::S, ein, S, (int)blockIdx.x);
+    contract_tile<TT, EK, false, SPLIT>(E, T, xs, ein, S, (int)blockIdx.x);
 }
 
 // ------------------------------------------------------------ resident kernel
@@ -602,16 +477,16 @@ resident2d(Resident2D R) {
     ep.vec_ok = R.vec_ok;
     ep.part = R.part;
 
-    // factor bands: staged once for the whole launch
-    stage_bands<TT>(B, T, S);
+    // factor bands: made once for the whole launch
+    build_bands<TT, SPLIT>(B, T, S);
     int off[halo_copies<TT>()];
-    halo_offsets<TT>(B, T, off);
+    const uint32_t cut = halo_offsets<TT>(B, T, off);
     // epilogue inputs that do not change over the iteration (q; the energy's fields)
     EpiIn inq[NO], inp[NO];
 #pragma unroll
     for (int u = 0; u < NO; ++u) {
-        inq[u] = epi_prefetch<EK_BUPDATE>(eb, T.eidx[u], T.ecnt[u]);
-        inp[u] = epi_prefetch<PK>(ep, T.eidx[u], T.ecnt[u]);
+        inq[u] = epi_prefetch<EK_BUPDATE, false, false, 1>(eb, T.eidx[u], T.ecnt[u]);
+        inp[u] = epi_prefetch<PK, false, false, 1>(ep, T.eidx[u], T.ecnt[u]);
     }
     __syncthreads();
     const int nn = n_nbr;
@@ -628,7 +503,7 @@ resident2d(Resident2D R) {
         E.check = CHK ? 1 : 0;
         if (EKv >= EK_PROX) E.write_p = CHK ? 1 : 0;
         B.X = X;
-        copy_halo<TT>(B, T, off, S.Xs);
+        copy_halo<TT>(B, T, off, cut, S.Xs);
         contract_tile<TT, EKv, true, SPLIT>(E, T, T.LJp + 4, in, S, slot);
     };
     const std::integral_constant<int, EK_BUPDATE> ekb;
@@ -642,7 +517,7 @@ resident2d(Resident2D R) {
 #pragma unroll
         for (int u = 0; u < NO; ++u) {
             ia[u] = inq[u];
-            if (chk) ia[u].v = ld4_coh(R.b, T.eidx[u], T.ecnt[u], 0.f);
+            if (chk) ia[u].v = ld4_coh<1>(R.b, T.eidx[u], T.ecnt[u], 0.f);
         }
         if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         if (chk) phase(ekb, yes(), eb, ia, R.a);
@@ -743,9 +618,9 @@ resident_adj(ResidentAdj R) {
         n_nbr = neighbours_of<TT>(B, logical, nb, nbr);
         failed = 0;
     }
-    stage_bands<TT>(B, T, S);
+    build_bands<TT, SPLIT>(B, T, S);
     int off[halo_copies<TT>()];
-    halo_offsets<TT>(B, T, off);
+    const uint32_t cut = halo_offsets<TT>(B, T, off);
     EpiArgs eb{};
     eb.kind = EpiKind::ADJ_B;
     eb.q = R.q;
@@ -766,20 +641,20 @@ resident_adj(ResidentAdj R) {
         eb.hin = R.hist + (2 * (int64_t)(k - 1)) * R.hist_stride;
         EpiIn ia[NO];
 #pragma unroll
-        for (int u = 0; u < NO; ++u) ia[u] = epi_prefetch<EK_ADJ_B, true>(eb, T.eidx[u], T.ecnt[u]);
+        for (int u = 0; u < NO; ++u) ia[u] = epi_prefetch<EK_ADJ_B, true, false, 1>(eb, T.eidx[u], T.ecnt[u]);
         if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         B.X = R.sbar;
-        copy_halo<TT>(B, T, off, S.Xs);
+        copy_halo<TT>(B, T, off, cut, S.Xs);
         contract_tile<TT, EK_ADJ_B, true, SPLIT>(eb, T, T.LJp + 4, ia, S, slot);
         publish(R.sync, slot, ++count);
         if (k == 1) break;
         ep.hin = R.hist + (2 * (int64_t)(k - 2) + 1) * R.hist_stride;
         EpiIn ip[NO];
 #pragma unroll
-        for (int u = 0; u < NO; ++u) ip[u] = epi_prefetch<AK, true>(ep, T.eidx[u], T.ecnt[u]);
+        for (int u = 0; u < NO; ++u) ip[u] = epi_prefetch<AK, true, false, 1>(ep, T.eidx[u], T.ecnt[u]);
         if (!wait_for(R.sync, nn, nbr, count, R.spin_limit, &failed)) return;
         B.X = R.tbar;
-        copy_halo<TT>(B, T, off, S.Xs);
+        copy_halo<TT>(B, T, off, cut, S.Xs);
         contract_tile<TT, AK, true, SPLIT>(ep, T, T.LJp + 4, ip, S, slot);
         publish(R.sync, slot, ++count);
     }
@@ -825,10 +700,6 @@ const void* resident_kernel(int tile, int prox_kind, bool split) {
 
 template <int TT, bool SPLIT>
 void launch_g2(int ek, dim3 grid, dim3 block, const Band2D& b, const EpiArgs& epi, hipStream_t stream) {
-    if (b.gamma > 0.0 && ek == EK_STORE) {
-        hipLaunchKernelGGL((gibbs2d_kernel<TT, EK_STORE, SPLIT, true>), grid, block, 0, stream, b, epi);
-        return;
-    }
 #define JKO_G2(EKV) hipLaunchKernelGGL((gibbs2d_kernel<TT, EKV, SPLIT>), grid, block, 0, stream, b, epi); break
     switch (ek) {
         case EK_STORE: JKO_G2(EK_STORE);

@@ -152,18 +152,12 @@ int64_t contract_slow_blocks(const Pass& pass);
 struct Band2D {
     int n0, n1;            // grid
     int W0, W1;            // band half-widths of K1_0, K1_1
-    const float* K0;       // n0 x n0
-    const float* K1;       // n1 x n1
+    double gamma;          // of the factors, whose bands the blocks make themselves
     const float* X;        // n0 x n1 input
-    const uint16_t* K0hi;  // split precision: bfloat16 hi / lo of the factors
-    const uint16_t* K0lo;
-    const uint16_t* K1hi;
-    const uint16_t* K1lo;
     int tile;              // output tile edge: 16 or 32
     int batch;             // per-application kernel only: this many n0 x n1 fields stacked in X and in
                            // the epilogue's fields, one block per (field, tile); 0 or 1: one field
-    double gamma;          // per-application kernel, STORE epilogue: > 0 and each block computes its
-                           // factor bands from it (K0 .. K1lo are not read)
+    bool padded;           // per-application kernel only: X's allocation is a multiple of 16 bytes long
 };
 // The tile's halo (tile + 2 W, aligned) fits the kernel's LDS.
 bool gibbs2d_fits(int n0, int n1, int W0, int W1, int32_t precision, int tile);
@@ -183,7 +177,7 @@ constexpr int64_t resident_sync_words(int64_t nblocks) { return 64 + 16 * nblock
 // the absorption switch the launch returns after that iteration's proximal
 // half-step (ctl->exit_iter) and the host continues on the log-domain passes.
 struct Resident2D {
-    Band2D B;              // geometry and factors (B.X unused)
+    Band2D B;              // geometry and gamma (B.X unused)
     const float* q;        // old density
     float* a;              // scalings, in/out (a starts at 1, or 0 = log 1)
     float* b;
@@ -207,7 +201,7 @@ struct Resident2D {
 // The reverse sweep of one step in one cooperative launch (the adjoint of
 // the above, on the same tiles).
 struct ResidentAdj {
-    Band2D B;              // geometry and factors (B.X unused)
+    Band2D B;              // geometry and gamma (B.X unused)
     const float* q;        // the step's input density
     const float* hist;     // t_k at hist + (2(k-1)) stride, s_k at + stride
     int64_t hist_stride;   // floats

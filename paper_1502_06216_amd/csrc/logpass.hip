@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(kLThr) log_pass_kernel(LogPass L, EpiArgs E) {
         const int f = live ? f_ : 0, i = live ? i0 + il : 0;
         const int64_t idx = contig ? (r0 + f) * n + i : (o * n + i) * L.inner + j0 + f;
         EpiIn in;
-        if (EK != EK_STORE && split == 0) in = epi_prefetch<EK>(E, (int)idx, live ? 1 : 0);
+        if (EK != EK_STORE && split == 0) in = epi_prefetch<EK, false, false, 1>(E, (int)idx, live ? 1 : 0);
 
         // stage the fibres and take each one's largest value
         __syncthreads();   // (the previous item's reads are done)

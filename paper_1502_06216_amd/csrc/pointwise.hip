@@ -299,7 +299,7 @@ hipError_t launch_prepare_energy(const jko_energy* en, double sigma, int64_t N, 
 
 hipError_t launch_attraction_prox(const float* s, float* a, float* p, const float* kappa, float kappa_s,
                                   double alpha, int64_t N, const Ctl* ctl, hipStream_t st) {
-    hipLaunchKernelGGL(k_attraction_prox, dim3(blocks_for(N, 1024)), dim3(256), 0, st, s, a, p, kappa, kappa_s,
+    hipLaunchKernelGGL(k_attraction_prox, dim3(blocks_for(N)), dim3(256), 0, st, s, a, p, kappa, kappa_s,
                        (float)alpha, N, ctl);
     return hipGetLastError();
 }

@@ -134,28 +134,31 @@ small2d(Resident2D R) {
     for (int i = tid; i < L.K1; i += kSThr) lds[i] = 0.f;
     if (tid == 0) C = *R.ctl;
     if (tid < kSTiles) perr[tid] = pmass[tid] = pla[tid] = plb[tid] = 0.0;
+    // (an entry depends on |i - k| alone: one of each, in the partial sums' LDS)
+    uint32_t* const tab = reinterpret_cast<uint32_t*>(red);
+    for (int u = tid; u < n0 + n1; u += kSThr)
+        tab[u] = u < n0 ? gibbs_bits<SPLIT>(u, n0, B.gamma) : gibbs_bits<SPLIT>(u - n0, n1, B.gamma);
+    __syncthreads();
     for (int u = tid; u < 16 * T1 * L.SK1; u += kSThr) {
         const int j = u / L.SK1, c = u % L.SK1;
         const SBand b = band_of(j / 16, n1, B.W1, RND);
-        const bool in = j < n1 && c < b.L;
-        const int off = in ? j * n1 + b.lo + c : 0;
+        const uint32_t v = j < n1 && c < b.L ? tab[n0 + abs(j - b.lo - c)] : 0u;
         if (SPLIT) {
-            K1h[u] = in ? B.K1hi[off] : (uint16_t)0;
-            K1l[u] = in ? B.K1lo[off] : (uint16_t)0;
+            K1h[u] = (uint16_t)v;
+            K1l[u] = (uint16_t)(v >> 16);
         } else {
-            K1f[u] = in ? B.K1[off] : 0.f;
+            K1f[u] = __uint_as_float(v);
         }
     }
     for (int u = tid; u < 16 * L.T0 * L.SK0; u += kSThr) {
         const int i = u / L.SK0, c = u % L.SK0;
         const SBand b = band_of(i / 16, n0, B.W0, RND);
-        const bool in = i < n0 && c < b.L;
-        const int off = in ? i * n0 + b.lo + c : 0;
+        const uint32_t v = i < n0 && c < b.L ? tab[abs(i - b.lo - c)] : 0u;
         if (SPLIT) {
-            K0h[u] = in ? B.K0hi[off] : (uint16_t)0;
-            K0l[u] = in ? B.K0lo[off] : (uint16_t)0;
+            K0h[u] = (uint16_t)v;
+            K0l[u] = (uint16_t)(v >> 16);
         } else {
-            K0f[u] = in ? B.K0[off] : 0.f;
+            K0f[u] = __uint_as_float(v);
         }
     }
 
@@ -182,8 +185,8 @@ small2d(Resident2D R) {
         eidx[v] = i * n1 + j;
         exs[v] = i * L.SX + j;
         erd[v] = (t * L.nch * 4 + (jl & 3)) * kSRow + il + 16 * (jl >> 2);
-        inq[v] = epi_prefetch<EK_BUPDATE>(eb, eidx[v], ecnt[v]);
-        inp[v] = epi_prefetch<PK>(ep, eidx[v], ecnt[v]);
+        inq[v] = epi_prefetch<EK_BUPDATE, false, false, 1>(eb, eidx[v], ecnt[v]);
+        inp[v] = epi_prefetch<PK, false, false, 1>(ep, eidx[v], ecnt[v]);
     }
     __syncthreads();
 #pragma unroll

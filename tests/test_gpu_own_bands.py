@@ -1,8 +1,9 @@
-"""A 2D product whose tile blocks compute their factor bands themselves, against
-the same product from stored factors: one iteration of a step under the zero
-energy from a = 1 is b = q / (xi 1), p = xi b, so two products give the step's
-density bit for bit.  Grids at the edges of the tiles of both sizes, narrow and
-wide bands, and bands cut by both edges of the grid."""
+"""A 2D product of a caller's field (whose memory may start at any float and may
+not be read past its end) against the same product inside a step, whose fields
+lie in the workspace: one iteration under the zero energy from a = 1 is
+b = q / (xi 1), p = xi b, so two products give the step's density bit for bit.
+Grids at the edges of the tiles of both sizes, narrow and wide bands, and bands
+cut by both edges of the grid."""
 import pytest
 import torch
 
@@ -18,7 +19,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape,cells", [((16, 16), 2.0), ((1, 250), 3.0), ((17, 33), 1.0), ((45, 70), 3.0),
                                          ((201, 161), 3.0), ((256, 256), 4.0), ((64, 48), 5.0), ((300, 270), 2.5),
                                          ((511, 500), 4.0)])
-def test_same_bits_as_stored_factors(shape, cells, precision):
+def test_same_bits_as_in_a_step(shape, cells, precision):
     banner(f"own bands {shape} {cells} {precision}")
     gamma = (cells / max(shape)) ** 2
     q = dev(small_case(shape, "zero", seed=2).p0)
@@ -27,3 +28,16 @@ def test_same_bits_as_stored_factors(shape, cells, precision):
     t = jk.gibbs_apply(torch.ones_like(q), gamma, precision)
     b = torch.where(q == 0, torch.zeros_like(q), q / t)
     assert torch.equal(jk.gibbs_apply(b, gamma, precision), p)
+    # the same input one float later, with values behind it that no output may see
+    buf = torch.full((b.numel() + 5,), float("nan"), device=b.device)
+    buf[1:1 + b.numel()] = b.reshape(-1)
+    assert torch.equal(jk.gibbs_apply(buf[1:1 + b.numel()].view(*shape), gamma, precision), p)
+    # a value that isn't finite stays out of the row before its own
+    if min(shape) > 1 and cells * 11 < shape[0] / 4:
+        x = torch.ones_like(q)
+        r = shape[0] // 2
+        x[r, 0] = float("inf")
+        y = jk.gibbs_apply(x, gamma, precision)
+        assert not torch.isfinite(y[r, 0])
+        if cells * 11 + 20 < shape[1]:
+            assert torch.isfinite(y[:, -1]).all()
