@@ -274,8 +274,9 @@ jko_status carve(Plan* P, const Geo& g, int op, int64_t extra, void* ws, size_t 
 }
 
 // The plan's paths, and the stored factors of those that read them (the tile
-// kernels make their own bands).
-jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
+// kernels make their own bands).  stacked: axis 0 holds two fields, and the
+// caller picks a path that keeps them apart.
+jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool stacked = false) {
     P.gamma = gamma;
     for (int k = 0; k < P.g.d; ++k) P.W[k] = band_halfwidth(P.g.n[k], gamma);
     P.plane3d = P.g.d == 3 && !(flags & JKO_FLAG_AXIS_PASSES) &&
@@ -290,7 +291,7 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
     P.tile = 0;
     const bool passes2d =
         P.g.d == 2 && resident_pass2d_shape_fits(P.g.n[0], P.g.n[1], P.W[0], P.W[1], 1);
-    if (P.g.d == 2 && !(flags & JKO_FLAG_AXIS_PASSES))
+    if (P.g.d == 2 && !stacked && !(flags & JKO_FLAG_AXIS_PASSES))
         for (int tt : {16, 32}) {
             if (tt == 32 && passes2d) break;
             if (gibbs2d_fits(P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.prec, tt) &&
@@ -1169,17 +1170,17 @@ jko_status attraction_flow(const Geo& g, const jko_energy* en, const jko_params*
     jko_status s = carve(&P, stacked_of(g), flow ? OP_FLOW : OP_STEP, n_steps, ws, ws_bytes, pr->precision, st);
     if (s) return s;
     if ((s = readback_init())) return s;
-    if ((s = build_factors(P, pr->gamma, pr->flags))) return s;
+    if ((s = build_factors(P, pr->gamma, pr->flags, true))) return s;
     // the stacking axis: gamma -> 0 rounds every off-diagonal entry to zero
     HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[0]), const_cast<uint16_t*>(P.K1hi[0]),
                                 const_cast<uint16_t*>(P.K1lo[0]), 2, 2, 1e-30, P.st));
     P.ident[0] = true;
-    // 2D grids: both couplings in one launch of the fused 2D kernel per
-    // application (axis 0 of the stacked field is the identity)
+    // both couplings in one launch of the fused 2D kernel per application (axis
+    // 0 of the stacked field is the identity; a 1D grid is one column of cells)
     // the resident pass kernel (paired tiles) where the grid and bands suit it
     const bool respass2 = g.d == 2 && !(pr->flags & JKO_FLAG_NO_RESIDENT) &&
                           resident_pass2d_shape_fits(g.n[0], g.n[1], P.W[1], P.W[2], 2);
-    if (g.d == 2 && !respass2 && !(pr->flags & JKO_FLAG_AXIS_PASSES))
+    if (g.d <= 2 && !respass2 && !(pr->flags & JKO_FLAG_AXIS_PASSES))
         for (int tt : {16, 32})
             if (gibbs2d_fits(g.n[0], g.n[1], P.W[1], P.W[2], P.prec, tt) &&
                 gibbs2d_blocks(g.n[0], g.n[1], tt) <= kFusedMaxBlocks) {
