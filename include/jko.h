@@ -175,8 +175,8 @@ typedef struct {
 } jko_params;
 
 /* Execution flags of jko_params.flags.
- * 2D applications of xi run as the fused tile kernel (16 x 16 tiles) where at
- * most 256 tiles cover the grid; else, on axes of a multiple of 32 with at
+ * 1D and 2D applications of xi (a 1D grid is one column of cells) run as the
+ * fused tile kernel (16 x 16 tiles) where at most 256 tiles cover the grid; else, on axes of a multiple of 32 with at
  * most 256 tiles of 32 x 32 and bands of at most seven 32-cell panels, as
  * two per-axis passes; else as the fused kernel with 32 x 32 tiles where it
  * fits, else as the passes.  A step whose applications are fused tiles or
@@ -192,7 +192,7 @@ typedef struct {
  *   chip) and an axis-0 pass; this flag runs three axis passes instead.  Both
  *   give the same bits where every axis is a multiple of 32, and the same
  *   values to rounding on others.
- *   On 2D grids it runs every application as per-axis passes instead of the
+ *   On 1D and 2D grids it runs every application as per-axis passes instead of the
  *   fused tile kernel (and a step on the resident pass kernel where its
  *   shape allows).
  * JKO_FLAG_ABSORB_ON_A: the absorption switch (finite absorb_threshold)

@@ -291,7 +291,10 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool stacked 
     P.tile = 0;
     const bool passes2d =
         P.g.d == 2 && resident_pass2d_shape_fits(P.g.n[0], P.g.n[1], P.W[0], P.W[1], 1);
-    if (P.g.d == 2 && !stacked && !(flags & JKO_FLAG_AXIS_PASSES))
+    // A 1D grid is one column of cells (W[1] = 0).  A step of 50 iterations, as
+    // one launch per application and so, us: 100 cells FP32 581, 227; 467 cells
+    // FP32 654, 371, split 850, 379; 1024 cells, wide band, split 926, 378.
+    if (P.g.d <= 2 && !stacked && !(flags & JKO_FLAG_AXIS_PASSES))
         for (int tt : {16, 32}) {
             if (tt == 32 && passes2d) break;
             if (gibbs2d_fits(P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.prec, tt) &&
