@@ -287,6 +287,7 @@ hipError_t launch_attraction_prox(const float* s, float* a, float* p, const floa
                                   double alpha, int64_t N, const Ctl* ctl, hipStream_t st);
 hipError_t launch_prepare_energy(const jko_energy* en, double sigma, int64_t N, float* g,
                                  float* kf, hipStream_t s);
+hipError_t launch_step_init(Ctl* ctl, int logmode, float* a, float v, int64_t n, hipStream_t s);
 hipError_t launch_ctl_reset(Ctl* ctl, int logmode, hipStream_t s);
 // Sum of the per-block err partials -> ctl->err; stop / non-finite decision;
 // switch to the log domain when max|log a| or max|log b| > absorb (absorb > 0;

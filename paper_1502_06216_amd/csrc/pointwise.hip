@@ -122,21 +122,30 @@ __global__ void k_attraction_prox(const float* __restrict__ s, float* __restrict
     }
 }
 
+__device__ __forceinline__ void ctl_init(Ctl* c, int logmode) {
+    c->done = 0;
+    c->stop_iter = 0;
+    c->nonfinite = 0;
+    c->absorptions = logmode ? 1 : 0;
+    c->absorb_pending = 0;
+    c->logmode = logmode;
+    c->exit_iter = 0;
+    c->err = 0.0;
+    c->mass = 0.0;
+    c->maxloga = 0.0;
+    c->maxlogb = 0.0;
+    for (int i = 0; i < 4; ++i) c->aux[i] = 0.0;
+}
+
 __global__ void k_ctl_reset(Ctl* c, int logmode) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        c->done = 0;
-        c->stop_iter = 0;
-        c->nonfinite = 0;
-        c->absorptions = logmode ? 1 : 0;
-        c->absorb_pending = 0;
-        c->logmode = logmode;
-        c->exit_iter = 0;
-        c->err = 0.0;
-        c->mass = 0.0;
-        c->maxloga = 0.0;
-        c->maxlogb = 0.0;
-        for (int i = 0; i < 4; ++i) c->aux[i] = 0.0;
-    }
+    if (threadIdx.x == 0 && blockIdx.x == 0) ctl_init(c, logmode);
+}
+
+// The control block reset and a = v.
+__global__ void k_step_init(Ctl* c, int logmode, float* a, float v, int64_t n) {
+    if (threadIdx.x == 0 && blockIdx.x == 0) ctl_init(c, logmode);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        a[i] = v;
 }
 
 // Deterministic single-block sum of `n` partials.
@@ -306,6 +315,11 @@ hipError_t launch_attraction_prox(const float* s, float* a, float* p, const floa
 
 hipError_t launch_ctl_reset(Ctl* ctl, int logmode, hipStream_t s) {
     hipLaunchKernelGGL(k_ctl_reset, dim3(1), dim3(64), 0, s, ctl, logmode);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_init(Ctl* ctl, int logmode, float* a, float v, int64_t n, hipStream_t s) {
+    hipLaunchKernelGGL(k_step_init, dim3(blocks_for(n, 1024)), dim3(256), 0, s, ctl, logmode, a, v, n);
     return hipGetLastError();
 }
 
