@@ -449,10 +449,9 @@ def pmc_probe(name, precision):
 
 
 def heat_pass_traffic():
-    """Calibrated HBM bytes of one operator pass (tile pass plus b-update
-    finish) from the
-    committed counter summary, or None when it is missing or the heat
-    kernels' sources changed since it was taken."""
+    """Calibrated memory-side bytes of one product in a step's resident
+    launch from the committed counter summary, or None when it is missing or
+    the kernel's sources changed since it was taken."""
     import re
     path = os.path.join(PROFILES, "heat_pass_heat100.md")
     if not os.path.exists(path):
@@ -460,7 +459,7 @@ def heat_pass_traffic():
     txt = open(path).read()
     m_h = re.search(r"^source_sha256:\s*([0-9a-f]{64})", txt, re.M)
     m_t = re.search(r"^traffic_bytes_per_pass:\s*([0-9]+)", txt, re.M)
-    if not m_h or not m_t or m_h.group(1) != kernel_source_hash("heat.hip"):
+    if not m_h or not m_t or m_h.group(1) != kernel_source_hash("heatres.hip"):
         return None
     return int(m_t.group(1))
 
