@@ -529,7 +529,7 @@ def heat_solve_bench(wl, steps=1, iters=100):
     N = int(np.prod(wl.shape))
     nu = [wl.gamma * n * n / wl.heat_L for n in wl.shape]
     beta = 1.0 + 4.0 * sum(nu)
-    K = _chebyshev_terms(beta, wl.heat_L, 1e-15)
+    K = _chebyshev_terms(beta, wl.heat_L, 10.0 ** -min(21 * wl.heat_L, 85))
     per_product = 48 * math.ceil(K / 16) * N
     achieved = 2 * per_product * it / el / 1e9
     return {"iters_per_s": round(it / el, 2), "grid": list(wl.shape), "free_cells": int(wl.mask.sum()),
@@ -545,7 +545,7 @@ def _chebyshev_terms(beta, L, tol):
     """Terms of the Chebyshev series of x^-L on [1, beta] down to a tail of tol
     (backward recurrence from a degree far in it)."""
     theta, delta = 0.5 * (beta + 1.0), 0.5 * (beta - 1.0)
-    K = int(45.0 / math.log((math.sqrt(beta) + 1.0) / (math.sqrt(beta) - 1.0))) + 16 + 4 * L
+    K = int((25.0 - math.log(tol)) / math.log((math.sqrt(beta) + 1.0) / (math.sqrt(beta) - 1.0))) + 16 + 4 * L
     d = [0.0] * (K + 2)
     d[K] = 1e-200
     for k in range(K, 0, -1):

@@ -341,8 +341,8 @@ jko_status jko_time_iteration(const jko_grid* grid, const jko_energy* energy, co
  * (or with per_product = 1) it stores nothing: each
  * product is the Chebyshev series of (Id - (gamma/L) Delta_M)^-L on the grid
  * in FP64 (one five-point stencil sweep per degree, 16 sweeps per launch on
- * tiles with a halo of 16 cells, to 1e-15 of the input's norm; linear in the
- * grid's size), rounded to float32.  The flow uses the iteration and stop test
+ * tiles with a halo of 16 cells, cut at 1e-85 of the input's norm, for small L
+ * at 1e-21 for each of the L; linear in the grid's size), rounded to float32.  The flow uses the iteration and stop test
  * of jko_step with xi replaced by xi~; float32 only, no log domain, no
  * backward.
  * ------------------------------------------------------------------------ */
@@ -365,8 +365,8 @@ size_t jko_heat_workspace_bytes(const jko_heat_domain* domain);
 /* Builds xi~ for this domain and gamma into the workspace (which then holds
  * it for jko_heat_apply and jko_heat_flow with the same domain and gamma).
  * Each column is the Chebyshev series of (Id - (gamma/L) Delta_M)^-L applied
- * to a unit vector in FP64, to 1e-15, rounded to float32.
- * Synchronous.  Cost: about 25 sqrt(1 + 4 gamma (n0^2 + n1^2) / L)
+ * to a unit vector in FP64, cut at 1e-46 (L = 1, 2: 1e-21, 1e-42), rounded to
+ * float32.  Synchronous.  Cost: about 63 sqrt(1 + 4 gamma (n0^2 + n1^2) / L)
  * stencil sweeps of the grid per column for L = 10. */
 jko_status jko_heat_build(const jko_heat_domain* domain, double gamma, void* workspace,
                           size_t workspace_bytes, void* stream);

@@ -44,9 +44,9 @@ __device__ __forceinline__ bool is_free(const uint8_t* mask, int64_t i) { return
 //   x^-L = c_0 / 2 + sum_k c_k T_k(u) + O(tol)          (heat_series)
 // and xi~ v = M^-L v takes K sweeps of the recurrence
 //   T_0 = v,  T_1 = Mh v,  T_{k+1} = 2 Mh T_k - T_{k-1},   Mh = (M - theta) / delta,
-// each one five-point stencil, where L successive solves take L times a
-// solve's iterations: 75 sweeps instead of 450 for L = 10 and nu = 1
-// (beta = 9).  FP64 throughout.
+// each one five-point stencil: 325 sweeps for L = 10 and nu = 1 (beta = 9), where
+// L successive solves to 1e-13 take 450 and lose more of the tail
+// (heat_series_tol).  FP64 throughout.
 //
 // k_heat_series runs up to kPS sweeps per launch, blocked in time: a block
 // holds T_k and T_{k-1} of a kPTileH x kPTileW tile and a halo of kPS cells
@@ -58,7 +58,7 @@ __device__ __forceinline__ bool is_free(const uint8_t* mask, int64_t i) { return
 // A cell outside the domain holds zeros in every T_k, so the neighbours'
 // weights are the same everywhere and only the diagonal differs by cell.
 // 300 x 300 room, one product: 754 us as L solves (60 launches of 11.9 us, eight
-// sweeps each through LDS, and 10 of 4.8 us), 64 us as five launches of this.
+// sweeps each through LDS, and 10 of 4.8 us), 260 us as 21 launches of this.
 // Bound: launch and load latency (about 4 us of a launch), then FP64 issue:
 // 7 FP64 operations and 4 lane moves per cell and sweep, 12 rows per SIMD.
 constexpr int kPS = kHeatSweeps;           // sweeps per launch = halo width
@@ -386,12 +386,12 @@ struct SeriesPlan {
     HeatSeries s;
     unsigned tiles = 0;
 };
-SeriesPlan series_plan(int n0, int n1, double gamma, int L) {
+SeriesPlan series_plan(int n0, int n1, double gamma, int L, bool stored) {
     SeriesPlan p;
     const double nu0 = n0 > 1 ? gamma * (double)n0 * n0 / L : 0.0;
     const double nu1 = n1 > 1 ? gamma * (double)n1 * n1 / L : 0.0;
     const double beta = 1.0 + 4.0 * (nu0 + nu1);
-    p.s = heat_series(beta, L, kHeatSeriesTol);
+    p.s = heat_series(beta, L, heat_series_tol(L, stored));
     if (p.s.c.empty()) return p;
     p.a.n0 = n0;
     p.a.n1 = n1;
@@ -433,7 +433,7 @@ hipError_t run_series(SeriesPlan& p, double* const T[2], double* const Q[2], uns
 template <int EK>
 hipError_t solve_as(const HeatGemv& g, const HeatSolve& h, hipStream_t st) {
     if (g.N <= 0) return hipSuccess;   // no free cell
-    SeriesPlan p = series_plan(h.n0, h.n1, h.gamma, h.L);
+    SeriesPlan p = series_plan(h.n0, h.n1, h.gamma, h.L, false);
     p.a.mask = h.mask;
     p.a.cidx = h.cidx;
     p.a.x = g.x;
@@ -470,8 +470,10 @@ HeatSeries heat_series(double beta, int L, double tol) try {
     const double theta = 0.5 * (beta + 1.0), delta = 0.5 * (beta - 1.0);
     const double rho = (sqrt(beta) + 1.0) / (sqrt(beta) - 1.0);   // the terms' final ratio
     constexpr double kMost = (double)(1 << 28);   // far beyond a degree that could be run
-    if (!(45.0 / log(rho) < kMost)) return out;
-    int64_t K = (int64_t)(45.0 / log(rho)) + 16 + 4 * (int64_t)L;
+    // e^-25 below the cut, where the recurrence's other solution has died out
+    const double reach = (25.0 - log(tol)) / log(rho);
+    if (!(reach < kMost)) return out;
+    int64_t K = (int64_t)reach + 16 + 4 * (int64_t)L;
     std::vector<double> d;   // (-1)^k c_k
     double sum = 0.0;
     for (;;) {
@@ -485,7 +487,7 @@ HeatSeries heat_series(double beta, int L, double tol) try {
         }
         sum = 0.5 * d[0];
         for (int64_t k = 1; k <= K; ++k) sum += d[(size_t)k];
-        if (d[(size_t)K] <= 1e-25 * sum) break;
+        if (d[(size_t)K] <= 1e-10 * tol * sum) break;
         if ((K *= 2) > (int64_t)kMost) return out;
     }
     double tail = 0.0;
@@ -504,7 +506,7 @@ hipError_t heat_build_operator(const uint8_t* mask, int n0, int n1, double gamma
     const int64_t N = (int64_t)n0 * n1;
     hipLaunchKernelGGL(k_heat_zero, dim3(grid_for(heat_operator_floats(nf))), dim3(256), 0, st, A,
                        heat_operator_floats(nf));
-    SeriesPlan p = series_plan(n0, n1, gamma, L);
+    SeriesPlan p = series_plan(n0, n1, gamma, L, true);
     // columns per chunk: T and Q twice each, and Y
     const int64_t C = std::max<int64_t>(1, 4 * ((int64_t)1 << chunk_log2(N)) / 5);
     p.a.mask = mask;
