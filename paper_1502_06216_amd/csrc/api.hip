@@ -736,7 +736,8 @@ jko_status launch_respass(const Plan& P, int B, int W0, int W1, int k0, int k1, 
 // because part of the device is unavailable: the caller then runs the launch
 // path instead.
 jko_status launch_resident(const Plan& P, const float* q, float* p_out, const ProxArgs& px, int K, int ce,
-                           bool checks, double tol, double absorb, int a_only, bool record_hist, bool* launched) {
+                           bool checks, double tol, double absorb, int a_only, bool record_hist, bool tiles,
+                           bool* launched) {
     *launched = false;
     Resident2D r{};
     r.B = Band2D{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.gamma, nullptr, P.tile};
@@ -757,6 +758,7 @@ jko_status launch_resident(const Plan& P, const float* q, float* p_out, const Pr
     r.tol = tol;
     r.absorb = absorb;
     r.a_only = a_only;
+    r.tiles = tiles ? 1 : 0;
     r.spin_limit = kBarrierSpinLimit;
     EpiArgs al{};
     al.q = q;
@@ -779,9 +781,16 @@ jko_status launch_resident(const Plan& P, const float* q, float* p_out, const Pr
     return JKO_OK;
 }
 
-// Synchronous: the control block and, in the same copy, the word that says a
-// wait of the last resident launch ran out (a failure).
-jko_status read_ctl_resident(const Plan& P, Ctl* out) {
+// The word that a resident launch leaves: a failure where a wait ran out, and
+// *redo where the one-block kernel asks for the step again on the tile kernel.
+jko_status resident_word(uint32_t w, bool* redo) {
+    if (redo) *redo = w == kResidentRedo;
+    if (w && w != kResidentRedo) return fail(JKO_ERR_HIP, "resident kernel: a wait for another block timed out");
+    return JKO_OK;
+}
+
+// Synchronous: the control block and, in the same copy, that word.
+jko_status read_ctl_resident(const Plan& P, Ctl* out, bool* redo) {
     constexpr size_t kWord = (sizeof(Ctl) + kAlign - 1) / kAlign * kAlign;   // layout_of: sync follows ctl
     static_assert(kWord + sizeof(uint32_t) <= 4 * sizeof(Ctl), "within the read-back buffer");
     HIP_TRY(hipMemcpyAsync(rb().host, P.ctl, kWord + sizeof(uint32_t), hipMemcpyDeviceToHost, P.st));
@@ -789,18 +798,16 @@ jko_status read_ctl_resident(const Plan& P, Ctl* out) {
     *out = *rb().host;
     uint32_t w = 0;
     memcpy(&w, reinterpret_cast<const char*>(rb().host) + kWord, sizeof w);
-    if (w) return fail(JKO_ERR_HIP, "resident kernel: a wait for another block timed out");
-    return JKO_OK;
+    return resident_word(w, redo);
 }
 
-// Synchronous: fails if a wait of the last resident launch ran out.
-jko_status resident_check(const Plan& P) {
+// Synchronous: the word alone.
+jko_status resident_check(const Plan& P, bool* redo = nullptr) {
     uint32_t w = 0;
     HIP_TRY(hipMemcpyAsync(rb().host, P.sync, sizeof w, hipMemcpyDeviceToHost, P.st));
     HIP_TRY(hipStreamSynchronize(P.st));
     memcpy(&w, rb().host, sizeof w);
-    if (w) return fail(JKO_ERR_HIP, "resident kernel: a wait for another block timed out");
-    return JKO_OK;
+    return resident_word(w, redo);
 }
 
 // ----------------------------------------------------------------- one step
@@ -813,9 +820,10 @@ struct StepOut {
 // `record_hist` is set, iteration k stores t_k and s_k into
 // P.hist(2(k-1)) and P.hist(2(k-1)+1) (adjoint recomputation, fixed count).
 // `st_out` (host) and `st_dev` (device, 8 doubles) receive the statistics;
-// only the host record makes the step wait for them.
+// only the host record makes the step wait for them.  tiles: no one-block kernel.
 jko_status run_step(const Plan& P, const jko_params* pr, const ProxArgs& px, const float* q, float* p_out,
-                    bool want_stats, bool record_hist, jko_stats* st_out, double* st_dev = nullptr) {
+                    bool want_stats, bool record_hist, jko_stats* st_out, double* st_dev = nullptr,
+                    bool tiles = false) {
     const int K = pr->max_iters;
     const int ce = pr->check_every;
     const bool tolmode = pr->tol_l1 > 0.0;
@@ -855,19 +863,22 @@ jko_status run_step(const Plan& P, const jko_params* pr, const ProxArgs& px, con
     int k0 = 1;   // first iteration left to the launch path
     bool resident = false;
     bool unread = false;   // a resident launch whose outcome the closing read-back brings
+    bool redo = false;
+    auto again = [&]() { return run_step(P, pr, px, q, p_out, want_stats, record_hist, st_out, st_dev, true); };
     const bool respass = !logd && use_respass(P, pr, px, record_hist);
     if (!logd && (respass || use_resident(P, pr, px))) {
         jko_status s = respass ? launch_respass(P, 1, P.W[0], P.W[1], 0, 1, q, p_out, px, 0.f, K, ce, checks,
                                                 pr->tol_l1, absorb, a_only, &resident)
                                : launch_resident(P, q, p_out, px, K, ce, checks, pr->tol_l1, absorb, a_only,
-                                                 record_hist, &resident);
+                                                 record_hist, tiles, &resident);
         if (s) return s;
         if (resident && absorb > 0.0) {
             // The kernel returns after the proximal half-step of an iteration
             // whose check asked for the switch: convert the scalings and run
             // the rest of the step on the log-domain passes.
             Ctl c{};
-            if ((s = read_ctl_resident(P, &c))) return s;
+            if ((s = read_ctl_resident(P, &c, &redo))) return s;
+            if (redo) return again();
             if (c.exit_iter > 0 && !c.done) {
                 HIP_TRY(launch_absorb(P.ctl, a, b, P.g.N, P.st));
                 HIP_TRY(launch_ctl_commit(P.ctl, c.exit_iter, P.st));
@@ -881,7 +892,8 @@ jko_status run_step(const Plan& P, const jko_params* pr, const ProxArgs& px, con
             // read-back brings both: one wait a step, not three.  A 40-cell
             // step of 50 iterations: 179 us with three, 152 with one.
             unread = tolmode || want_stats;
-            if (!unread && (s = resident_check(P))) return s;
+            if (!unread && (s = resident_check(P, &redo))) return s;
+            if (redo) return again();
         }
     }
 
@@ -981,7 +993,8 @@ jko_status run_step(const Plan& P, const jko_params* pr, const ProxArgs& px, con
     Ctl c{};
     if (unread) {
         jko_status s = want_stats || st_dev ? monitor() : JKO_OK;
-        if (s || (s = read_ctl_resident(P, &c))) return s;
+        if (s || (s = read_ctl_resident(P, &c, &redo))) return s;
+        if (redo) return again();
     } else if (tolmode || want_stats) {
         jko_status s = read_ctl(P, &c);
         if (s) return s;
@@ -1508,7 +1521,7 @@ jko_status jko_time_iteration(const jko_grid* grid, const jko_energy* energy, co
             s = respass ? launch_respass(P, 1, P.W[0], P.W[1], 0, 1, p_in, nullptr, px, 0.f, params->max_iters, 1,
                                          false, 0.0, 0.0, 0, &launched)
                         : launch_resident(P, p_in, P.F(F_Z1), px, params->max_iters, 1, false, 0.0, 0.0, 0, false,
-                                          &launched);
+                                          false, &launched);
             if (s) break;
             if (!launched) {
                 s = fail(JKO_ERR_HIP, "the cooperative grid of the resident kernel was refused");

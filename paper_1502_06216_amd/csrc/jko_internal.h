@@ -195,6 +195,7 @@ struct Resident2D {
     int32_t spin_limit;    // polls before a wait gives up
     int32_t split;         // split-BF16 contractions
     int32_t a_only;        // the absorption trigger watches max|log a| alone
+    int32_t tiles;         // on the tile kernel, also where one block would do
     double tol;
     double absorb;
 };
@@ -225,6 +226,9 @@ bool resident2d_fits(int n0, int n1, int W0, int W1, int prox_kind, int32_t prec
 hipError_t launch_resident2d(const Resident2D& r, hipStream_t stream);
 
 // The same on a small grid in one block (small2d.hip): no other block to wait for.
+// It leaves kResidentRedo in the first sync word where a product wasn't finite:
+// run the step again on the tile kernel (Resident2D::tiles).
+constexpr uint32_t kResidentRedo = 2;
 bool small2d_fits(int n0, int n1, int W0, int W1, bool split);
 hipError_t launch_small2d(const Resident2D& r, hipStream_t stream);
 

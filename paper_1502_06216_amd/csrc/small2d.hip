@@ -10,7 +10,12 @@
 // 16- or 32-k chunks of Y^T = Z^T K1_0^T each from zero into LDS, their sum in
 // chunk order and the epilogue in the tile kernel's lanes, the FP64 partial
 // sums wave by wave and tile by tile.  So the bits are those of the tile
-// kernel and of the launch path.
+// kernel and of the launch path, as long as every product is finite: that
+// kernel has zeros past a tile's halo, the rows here go on to the next tile's
+// cells, and a zero of the factor cancels a finite value there, not an infinite
+// one.  A product that isn't finite is therefore reported (kResidentRedo), and the
+// step runs again on the tile kernel.  (Zeros in place of what lies past the
+// halos, selected as the rows are read: 7 to 15 % of an iteration.)
 //
 // Bound: MFMA issue plus three barriers and two LDS round trips per
 // application, about 0.4 us of latency.  The MFMA work of all tiles falls on
@@ -194,6 +199,7 @@ small2d(Resident2D R) {
         if (ecnt[v]) Xs[exs[v]] = R.a[eidx[v]];
     __syncthreads();
 
+    float trace = 0.f;   // NaN once a product of this thread's wasn't finite
     float bold[kSV];   // this thread's b (the scaling the violation is taken with)
 #pragma unroll
     for (int v = 0; v < kSV; ++v) bold[v] = 0.f;
@@ -261,6 +267,7 @@ small2d(Resident2D R) {
                 for (int w = 0; w < 4; ++w) c[w] = w < nch ? red[erd[v] + w * 4 * kSRow] : 0.f;
                 float y = ((c[0] + c[1]) + c[2]) + c[3];
                 for (int w = 4; w < nch; ++w) y += red[erd[v] + w * 4 * kSRow];
+                trace = __builtin_fmaf(y, 0.f, trace);
                 float out;
                 epi_apply<EKv, false, 1, true>(E, eidx[v], 1, f4{y, 0.f, 0.f, 0.f}, false, in[v], ea, &out);
                 Xs[exs[v]] = out;
@@ -301,8 +308,12 @@ small2d(Resident2D R) {
     };
     const std::integral_constant<int, EK_BUPDATE> ekb;
     const std::integral_constant<int, PK> ekp;
-    // the scalings to memory, where the launch ends
+    // where the launch ends: the report, and the scalings to memory
+    auto report = [&]() {
+        if (trace != 0.f) *R.sync = kResidentRedo;
+    };
     auto keep = [&]() {
+        report();
 #pragma unroll
         for (int v = 0; v < kSV; ++v)
             if (ecnt[v]) {
@@ -346,7 +357,10 @@ small2d(Resident2D R) {
                 g->maxloga = C.maxloga;
                 g->maxlogb = C.maxlogb;
             }
-            if (C.done) return;   // (the step returns the p of the last candidate)
+            if (C.done) {   // (the step returns the p of the last candidate)
+                report();
+                return;
+            }
             switching = C.absorb_pending != 0;
         } else {
             phase(ekb, no(), eb, inq);

@@ -2,13 +2,14 @@
 16 x 16) against the launch-per-application path: the same tile arithmetic and
 order of sums, so the same bits, on grids at the edges of its tiles, chunks and
 selection (the last two are beyond it in FP32)."""
+import numpy as np
 import pytest
 import torch
 
 import paper_1502_06216_amd as jk
 from workloads import small_case
 
-from _util import banner, dev, energies
+from _util import banner, dev, energies, host64
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,23 @@ def test_step_and_gradient_same_bits(shape, width, precision):
         assert torch.equal(a, b), f"max |diff| {float((a - b).abs().max()):.3e}"
     for k in KEYS:
         assert out[0][1][k] == out[1][1][k], k
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("shape", [(64, 64), (48, 40), (33, 61), (200,)])
+def test_values_that_are_not_finite_stay_where_they_are(shape, precision):
+    """An infinite scaling reaches the tiles whose halo holds its cell, and no other: the one-block kernel's rows
+    go on past a tile's halo, where the tile kernel has zeros (every cell the same, NaN for NaN)."""
+    banner(f"small non-finite {shape} {precision}")
+    n = max(shape)
+    gamma = (1.2 / n) ** 2
+    rng = np.random.default_rng(5)
+    p = dev(rng.uniform(0.5, 1.5, shape) / np.prod(shape))
+    for cell in rng.choice(int(np.prod(shape)), 12, replace=False):
+        w, kappa = np.zeros(shape), np.full(shape, 2.0)
+        w.flat[cell], kappa.flat[cell] = -1e30, np.inf     # p = s exp(-sigma w) = inf there, and a = p / s
+        en = jk.EnergySpec(kind="congestion", w=dev(w), kappa=dev(kappa))
+        got, ref = [host64(jk.step(p, en, gamma, 4 * gamma, max_iters=2, precision=precision, with_stats=False,
+                                   resident=r)[0]) for r in (True, False)]
+        assert not np.isfinite(ref).all()
+        np.testing.assert_array_equal(got, ref)
