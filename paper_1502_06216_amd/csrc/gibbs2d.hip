@@ -797,7 +797,8 @@ bool resident2d_fits(int n0, int n1, int W0, int W1, int prox_kind, int32_t prec
 }
 
 hipError_t launch_resident2d(const Resident2D& r, hipStream_t stream) {
-    if (!r.tiles && r.B.tile == 16 && small2d_fits(r.B.n0, r.B.n1, r.B.W0, r.B.W1, r.split != 0))
+    if (!r.tiles && r.B.tile == 16 &&
+        small2d_fits(r.B.n0, r.B.n1, r.B.W0, r.B.W1, r.split != 0, r.prox.kind, r.checks ? r.ce : 0))
         return launch_small2d(r, stream);
     const int64_t nb = gibbs2d_blocks(r.B.n0, r.B.n1, r.B.tile);
     Resident2D arg = r;

@@ -229,7 +229,8 @@ hipError_t launch_resident2d(const Resident2D& r, hipStream_t stream);
 // It leaves kResidentRedo in the first sync word where a product wasn't finite:
 // run the step again on the tile kernel (Resident2D::tiles).
 constexpr uint32_t kResidentRedo = 2;
-bool small2d_fits(int n0, int n1, int W0, int W1, bool split);
+// ce: the check cadence, 0 without checks.
+bool small2d_fits(int n0, int n1, int W0, int W1, bool split, int prox_kind, int ce);
 hipError_t launch_small2d(const Resident2D& r, hipStream_t stream);
 
 // A whole 2D step in one cooperative launch with every application of xi

@@ -36,7 +36,7 @@ namespace {
 
 constexpr int kSThr = 1024;
 constexpr int kSWaves = kSThr / 64;
-constexpr int kSTiles = 16;                  // at most this many 16 x 16 tiles
+constexpr int kSTiles = 16;                  // at most this many 16 x 16 tiles (small2d_fits)
 constexpr int kSV = kSTiles * 4 / kSWaves;   // tile-kernel waves each wave stands in for
 constexpr int kSMostWork = 1792;             // FP32: tiles x k (see small2d_fits)
 constexpr int kSUnits = 4;                   // k-chunks of the second contraction per wave, at most
@@ -390,15 +390,26 @@ const void* small_kernel_of(int kind) {
 
 }  // namespace
 
-bool small2d_fits(int n0, int n1, int W0, int W1, bool split) {
-    if ((int64_t)((n0 + 15) / 16) * ((n1 + 15) / 16) > kSTiles) return false;
+bool small2d_fits(int n0, int n1, int W0, int W1, bool split, int kind, int ce) {
+    // The epilogues of all tiles and the sums of a check fall on one CU as well,
+    // where the tile kernel spreads them.  Where the lines lie, us of 50
+    // iterations, this form against the tile kernel, the generalised entropy's
+    // Newton steps or the crowd's one, band 5 cells wide:
+    //   Newton: 7 tiles 16 x 112 FP32 437 / 409, split 410 / 428, 100 cells on a
+    //     line FP32 398 / 454; 8 tiles 32 x 64 FP32 469 / 395, split 424 / 399; 12
+    //     tiles 180 cells FP32 639 / 469; 16 tiles 64 x 64 split 754 / 413
+    //   no checks: 64 x 64 split 310 / 360
+    //   a check every 3 iterations: 10 tiles 16 x 160 FP32 412 / 432, split 358 /
+    //     448; 12 tiles 48 x 64 FP32 454 / 415; every iteration split 648 / 610
+    //   every 4: 48 x 64 FP32 421 / 406, split 353 / 403; 64 x 64 split 426 / 399
+    //   every 10: 64 x 64 split 349 / 375
+    const bool newton = kind == JKO_F_POROUS || kind == JKO_F_GEN_ENTROPY;
+    const int most = newton ? 7 : ce == 0 ? kSTiles : ce < 4 || !split ? 10 : ce < 10 ? 12 : kSTiles;
+    if ((int64_t)((n0 + 15) / 16) * ((n1 + 15) / 16) > most) return false;
     const SLayout L = layout_small(n0, n1, W0, W1, split);
     if (L.NT * L.nch > kSUnits * kSWaves || L.total * (int64_t)sizeof(float) > 144 * 1024) return false;
     // FP32: the tiles' k-steps, NT (Lp0 + Lp1) / 4 products of 32 cycles over
-    // four matrix units.  Where the line lies (us per iteration, this form
-    // against the tile kernel): 64 x 64 at band 15, 1536: 5.5 / 6.4; 64 x 48 at
-    // band 42, 1344: 5.2 / 5.9; 64 x 64 at band 42, 2048: 7.2 / 6.3.  Split-BF16
-    // is ahead everywhere (64 x 64 at band 42: 4.6 / 6.2).
+    // four matrix units.  64 x 48 at band 42, 1344: 5.2 / 5.9.
     return split || L.NT * (16 * L.nch + max_extent(n1, W1, 16)) <= kSMostWork;
 }
 

@@ -2,6 +2,8 @@
 16 x 16) against the launch-per-application path: the same tile arithmetic and
 order of sums, so the same bits, on grids at the edges of its tiles, chunks and
 selection (the last two are beyond it in FP32)."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -56,3 +58,28 @@ def test_values_that_are_not_finite_stay_where_they_are(shape, precision):
                                    resident=r)[0]) for r in (True, False)]
         assert not np.isfinite(ref).all()
         np.testing.assert_array_equal(got, ref)
+
+
+def _us(shape, kind, precision, **kw):
+    """The fastest of several steps of 50 iterations, in microseconds."""
+    n = float(np.prod(shape))
+    p = np.random.default_rng(3).uniform(0.5, 1.5, shape)
+    p = dev(p / p.sum())
+    gamma = (3.0 / max(shape)) ** 2
+    en = jk.EnergySpec(kind=kind, kappa_scalar=float(p.max()), m=1.5, density_scale=n)
+    best = np.inf
+    for _ in range(20):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        jk.step(p, en, gamma, 2 * gamma, max_iters=50, precision=precision, **kw)
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return 1e6 * best
+
+
+@pytest.mark.parametrize("kind,kw", [("gen_entropy", {}), ("porous", {}), ("congestion", dict(tol=1e-30, check_every=1))])
+def test_a_smaller_grid_is_not_slower(kind, kw):
+    """16 tiles against the 20 of a grid that only the tile kernel takes (a fifth more is the clock's)."""
+    small, large = [_us(s, kind, "split_bf16", **kw) for s in ((64, 64), (64, 80))]
+    banner(f"small {kind} {kw}: 64 x 64 {small:.0f} us, 64 x 80 {large:.0f} us")
+    assert small <= 1.2 * large
