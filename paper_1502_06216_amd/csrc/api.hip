@@ -14,6 +14,7 @@
 // block says the step is done, so the GPU never idles on the read-back.
 #include <math.h>
 #include <stdarg.h>
+#include <stddef.h>
 #include <stdio.h>
 #include <string.h>
 
@@ -1887,47 +1888,41 @@ jko_status heat_step(const HeatLayout& H, char* base, int64_t nf, const HeatSolv
     bool bytol = false;
     double h[3] = {0.0, 0.0, 0.0};
     int k0 = 1;   // first iteration left to one launch per product
+    double stop_err = -1.0;   // the violation that ended the resident step
     if (!H.solve && heat_resident_fits(gt.nT, kind)) {
-        // the resident kernel, in one launch or, in tolerance mode, in one
-        // launch up to each check's t = A a
         HeatResident r{};
         r.t = gt;
         r.s = gs;
+        r.tol = pr->tol_l1;
         r.spin_limit = kBarrierSpinLimit;
         r.sync = reinterpret_cast<uint32_t*>(base + H.sync);
-        const int64_t total = 2 * (int64_t)pr->max_iters;
-        if (total < INT32_MAX) {
-            k0 = pr->max_iters + 1;
-            int64_t next_check = tolmode ? 2 * (int64_t)pr->check_every : total;   // product of the next check
-            for (int64_t done = 0; done < total;) {
-                const int64_t last = std::min(total, tolmode ? next_check + 1 : total);
-                r.first = (int32_t)done;
-                r.last = (int32_t)last;
-                r.check = tolmode && last == next_check + 1 ? 1 : 0;
-                HIP_TRY(launch_fill(reinterpret_cast<float*>(r.sync), 0.f, heat_resident_sync_words(), st));
-                const hipError_t e = launch_heat_resident(r, kind, st);
-                if (e == hipErrorCooperativeLaunchTooLarge && done == 0) {
-                    (void)hipGetLastError();
-                    k0 = 1;
-                    break;
-                }
+        const int64_t total = 2 * (int64_t)pr->max_iters, period = 2 * (int64_t)pr->check_every;
+        if (total < (1 << 30)) {   // (two phases a product, counted in 31 bits)
+            r.last = (int32_t)total;
+            r.period = tolmode && period < total ? (int32_t)period : 0;
+            HIP_TRY(launch_fill(reinterpret_cast<float*>(r.sync), 0.f, heat_resident_sync_words(), st));
+            const hipError_t e = launch_heat_resident(r, kind, st);
+            if (e == hipErrorCooperativeLaunchTooLarge) {
+                (void)hipGetLastError();
+            } else {
                 HIP_TRY(e);
-                uint32_t w = 0;
+                struct {
+                    uint32_t abort, unused;
+                    HeatOutcome o;
+                } w;
+                static_assert(offsetof(decltype(w), o) == kHeatOutcome * sizeof(uint32_t), "sync words");
                 HIP_TRY(hipMemcpyAsync(rb().host, r.sync, sizeof w, hipMemcpyDeviceToHost, st));
                 HIP_TRY(hipStreamSynchronize(st));
                 memcpy(&w, rb().host, sizeof w);
-                if (w) return fail(JKO_ERR_HIP, "resident heat kernel: a wait for another block timed out");
-                done = last;
-                if (r.check) {
-                    jko_status s = heat_sums(err, nf, nullptr, 0, dout, st, h);
-                    if (s) return s;
-                    if (h[2] > 0.0) break;
-                    if (h[0] <= pr->tol_l1) {
-                        iters = (int)(next_check / 2);
+                if (w.abort) return fail(JKO_ERR_HIP, "resident heat kernel: a wait for another block timed out");
+                k0 = pr->max_iters + 1;
+                if (w.o.prod > 0) {
+                    h[2] = w.o.bad ? 1.0 : 0.0;
+                    if (!w.o.bad && w.o.err <= pr->tol_l1) {
+                        stop_err = w.o.err;
+                        iters = w.o.prod / 2;
                         bytol = true;
-                        break;
                     }
-                    next_check += 2 * (int64_t)pr->check_every;
                 }
             }
         }
@@ -1954,6 +1949,7 @@ jko_status heat_step(const HeatLayout& H, char* base, int64_t nf, const HeatSolv
     }
     jko_status s = heat_sums(err, nf, p_out, H.N, dout, st, h);
     if (s) return s;
+    if (stop_err >= 0.0) h[0] = stop_err;
     const bool bad = h[2] > 0.0 || !isfinite(h[0]) || !isfinite(h[1]);
     if (st_out) {
         jko_stats& o = *st_out;

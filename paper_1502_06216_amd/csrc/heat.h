@@ -156,17 +156,24 @@ enum : int { HEAT_EK_STORE = 0, HEAT_EK_BUPDATE = 1, HEAT_EK_MONITOR = 2, HEAT_E
 
 hipError_t launch_heat_gemv(int ek, const HeatGemv& g, hipStream_t st);
 
-// Products [first, last) of a step's iteration with the stored operator in one
-// cooperative launch (heatres.hip): product 2 (k - 1) is t = A a with the
-// b-update of iteration k (record t), product 2 (k - 1) + 1 is s = A b with the
-// proximal update (record s, whose p is written by the launch's last one).
+// The products of a step's iteration with the stored operator in one cooperative
+// launch (heatres.hip): product 2 (k - 1) is t = A a with the b-update of
+// iteration k (record t), product 2 (k - 1) + 1 is s = A b with the proximal
+// update (record s, whose p is written where the step may end).
 struct HeatResident {
     HeatGemv t, s;
-    int32_t first, last;
-    int32_t check;           // the last product, a t = A a, writes errrow
+    int32_t last;            // products
+    int32_t period;          // a check with every t = A a at a multiple of this (> 0) product; 0: none
+    double tol;              // the step ends at a check whose violation is at most this, or not finite
     int32_t spin_limit;      // polls before a wait gives up
     uint32_t* sync;          // heat_resident_sync_words() words, zeroed before the launch; [0] != 0
-                             // afterwards: a wait ran out
+                             // afterwards: a wait ran out; a HeatOutcome at [kHeatOutcome]
+};
+constexpr int kHeatOutcome = 2;
+struct HeatOutcome {         // of the last check
+    int32_t prod;            // its product (0: there was none)
+    int32_t bad;             // entries that weren't finite
+    double err;              // the sum of the others
 };
 int64_t heat_resident_sync_words();
 bool heat_resident_fits(int nT, int kind);

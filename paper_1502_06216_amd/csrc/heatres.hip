@@ -29,6 +29,7 @@
 // 80 x 80 (all kept) 16.1 us, 64 x 64 13.8 us.
 #include <algorithm>
 
+#include "epilogue.h"
 #include "heat_tile.h"
 
 namespace jko {
@@ -42,8 +43,10 @@ constexpr int kMaxTiles = 16;    // tiles of one block
 constexpr int kMaxBlocks = 256;
 constexpr int kSlotBytes = 4 * kHeatTile;
 constexpr int kSlots = 12;       // slots of a cell per wave: nT <= 90 with at most 16 x 256 tiles
-// Sync words: [0] abort; the blocks' phase counts from kFlag0, packed; from kGo
-// the number of phases all blocks have finished, in kGoCopies lines.  Block 0
+// Sync words: [0] abort, the outcome of the last check from kHeatOutcome; the
+// blocks' phase counts from kFlag0, packed; from kGo the number of phases all
+// blocks have finished, with kStop set where the step ends there, in kGoCopies
+// lines.  Block 0
 // alone reads the counts and writes the copies, each polled by a sixteenth of
 // the blocks: with every block polling every count, or one atomic counter, 256
 // requests at a time queue for the same line (6 us a wait; an iteration of the
@@ -52,6 +55,7 @@ constexpr int kFlag0 = 64;
 constexpr int kGo = kFlag0 + kMaxBlocks;
 constexpr int kGoCopies = 16;
 constexpr int kGoStride = 64;
+constexpr uint32_t kStop = 1u << 31;
 
 __device__ __forceinline__ bool poll(const uint32_t* word, uint32_t count, uint32_t* sync, int spin_limit) {
     for (int spins = 0; __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < count; ++spins) {
@@ -76,18 +80,29 @@ __device__ __forceinline__ void publish_phase(uint32_t* sync, int slot, uint32_t
 }
 
 // Every block has finished `count` phases (bounded; the abort word is watched).
+// decide(): block 0's, between the two: the step ends here.  Returns whether to
+// go on.
+template <typename Decide>
 __device__ __forceinline__ bool wait_all(uint32_t* sync, int slot, int nb, uint32_t count, int spin_limit,
-                                         uint32_t* failed) {
+                                         uint32_t* failed, Decide decide) {
     const int t = threadIdx.x;
     if (slot == 0) {
         if (t < nb && !poll(sync + kFlag0 + t, count, sync, spin_limit)) *failed = 1;
         __syncthreads();
-        if (t < kGoCopies && *failed == 0)
-            __hip_atomic_store(sync + kGo + kGoStride * t, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        if (t == 0 && !poll(sync + kGo + kGoStride * (slot % kGoCopies), count, sync, spin_limit)) *failed = 1;
-        __syncthreads();
+        if (*failed != 0) return false;
+        const bool stop = decide();   // (the same in every thread)
+        if (t < kGoCopies)
+            __hip_atomic_store(sync + kGo + kGoStride * t, count | (stop ? kStop : 0u), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        return !stop;
     }
+    if (t == 0) {
+        const uint32_t* go = sync + kGo + kGoStride * (slot % kGoCopies);
+        if (!poll(go, count, sync, spin_limit) ||
+            (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStop))
+            *failed = 1;
+    }
+    __syncthreads();
     return *failed == 0;
 }
 
@@ -123,6 +138,8 @@ heat_resident(HeatResident R) {
     __shared__ float rows[kHeatWaves][kHeatTile];                               // a run's row sums by wave
     __shared__ float red[kHeatWaves][64];
     __shared__ uint32_t failed;
+    __shared__ double shd[kHeatWaves];
+    __shared__ uint32_t word;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int nb = (int)gridDim.x, slot = (int)blockIdx.x;
     const HeatGemv& G = R.t;
@@ -195,8 +212,35 @@ heat_resident(HeatResident R) {
     uint32_t count = 0;
     const int rg = lane >> 2, coff = 4 * (16 * wave + 4 * (lane & 3) + (lane >> 4));
 
-    for (int prod = R.first; prod < R.last; ++prod) {
+    auto no_decision = []() { return false; };
+    // Block 0, after product `prod`: the violation of the iterate before it, in a
+    // fixed order; the step ends where it is small enough, or not finite.
+    auto outcome = [&](int prod) {
+        double e = 0.0, bad = 0.0;
+        for (int64_t i = tid; i < G.N; i += kHeatThr) {
+            const double v = __hip_atomic_load(G.errrow + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (isfinite(v)) e += v;
+            else bad += 1.0;
+        }
+        e = block_sum(e, shd);
+        bad = block_sum(bad, shd);
+        if (tid == 0) {   // (every thread's sums are wave 0's: block_sum)
+            HeatOutcome* o = reinterpret_cast<HeatOutcome*>(R.sync + kHeatOutcome);
+            o->prod = prod;
+            o->bad = bad > 0.0 ? 1 : 0;
+            o->err = e;
+            word = bad > 0.0 || e <= R.tol ? 1u : 0u;
+        }
+        __syncthreads();
+        return word != 0u;
+    };
+
+    int to_check = R.period;   // products up to the next check
+    for (int prod = 0; prod < R.last; ++prod) {
         const bool bstep = (prod & 1) == 0;   // t = A a, b = q / t; else s = A b, p = Prox(s), a = p / s
+        const bool chk = R.period > 0 && to_check == 0;
+        if (chk) to_check = R.period;
+        --to_check;
         const float* x = bstep ? R.t.x : R.s.x;
         // ---- tiles
         f4 xv[(2 * kMaxTiles * kHeatTile / 4 + kHeatThr - 1) / kHeatThr];
@@ -207,7 +251,7 @@ heat_resident(HeatResident R) {
                 xv[v] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rs_x, xoff[v], 0, kCoh));
         }
         int sn = 0;   // streamed tile on its way (waves 1 .. 7: since before the wait)
-        if (ns > 0 && (wave == 0 || prod == R.first)) load_tile(str, rs_A, b0 + s0, voff);
+        if (ns > 0 && (wave == 0 || prod == 0)) load_tile(str, rs_A, b0 + s0, voff);
 #pragma unroll
         for (int v = 0; v < (int)(sizeof xv / sizeof xv[0]); ++v)
             if (tid + v * kHeatThr < 2 * m * (kHeatTile / 4))
@@ -280,7 +324,7 @@ heat_resident(HeatResident R) {
         }
         close_run();
         publish_phase(R.sync, slot, ++count);
-        if (!wait_all(R.sync, slot, nb, count, R.spin_limit, &failed)) return;
+        if (!wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision)) return;
 
         // ---- finish: wave w sums slots w, w + 8, ..., wave 0 adds the waves' sums in order
         float y = 0.f;
@@ -301,20 +345,24 @@ heat_resident(HeatResident R) {
 #pragma unroll
             for (int w = 1; w < kHeatWaves; ++w) v += red[w][lane];
             if (bstep) {
-                if (R.check && prod + 1 == R.last) G.errrow[cell] = fabs((double)bold * (double)v - (double)q);
+                if (chk)
+                    __hip_atomic_store(G.errrow + cell, fabs((double)bold * (double)v - (double)q), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
                 bold = q == 0.f ? 0.f : q / v;
                 coh_store(rsrc_of(G.b, nT * kSlotBytes), 4 * cell, 0, bold);
             } else {
                 const float p = prox_val<KIND>(R.s.px, v, pu, pv);
                 coh_store(rsrc_of(R.s.a, nT * kSlotBytes), 4 * cell, 0, p == 0.f ? 0.f : p / v);
-                if (prod + 2 >= R.last) R.s.p[gi] = p;   // (the launch's last one)
+                if (to_check == 0 || prod + 1 == R.last) R.s.p[gi] = p;   // (what a check or the end returns)
             }
         }
         if (prod + 1 == R.last) break;
         publish_phase(R.sync, slot, ++count);
         // (wave 0 polls: its loads would have to land first)
         if (ns > 0 && wave != 0) load_tile(str, rs_A, b0 + s0, voff);
-        if (!wait_all(R.sync, slot, nb, count, R.spin_limit, &failed)) return;
+        const bool on = chk ? wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, [&]() { return outcome(prod); })
+                            : wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision);
+        if (!on) return;
     }
 }
 

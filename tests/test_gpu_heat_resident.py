@@ -2,6 +2,8 @@
 the per-product form, which shares none of its code but the epilogue: operators
 of few and of many tiles (with streamed ones), tolerance mode at several check
 cadences, every energy."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -61,3 +63,59 @@ def test_energies(kind):
         assert (a != b).mean() < 0.01
     else:
         assert rel_l1(a, b) <= TOL
+
+
+@pytest.mark.parametrize("shape", [(30, 40), (104, 103)])
+@pytest.mark.parametrize("ce", [1, 2, 5])
+def test_a_stop_returns_the_checked_iterate(shape, ce):
+    """A step that stops by tolerance returns, bit for bit, the iterate whose violation was small enough, and one
+    that does not runs to its cap; the checks change nothing else."""
+    banner(f"heat resident stop {shape} ce={ce}")
+    wl = heat_room(*shape, seed=5)
+    en, _ = energies(wl)
+    op = _ops(wl)[0]
+    p, st = op.step(dev(wl.p0), en, wl.tau, max_iters=40, tol=1e-4, check_every=ce)
+    assert st["stop"] == "tol" and st["iters"] % ce == 0 and 0 < st["iters"] < 40
+    assert st["marginal_l1"] <= 1e-4
+    k = st["iters"]
+    q, sq = op.step(dev(wl.p0), en, wl.tau, max_iters=k)
+    assert torch.equal(p, q)
+    assert sq["marginal_l1"] == pytest.approx(st["marginal_l1"], rel=1e-3)
+    if k > ce:      # the check before did not pass
+        assert op.step(dev(wl.p0), en, wl.tau, max_iters=k - ce)[1]["marginal_l1"] > 1e-4
+    p, st = op.step(dev(wl.p0), en, wl.tau, max_iters=k, tol=1e-30, check_every=ce)
+    assert (st["stop"], st["iters"]) == ("cap", k) and torch.equal(p, q)
+
+
+@pytest.mark.parametrize("ce", [1, 3, 50])
+def test_a_value_that_is_not_finite_ends_the_step(ce):
+    banner(f"heat resident not finite ce={ce}")
+    n = 512
+    x = np.arange(n) - 0.15 * n
+    p = np.exp(-x * x / 8.0)
+    p[p < 1e-6 * p.max()] = 0.0
+    gamma = 10.0 / n ** 2
+    op = jk.HeatOperator((1, n), gamma, 10)
+    with pytest.raises(jk.JKOError):
+        op.step(dev(p[None] / p.sum()), jk.EnergySpec(kind="entropy"), 10.0 * gamma, max_iters=100, tol=1e-6,
+                check_every=ce)
+
+
+def test_checks_cost_little():
+    """64 x 64: a check after each of 60 iterations against none at all."""
+    banner("heat resident check cost")
+    wl = heat_room(64, 64, seed=5)
+    en, _ = energies(wl)
+    op = _ops(wl)[0]
+    best = []
+    for kw in (dict(), dict(tol=1e-30, check_every=1)):
+        us = []
+        for _ in range(20):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            op.step(dev(wl.p0), en, wl.tau, max_iters=60, **kw)
+            torch.cuda.synchronize()
+            us.append(1e6 * (time.perf_counter() - t))
+        best.append(min(us))
+    print(f"[gpu-test] heat resident 64 x 64: {best[0]:.0f} us, with checks {best[1]:.0f}", flush=True)
+    assert best[1] <= 2.0 * best[0]
