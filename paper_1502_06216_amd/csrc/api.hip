@@ -1889,17 +1889,18 @@ jko_status heat_step(const HeatLayout& H, char* base, int64_t nf, const HeatSolv
     double h[3] = {0.0, 0.0, 0.0};
     int k0 = 1;   // first iteration left to one launch per product
     double stop_err = -1.0;   // the violation that ended the resident step
-    if (!H.solve && heat_resident_fits(gt.nT, kind)) {
+    const int64_t total = 2 * (int64_t)pr->max_iters, period = 2 * (int64_t)pr->check_every;   // products
+    const bool check = tolmode && period < total;
+    if (!H.solve && heat_resident_fits(gt.nT, kind, check)) {
         HeatResident r{};
         r.t = gt;
         r.s = gs;
         r.tol = pr->tol_l1;
         r.spin_limit = kBarrierSpinLimit;
         r.sync = reinterpret_cast<uint32_t*>(base + H.sync);
-        const int64_t total = 2 * (int64_t)pr->max_iters, period = 2 * (int64_t)pr->check_every;
         if (total < (1 << 30)) {   // (two phases a product, counted in 31 bits)
             r.last = (int32_t)total;
-            r.period = tolmode && period < total ? (int32_t)period : 0;
+            r.period = check ? (int32_t)period : 0;
             HIP_TRY(launch_fill(reinterpret_cast<float*>(r.sync), 0.f, heat_resident_sync_words(), st));
             const hipError_t e = launch_heat_resident(r, kind, st);
             if (e == hipErrorCooperativeLaunchTooLarge) {

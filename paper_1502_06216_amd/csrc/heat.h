@@ -176,7 +176,7 @@ struct HeatOutcome {         // of the last check
     double err;              // the sum of the others
 };
 int64_t heat_resident_sync_words();
-bool heat_resident_fits(int nT, int kind);
+bool heat_resident_fits(int nT, int kind, bool check);   // check: with a stop test (period > 0)
 hipError_t launch_heat_resident(const HeatResident& r, int kind, hipStream_t st);
 
 // x[0..n) = v, x[n..ld) = 0

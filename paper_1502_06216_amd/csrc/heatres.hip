@@ -80,9 +80,9 @@ __device__ __forceinline__ void publish_phase(uint32_t* sync, int slot, uint32_t
 }
 
 // Every block has finished `count` phases (bounded; the abort word is watched).
-// decide(): block 0's, between the two: the step ends here.  Returns whether to
-// go on.
-template <typename Decide>
+// CHECK: block 0 decides between the two whether the step ends here (decide(),
+// the same in every thread).  Returns whether to go on.
+template <bool CHECK, typename Decide>
 __device__ __forceinline__ bool wait_all(uint32_t* sync, int slot, int nb, uint32_t count, int spin_limit,
                                          uint32_t* failed, Decide decide) {
     const int t = threadIdx.x;
@@ -90,7 +90,7 @@ __device__ __forceinline__ bool wait_all(uint32_t* sync, int slot, int nb, uint3
         if (t < nb && !poll(sync + kFlag0 + t, count, sync, spin_limit)) *failed = 1;
         __syncthreads();
         if (*failed != 0) return false;
-        const bool stop = decide();   // (the same in every thread)
+        const bool stop = CHECK && decide();
         if (t < kGoCopies)
             __hip_atomic_store(sync + kGo + kGoStride * t, count | (stop ? kStop : 0u), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -98,8 +98,9 @@ __device__ __forceinline__ bool wait_all(uint32_t* sync, int slot, int nb, uint3
     }
     if (t == 0) {
         const uint32_t* go = sync + kGo + kGoStride * (slot % kGoCopies);
+        // (the word is read again where it may tell to stop: the poll keeps the shorter loop)
         if (!poll(go, count, sync, spin_limit) ||
-            (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStop))
+            (CHECK && (__hip_atomic_load(go, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kStop)))
             *failed = 1;
     }
     __syncthreads();
@@ -130,7 +131,9 @@ __device__ __forceinline__ void load_tile(HeatTileRegs& t, __amdgpu_buffer_rsrc_
 // A value that is the same in every lane, in a scalar register.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
-template <int KIND>
+// CHECK: with a stop test (R.period > 0); its code alone costs a step without one
+// 1 to 3 %.
+template <int KIND, bool CHECK>
 __global__ void __launch_bounds__(kHeatThr)
 heat_resident(HeatResident R) {
     extern __shared__ __attribute__((aligned(16))) float kept[];   // kLdsTiles operator tiles
@@ -238,9 +241,9 @@ heat_resident(HeatResident R) {
     int to_check = R.period;   // products up to the next check
     for (int prod = 0; prod < R.last; ++prod) {
         const bool bstep = (prod & 1) == 0;   // t = A a, b = q / t; else s = A b, p = Prox(s), a = p / s
-        const bool chk = R.period > 0 && to_check == 0;
+        const bool chk = CHECK && to_check == 0;
         if (chk) to_check = R.period;
-        --to_check;
+        if (CHECK) --to_check;
         const float* x = bstep ? R.t.x : R.s.x;
         // ---- tiles
         f4 xv[(2 * kMaxTiles * kHeatTile / 4 + kHeatThr - 1) / kHeatThr];
@@ -324,7 +327,7 @@ heat_resident(HeatResident R) {
         }
         close_run();
         publish_phase(R.sync, slot, ++count);
-        if (!wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision)) return;
+        if (!wait_all<false>(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision)) return;
 
         // ---- finish: wave w sums slots w, w + 8, ..., wave 0 adds the waves' sums in order
         float y = 0.f;
@@ -353,30 +356,35 @@ heat_resident(HeatResident R) {
             } else {
                 const float p = prox_val<KIND>(R.s.px, v, pu, pv);
                 coh_store(rsrc_of(R.s.a, nT * kSlotBytes), 4 * cell, 0, p == 0.f ? 0.f : p / v);
-                if (to_check == 0 || prod + 1 == R.last) R.s.p[gi] = p;   // (what a check or the end returns)
+                if ((CHECK && to_check == 0) || prod + 1 == R.last) R.s.p[gi] = p;   // (what a check or the end returns)
             }
         }
         if (prod + 1 == R.last) break;
         publish_phase(R.sync, slot, ++count);
         // (wave 0 polls: its loads would have to land first)
         if (ns > 0 && wave != 0) load_tile(str, rs_A, b0 + s0, voff);
-        const bool on = chk ? wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, [&]() { return outcome(prod); })
-                            : wait_all(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision);
-        if (!on) return;
+        if (chk) {
+            if (!wait_all<true>(R.sync, slot, nb, count, R.spin_limit, &failed, [&]() { return outcome(prod); })) return;
+        } else if (!wait_all<false>(R.sync, slot, nb, count, R.spin_limit, &failed, no_decision)) {
+            return;
+        }
     }
 }
 
-const void* kernel_of(int kind) {
+template <bool CHECK>
+const void* kernel_as(int kind) {
     switch (kind) {
-        case JKO_F_ZERO: return reinterpret_cast<const void*>(&heat_resident<JKO_F_ZERO>);
-        case JKO_F_CONGESTION: return reinterpret_cast<const void*>(&heat_resident<JKO_F_CONGESTION>);
-        case JKO_F_POROUS: return reinterpret_cast<const void*>(&heat_resident<JKO_F_POROUS>);
-        case JKO_F_ENTROPY: return reinterpret_cast<const void*>(&heat_resident<JKO_F_ENTROPY>);
-        case JKO_F_CONGESTION_BINARY: return reinterpret_cast<const void*>(&heat_resident<JKO_F_CONGESTION_BINARY>);
-        case JKO_F_GEN_ENTROPY: return reinterpret_cast<const void*>(&heat_resident<JKO_F_GEN_ENTROPY>);
+        case JKO_F_ZERO: return reinterpret_cast<const void*>(&heat_resident<JKO_F_ZERO, CHECK>);
+        case JKO_F_CONGESTION: return reinterpret_cast<const void*>(&heat_resident<JKO_F_CONGESTION, CHECK>);
+        case JKO_F_POROUS: return reinterpret_cast<const void*>(&heat_resident<JKO_F_POROUS, CHECK>);
+        case JKO_F_ENTROPY: return reinterpret_cast<const void*>(&heat_resident<JKO_F_ENTROPY, CHECK>);
+        case JKO_F_CONGESTION_BINARY:
+            return reinterpret_cast<const void*>(&heat_resident<JKO_F_CONGESTION_BINARY, CHECK>);
+        case JKO_F_GEN_ENTROPY: return reinterpret_cast<const void*>(&heat_resident<JKO_F_GEN_ENTROPY, CHECK>);
         default: return nullptr;
     }
 }
+const void* kernel_of(int kind, bool check) { return check ? kernel_as<true>(kind) : kernel_as<false>(kind); }
 
 int blocks_of(int nT) { return (int)std::min<int64_t>((int64_t)nT * (nT + 1) / 2, kMaxBlocks); }
 size_t lds_of(int nT) {
@@ -388,8 +396,8 @@ size_t lds_of(int nT) {
 
 int64_t heat_resident_sync_words() { return kGo + kGoStride * kGoCopies; }
 
-bool heat_resident_fits(int nT, int kind) {
-    const void* fn = kernel_of(kind);
+bool heat_resident_fits(int nT, int kind, bool check) {
+    const void* fn = kernel_of(kind, check);
     // (fewer row blocks leave a block more than 64 cells to finish)
     if (!fn || nT < 3) return false;
     const int64_t T = (int64_t)nT * (nT + 1) / 2, nb = blocks_of(nT);
@@ -403,7 +411,7 @@ bool heat_resident_fits(int nT, int kind) {
 }
 
 hipError_t launch_heat_resident(const HeatResident& r, int kind, hipStream_t st) {
-    const void* fn = kernel_of(kind);
+    const void* fn = kernel_of(kind, r.period > 0);
     if (!fn) return hipErrorInvalidValue;
     HeatResident arg = r;
     void* args[] = {&arg};
