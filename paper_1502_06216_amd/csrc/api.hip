@@ -214,6 +214,7 @@ struct Plan {
     const float* K1[3] = {};
     const uint16_t* K1hi[3] = {};
     const uint16_t* K1lo[3] = {};
+    const uint32_t* tab[3] = {}; // the factors' entries by distance, where tile launches read them stored
     float* field[24] = {};
     hipStream_t st = nullptr;
     int prec = 0;
@@ -274,10 +275,20 @@ jko_status carve(Plan* P, const Geo& g, int op, int64_t extra, void* ws, size_t 
     return JKO_OK;
 }
 
-// The plan's paths, and the stored factors of those that read them (the tile
-// kernels make their own bands).  stacked: axis 0 holds two fields, and the
-// caller picks a path that keeps them apart.
-jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool stacked = false) {
+// The entries of axes k0 and k1 by distance, where their factors would lie, for
+// the many tile launches of a step on the launch path.  identity: along k0 (gamma
+// -> 0 rounds every entry but the first to zero).
+jko_status build_tables(Plan& P, int k0, int k1, bool identity = false) {
+    P.tab[k0] = reinterpret_cast<const uint32_t*>(P.K1[k0]);
+    P.tab[k1] = P.tab[k0] + P.g.n[k0];   // (a 1D grid's second axis has one entry and no place of its own)
+    HIP_TRY(launch_build_tables(const_cast<uint32_t*>(P.tab[k0]), const_cast<uint32_t*>(P.tab[k1]), P.g.n[k0],
+                                P.g.n[k1], identity ? 1e-30 : P.gamma, P.gamma, P.prec == JKO_SPLIT_BF16, P.st));
+    return JKO_OK;
+}
+
+// The plan's paths.  stacked: axis 0 holds two fields, and the caller picks a
+// path that keeps them apart.
+void plan_paths(Plan& P, double gamma, int32_t flags, bool stacked) {
     P.gamma = gamma;
     for (int k = 0; k < P.g.d; ++k) P.W[k] = band_halfwidth(P.g.n[k], gamma);
     P.plane3d = P.g.d == 3 && !(flags & JKO_FLAG_AXIS_PASSES) &&
@@ -307,7 +318,10 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool stacked 
     P.fused2d = P.tile != 0;
     P.resident = P.fused2d;
     P.respass = !P.fused2d && passes2d;
-    if (P.fused2d) return JKO_OK;
+}
+
+// The stored factors of the paths that read them.
+jko_status store_factors(Plan& P) {
     for (int k = 0; k < P.g.d; ++k) {
         if (P.plane3d && plane3d_stride(P.g.n[k]) != P.g.n[k]) {
             // padded rows: only the form that this precision reads, over the
@@ -325,9 +339,17 @@ jko_status build_factors(Plan& P, double gamma, int32_t flags = 0, bool stacked 
         if (done) continue;
         HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[k]), const_cast<uint16_t*>(P.K1hi[k]),
                                     const_cast<uint16_t*>(P.K1lo[k]), P.g.n[k],
-                                    P.plane3d ? plane3d_stride(P.g.n[k]) : P.g.n[k], gamma, P.st));
+                                    P.plane3d ? plane3d_stride(P.g.n[k]) : P.g.n[k], P.gamma, P.st));
     }
     return JKO_OK;
+}
+
+// Both.  The tile kernels make their own bands, from stored entries where a step
+// runs as one launch per application.
+jko_status build_factors(Plan& P, double gamma, int32_t flags = 0) {
+    plan_paths(P, gamma, flags, false);
+    if (!P.fused2d) return store_factors(P);
+    return flags & JKO_FLAG_NO_RESIDENT ? build_tables(P, 0, 1) : JKO_OK;
 }
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
@@ -363,14 +385,15 @@ Pass slow_of(const Plan& P) {
 jko_status apply_xi(const Plan& P, const float* x, EpiArgs epi, int* nblocks) {
     set_vec(epi);
     if (P.batch2d) {
-        Band2D b{P.g.n[1], P.g.n[2], P.W[1], P.W[2], P.gamma, x, P.tile, P.g.n[0], P.owns(x)};
+        Band2D b{P.g.n[1], P.g.n[2], P.W[1],   P.W[2],   P.gamma,  x,
+                 P.tile,   P.g.n[0], P.owns(x), P.tab[1], P.tab[2]};
         int nb = 0;
         HIP_TRY(launch_gibbs2d(b, P.prec, epi, &nb, P.st));
         if (nblocks) *nblocks = nb;
         return JKO_OK;
     }
     if (P.fused2d) {
-        Band2D b{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.gamma, x, P.tile, 1, P.owns(x)};
+        Band2D b{P.g.n[0], P.g.n[1], P.W[0], P.W[1], P.gamma, x, P.tile, 1, P.owns(x), P.tab[0], P.tab[1]};
         int nb = 0;
         HIP_TRY(launch_gibbs2d(b, P.prec, epi, &nb, P.st));
         if (nblocks) *nblocks = nb;
@@ -1209,29 +1232,40 @@ jko_status attraction_flow(const Geo& g, const jko_energy* en, const jko_params*
     jko_status s = carve(&P, stacked_of(g), flow ? OP_FLOW : OP_STEP, n_steps, ws, ws_bytes, pr->precision, st);
     if (s) return s;
     if ((s = readback_init())) return s;
-    if ((s = build_factors(P, pr->gamma, pr->flags, true))) return s;
-    // the stacking axis: gamma -> 0 rounds every off-diagonal entry to zero
-    HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[0]), const_cast<uint16_t*>(P.K1hi[0]),
-                                const_cast<uint16_t*>(P.K1lo[0]), 2, 2, 1e-30, P.st));
+    plan_paths(P, pr->gamma, pr->flags, true);
     P.ident[0] = true;
-    // both couplings in one launch of the fused 2D kernel per application (axis
-    // 0 of the stacked field is the identity; a 1D grid is one column of cells)
-    // the resident pass kernel (paired tiles) where the grid and bands suit it
+    // both couplings in one launch of the fused 2D kernel per application: a 2D
+    // grid's as a batch of two fields, a 1D grid's as the two rows of one, with
+    // the identity along the stacking axis (a step of 50 iterations of 64 cells
+    // 618 us so, 685 as a batch of two columns; 500 cells 709, 727).
+    // The resident pass kernel (paired tiles) where the grid and bands suit it
     const bool respass2 = g.d == 2 && !(pr->flags & JKO_FLAG_NO_RESIDENT) &&
                           resident_pass2d_shape_fits(g.n[0], g.n[1], P.W[1], P.W[2], 2);
-    if (g.d <= 2 && !respass2 && !(pr->flags & JKO_FLAG_AXIS_PASSES))
-        for (int tt : {16, 32})
-            if (gibbs2d_fits(g.n[0], g.n[1], P.W[1], P.W[2], P.prec, tt) &&
-                gibbs2d_blocks(g.n[0], g.n[1], tt) <= kFusedMaxBlocks) {
+    const bool rows = g.d == 1;
+    if (!respass2 && !(pr->flags & JKO_FLAG_AXIS_PASSES))
+        for (int tt : {16, 32}) {
+            const int m0 = rows ? 2 : g.n[0], m1 = rows ? g.n[0] : g.n[1];
+            const int w0 = rows ? 0 : P.W[1], w1 = rows ? P.W[1] : P.W[2];
+            if (gibbs2d_fits(m0, m1, w0, w1, P.prec, tt) && gibbs2d_blocks(m0, m1, tt) <= kFusedMaxBlocks) {
                 P.tile = tt;
-                P.batch2d = true;
+                (rows ? P.fused2d : P.batch2d) = true;
                 break;
             }
+        }
+    if (P.fused2d) P.W[0] = 0;   // (the rows' identity)
     // bands too wide for the fused kernel: each field rotates through its own
     // two passes (rows of a field a multiple of 4), so no pass runs over the
     // identity axis
     if (g.d == 2 && !P.batch2d && g.n[0] % 4 == 0 && g.n[1] % 4 == 0) P.batch_pass = true;
     P.respass = respass2;
+    if (P.batch2d || P.fused2d) {
+        if ((s = build_tables(P, rows ? 0 : 1, rows ? 1 : 2, rows))) return s;
+    } else {
+        if ((s = store_factors(P))) return s;
+        // the stacking axis: gamma -> 0 rounds every off-diagonal entry to zero
+        HIP_TRY(launch_build_factor(const_cast<float*>(P.K1[0]), const_cast<uint16_t*>(P.K1hi[0]),
+                                    const_cast<uint16_t*>(P.K1lo[0]), 2, 2, 1e-30, P.st));
+    }
     // capacity of the initial density, and a target of the same mass
     double h[3], hr[3];
     HIP_TRY(launch_input_check(p0, en->kappa, en->kappa_scalar, g.N, 1, P.part.err, 3 * 256, P.hostout, P.st));

@@ -86,6 +86,18 @@ struct Smem {
     __device__ float* Z() { return Geom<TT>::kAliasZ ? Xs : Zown; }
 };
 
+// Division of the units of a copy by a row's length (uniform): one division a
+// block, then a multiplication a unit.  Exact for units below 2^13 and rows of
+// at most 64, as the quotient's error, units / 2^20, is below 1 / 64.  (Nine
+// divisions a thread, one for each copy that a halo may have, were 0.9 us of a
+// launch of 5.)
+struct Rows {
+    int len;
+    uint32_t m;
+    __device__ explicit Rows(int len_) : len(len_), m((1u << 20) / (uint32_t)len_ + 1u) {}
+    __device__ int row(int unit) const { return (int)((uint32_t)unit * m >> 20); }
+};
+
 __device__ __forceinline__ int xcd_block() {
     const int nb = gridDim.x, bid = blockIdx.x;
     if (nb % 8 != 0) return bid;
@@ -165,12 +177,13 @@ constexpr int kPastBuffer = 0x7ffffff0;
 // Returns the copies (one bit each) whose chunk crosses the end of a grid row.
 template <int TT>
 __device__ __forceinline__ uint32_t halo_offsets(const Band2D& B, const Tile<TT>& T, int (&off)[halo_copies<TT>()]) {
-    const int cols = T.LJp / 4 + 1;
+    static_assert((halo_copies<TT>() + 1) * kThr <= 1 << 13, "Rows");
+    const Rows rows(T.LJp / 4 + 1);
     uint32_t cut = 0;
 #pragma unroll
     for (int u = 0; u < halo_copies<TT>(); ++u) {
         const int unit = threadIdx.x + u * kThr;
-        const int r = unit / cols, c = 4 * (unit % cols);
+        const int r = rows.row(unit), c = 4 * (unit - r * rows.len);
         off[u] = (r < T.LI && c < T.LJ) ? 4 * ((T.ib0 + r) * B.n1 + T.jb0 + c) : kPastBuffer;
         if (r < T.LI && c < T.LJ && T.jb0 + c + 4 > B.n1) cut |= 1u << u;
     }
@@ -209,45 +222,121 @@ __device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, co
     cut_rows<TT>(B, cut, Xs);
 }
 
+// One axis's band as groups of four entries, spread over the threads: row r0 + r
+// of the factor, columns kb + c ...
+template <int TT> constexpr int band_count() {   // max groups per thread
+    return (TT * (Geom<TT>::kHalo / 4) + kThr - 1) / kThr;
+}
+template <int TT>
+struct BandUnits {
+    int rows, off, L, Lp;   // rows within the grid; the first row's first column's distance (signed)
+    int r[band_count<TT>()], c[band_count<TT>()];
+    __device__ __forceinline__ bool any(int u) const { return threadIdx.x + u * kThr < TT * (Lp / 4); }
+    __device__ __forceinline__ bool in(int u, int e) const { return any(u) && r[u] < rows && c[u] + e < L; }
+    __device__ __forceinline__ int d(int u, int e) const { return in(u, e) ? abs(off + r[u] - (c[u] + e)) : 0; }
+};
+template <int TT>
+__device__ __forceinline__ BandUnits<TT> band_units(int r0, int kb, int L, int Lp, int n) {
+    BandUnits<TT> b;
+    b.rows = n - r0;
+    b.off = r0 - kb;
+    b.L = L;
+    b.Lp = Lp;
+    const Rows rows(Lp / 4);
+#pragma unroll
+    for (int u = 0; u < band_count<TT>(); ++u) {
+        const int unit = threadIdx.x + u * kThr;
+        b.r[u] = rows.row(unit);
+        b.c[u] = 4 * (unit - b.r[u] * rows.len);
+    }
+    return b;
+}
+// Entries (the bits of gibbs_bits) to LDS, zeros outside the grid and the band.
+template <int TT, bool SPLIT>
+__device__ __forceinline__ void put_band(const BandUnits<TT>& b, const u32x4 (&v)[band_count<TT>()], float* kf,
+                                         uint16_t* kh, uint16_t* kl) {
+    constexpr int kS = Smem<TT, SPLIT>::S, kS2 = Smem<TT, SPLIT>::S2;
+#pragma unroll
+    for (int u = 0; u < band_count<TT>(); ++u) {
+        if (!b.any(u)) continue;
+        u32x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = b.in(u, e) ? v[u][e] : 0u;
+        if (SPLIT) {
+            u16x4 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                hi[e] = (uint16_t)w[e];
+                lo[e] = (uint16_t)(w[e] >> 16);
+            }
+            *reinterpret_cast<u16x4*>(&kh[b.r[u] * kS2 + b.c[u]]) = hi;
+            *reinterpret_cast<u16x4*>(&kl[b.r[u] * kS2 + b.c[u]]) = lo;
+        } else {
+            *reinterpret_cast<f4*>(&kf[b.r[u] * kS + b.c[u]]) = __builtin_bit_cast(f4, w);
+        }
+    }
+}
+template <int TT, bool SPLIT, typename Entry>
+__device__ __forceinline__ void store_band(const BandUnits<TT>& b, Entry entry, float* kf, uint16_t* kh, uint16_t* kl) {
+    u32x4 v[band_count<TT>()];
+#pragma unroll
+    for (int u = 0; u < band_count<TT>(); ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[u][e] = entry(b.d(u, e));
+    put_band<TT, SPLIT>(b, v, kf, kh, kl);
+}
+
 // The tile's factor bands.  An entry depends on |i - k| alone, so a band has
 // fewer distinct entries than a halo edge; each takes one thread one
 // exponential (the value that would be stored for the launch otherwise), and
-// the launch path's run while the halo's loads are in flight.  32 x 32: a
-// product is one launch of 4.8 us, not two of 5.8 (storing the factors) and
+// a product's run while the halo's loads are in flight.  32 x 32: a product on
+// its own is one launch of 4.8 us, not two of 5.8 (storing the factors) and
 // 5.0 us (reading the bands back).
 template <int TT, bool SPLIT>
 __device__ __forceinline__ void build_bands(const Band2D& B, const Tile<TT>& T, Smem<TT, SPLIT>& S) {
     constexpr int H = Geom<TT>::kHalo;
     static_assert(kThr >= 512 && H <= 256 && 2 * H <= 8 * 4 * kRS, "one thread per entry, in the partial sums' LDS");
-    constexpr int kS = Smem<TT, SPLIT>::S, kS2 = Smem<TT, SPLIT>::S2;
     const int tid = threadIdx.x;
     uint32_t* tab = reinterpret_cast<uint32_t*>(S.red);   // [axis][|i - k|]: a float, or hi and lo
     const int ax = tid >> 8, diff = tid & 255;
     if (diff < H) tab[ax * H + diff] = gibbs_bits<SPLIT>(diff, ax ? B.n0 : B.n1, B.gamma);
     __syncthreads();
-    // axis 1: rows j, then axis 0: rows i (zero outside the grid)
-    auto fill = [&](int axis, int n, int r0, int kb, int L, int Lp, float* kf, uint16_t* kh, uint16_t* kl) {
-        for (int unit = tid; unit < TT * (Lp / 4); unit += kThr) {
-            const int r = unit / (Lp / 4), c = 4 * (unit % (Lp / 4));
-            u32x4 v;
+    // axis 1: rows j, then axis 0: rows i
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
+    store_band<TT, SPLIT>(j, [&](int d) { return tab[d]; }, S.Kj, S.Kjh, S.Kjl);
+    store_band<TT, SPLIT>(i, [&](int d) { return tab[H + d]; }, S.Ki, S.Kih, S.Kil);
+}
+
+// The same from the stored tables, in two parts: the entries on their way to
+// registers, then to LDS.  A step on the launch path needs its bands hundreds of
+// times.  64 x 64 FP32, us a launch: 5.4 with each launch computing them, 4.9 so
+// (5.1 with rows of stored factors read instead, and a division per copy of the
+// halo); the 1D attraction's two rows of 64 cells 3.9 (5.2 as two columns of which
+// each computes its bands, 3.6 from stored factors).
+template <int TT>
+struct BandRegs {
+    u32x4 j[band_count<TT>()], i[band_count<TT>()];
+};
+template <int TT>
+__device__ __forceinline__ void load_bands(const Band2D& B, const Tile<TT>& T, BandRegs<TT>& r) {
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool in = r0 + r < n && c + e < L;
-                v[e] = in ? tab[axis * H + abs(r0 + r - (kb + c + e))] : 0u;
-            }
-            if (SPLIT) {
+    for (int u = 0; u < band_count<TT>(); ++u) {
+        r.j[u] = r.i[u] = u32x4{0, 0, 0, 0};
+        if (j.any(u))
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    kh[r * kS2 + c + e] = (uint16_t)v[e];
-                    kl[r * kS2 + c + e] = (uint16_t)(v[e] >> 16);
-                }
-            } else {
-                *reinterpret_cast<f4*>(&kf[r * kS + c]) = __builtin_bit_cast(f4, v);
-            }
-        }
-    };
-    fill(0, B.n1, T.j0, T.jb0, T.LJ, T.LJp, S.Kj, S.Kjh, S.Kjl);
-    fill(1, B.n0, T.i0, T.ib0, T.LI, T.LIp, S.Ki, S.Kih, S.Kil);
+            for (int e = 0; e < 4; ++e) r.j[u][e] = B.tab1[j.d(u, e)];
+        if (i.any(u))
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r.i[u][e] = B.tab0[i.d(u, e)];
+    }
+}
+template <int TT, bool SPLIT>
+__device__ __forceinline__ void place_bands(const Band2D& B, const Tile<TT>& T, const BandRegs<TT>& r,
+                                            Smem<TT, SPLIT>& S) {
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
+    put_band<TT, SPLIT>(j, r.j, S.Kj, S.Kjh, S.Kjl);
+    put_band<TT, SPLIT>(i, r.i, S.Ki, S.Kih, S.Kil);
 }
 
 // Both contractions of the staged tile and its epilogue, then the block's
@@ -398,10 +487,14 @@ gibbs2d_kernel(Band2D B, EpiArgs E) {
 
     // (every copy's LDS and the table's are distinct, so the copies land while
     // the bands are made)
+    const bool stored = B.tab0 != nullptr;   // (uniform)
+    BandRegs<TT> bands;
+    if (stored) load_bands<TT>(B, T, bands);
     int off[halo_copies<TT>()];
     const uint32_t cut = halo_offsets<TT>(B, T, off);
     issue_halo<TT, 0>(B, T, off, S.Xs, B.padded ? (B.n0 * B.n1 * 4 + 15) & ~15 : B.n0 * B.n1 * 4);
-    build_bands<TT, SPLIT>(B, T, S);
+    if (stored) place_bands<TT, SPLIT>(B, T, bands, S);
+    else build_bands<TT, SPLIT>(B, T, S);
     wait_vm_n<0>();
     cut_rows<TT>(B, cut, S.Xs);
     const int xs = T.LJp + 4;

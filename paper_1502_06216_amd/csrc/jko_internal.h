@@ -158,6 +158,10 @@ struct Band2D {
     int batch;             // per-application kernel only: this many n0 x n1 fields stacked in X and in
                            // the epilogue's fields, one block per (field, tile); 0 or 1: one field
     bool padded;           // per-application kernel only: X's allocation is a multiple of 16 bytes long
+    // per-application kernel only: the factors' entries by distance (gibbs_bits of 0 .. n - 1) stored for
+    // several applications, or NULL: the blocks compute them
+    const uint32_t* tab0;
+    const uint32_t* tab1;
 };
 // The tile's halo (tile + 2 W, aligned) fits the kernel's LDS.
 bool gibbs2d_fits(int n0, int n1, int W0, int W1, int32_t precision, int tile);
@@ -285,6 +289,9 @@ int band_halfwidth(int n, double gamma);
 // ----------------------------------------------------------------- pointwise
 hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int stride, double gamma,
                                hipStream_t s);
+// Band2D's tables of both axes.
+hipError_t launch_build_tables(uint32_t* tab0, uint32_t* tab1, int n0, int n1, double gamma0, double gamma1,
+                               bool split, hipStream_t s);
 hipError_t launch_fill(float* x, float v, int64_t n, hipStream_t s);
 hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t s);
 hipError_t launch_copy_scaled(float* dst, const float* src, double f, int64_t n, hipStream_t s);

@@ -14,6 +14,8 @@
 //  * the pointwise parts of the adjoint sweep.
 #include <math.h>
 
+#include <algorithm>
+
 #include "adjoint.h"
 #include "control.h"
 #include "factor.h"
@@ -38,6 +40,13 @@ __global__ void k_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int
     const double kd = j < n ? gibbs_entry(i - j, n, gamma) : 0.0;
     if (K1) K1[idx] = (float)kd;
     if (hi) gibbs_split(kd, &hi[idx], &lo[idx]);
+}
+
+// The factors' entries by distance, one axis a row of blocks.
+template <bool SPLIT>
+__global__ void k_build_tables(uint32_t* tab0, uint32_t* tab1, int n0, int n1, double gamma0, double gamma1) {
+    const int d = blockIdx.x * blockDim.x + threadIdx.x, n = blockIdx.y ? n1 : n0;
+    if (d < n) (blockIdx.y ? tab1 : tab0)[d] = gibbs_bits<SPLIT>(d, n, blockIdx.y ? gamma1 : gamma0);
 }
 
 __global__ void k_fill(float* x, float v, int64_t n) {
@@ -279,6 +288,14 @@ hipError_t launch_build_factor(float* K1, uint16_t* hi, uint16_t* lo, int n, int
                                hipStream_t s) {
     const int64_t nn = (int64_t)n * stride;
     hipLaunchKernelGGL(k_build_factor, dim3(blocks_for(nn)), dim3(256), 0, s, K1, hi, lo, n, stride, gamma);
+    return hipGetLastError();
+}
+
+hipError_t launch_build_tables(uint32_t* tab0, uint32_t* tab1, int n0, int n1, double gamma0, double gamma1,
+                               bool split, hipStream_t s) {
+    const dim3 grid((unsigned)((std::max(n0, n1) + 255) / 256), 2), block(256);
+    if (split) hipLaunchKernelGGL(k_build_tables<true>, grid, block, 0, s, tab0, tab1, n0, n1, gamma0, gamma1);
+    else hipLaunchKernelGGL(k_build_tables<false>, grid, block, 0, s, tab0, tab1, n0, n1, gamma0, gamma1);
     return hipGetLastError();
 }
 
