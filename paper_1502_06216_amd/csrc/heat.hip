@@ -249,39 +249,60 @@ __global__ void k_heat_gather(float* __restrict__ x, const float* __restrict__ s
 //   part[I][J] = A_IJ x_J             (its row sums, the tile's share of y_I)
 //   part[J][I] = A_IJ^T x_I  (I < J)  (its column sums, the share of y_J
 //                                      from the transposed lower tile)
-// so that every (row block, tile) slot of part is written exactly once.  The
-// loads are plain: the operator of a 100 x 100 room stays largely in the
-// last-level cache between passes (with the non-temporal hint the room's flow
-// ran 12 % slower).  A step runs on the resident kernel (heatres.hip) where
-// the operator suits it; this pass serves single products and larger operators.
-__global__ void __launch_bounds__(kHeatThr) k_heat_tiles(const float* __restrict__ A, const float* __restrict__ x,
-                                                         float* __restrict__ part, int nT) {
+// so that every (row block, tile) slot of part is written exactly once.  Wave w
+// takes the tile's strips w and w + 4, row by row in turn.  Bound: memory.  The
+// operator of a 100 x 100 room stays largely in the last-level cache between
+// passes, by plain loads (with the non-temporal hint the room's flow ran 12 %
+// slower).  One beyond that cache does not, and the hint (STREAM) saves filling
+// it: a product of a 120 x 120 room 117 -> 105 us, 160 x 160 283 -> 253, 200 x 200
+// 644 -> 573 (5.6 TB/s); eight waves of a strip each, without it, 117, 296, 692.
+// A step runs on the resident kernel (heatres.hip) where the operator suits it;
+// this pass serves single products and larger operators.
+constexpr int kPassWaves = kHeatWaves / 2;
+// 272 MB (a 108 x 108 room) 79 us by plain loads, 82 streamed; 362 MB (116 x 116) 107, 97
+constexpr int64_t kCacheBytes = 300000000;
+
+template <bool STREAM>
+__global__ void __launch_bounds__(64 * kPassWaves) k_heat_tiles(const float* __restrict__ A,
+                                                                const float* __restrict__ x,
+                                                                float* __restrict__ part, int nT) {
     constexpr int T = kHeatTile;
     __shared__ float rows[kHeatWaves][T];
     const int b = blockIdx.x;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, rg = lane >> 2;
-    HeatTileRegs a;
-    heat_load_tile(a, A, b, wave, lane);
+    HeatTileRegs a[2];
+    const f4* p = reinterpret_cast<const f4*>(A + (int64_t)b * kHeatTileFloats) + wave * 512 + lane;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const f4* q = p + 512 * kPassWaves * h + 64 * k;
+            a[h].v[k] = STREAM ? __builtin_nontemporal_load(q) : *q;
+        }
     int I = 0, start = 0;
     while (start + (nT - I) <= b) {    // uniform over the block; at most nT steps
         start += nT - I;
         ++I;
     }
     const int J = I + (b - start);
-    const f4 xj = reinterpret_cast<const f4*>(x + (int64_t)J * T)[4 * wave + (lane & 3)];
     const f4* xr = reinterpret_cast<const f4*>(x + (int64_t)I * T) + 2 * rg;
     const f4 x0 = xr[0], x1 = xr[1];
     const float xi[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-    float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    const f4 cs = heat_tile_fma([&](int q) { return a.v[q]; }, xj, xi, rs);
-    if (I != J) {
-        const float v = heat_column_sum(cs);
-        if ((lane & 12) == 0) part[((int64_t)J * nT + I) * T + 16 * wave + 4 * (lane & 3) + (lane >> 4)] = v;
-    }
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const float v = heat_row_sum(rs[q]);
-        if ((lane & 3) == 0) rows[wave][8 * rg + q] = v;
+    for (int h = 0; h < 2; ++h) {
+        const int w = wave + kPassWaves * h;
+        const f4 xj = reinterpret_cast<const f4*>(x + (int64_t)J * T)[4 * w + (lane & 3)];
+        float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        const f4 cs = heat_tile_fma([&](int q) { return a[h].v[q]; }, xj, xi, rs);
+        if (I != J) {
+            const float v = heat_column_sum(cs);
+            if ((lane & 12) == 0) part[((int64_t)J * nT + I) * T + 16 * w + 4 * (lane & 3) + (lane >> 4)] = v;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float v = heat_row_sum(rs[q]);
+            if ((lane & 3) == 0) rows[w][8 * rg + q] = v;
+        }
     }
     __syncthreads();
     const int t = threadIdx.x;
@@ -447,7 +468,11 @@ template <int EK>
 hipError_t gemv_as(const HeatGemv& g, hipStream_t st) {
     if (g.nT == 0) return hipSuccess;   // no free cell
     const int64_t tiles = (int64_t)g.nT * (g.nT + 1) / 2;
-    hipLaunchKernelGGL(k_heat_tiles, dim3((unsigned)tiles), dim3(kHeatThr), 0, st, g.A, g.x, g.part, g.nT);
+    const dim3 grid((unsigned)tiles), block(64 * kPassWaves);
+    if (tiles * (int64_t)(kHeatTileFloats * sizeof(float)) > kCacheBytes)
+        hipLaunchKernelGGL(k_heat_tiles<true>, grid, block, 0, st, g.A, g.x, g.part, g.nT);
+    else
+        hipLaunchKernelGGL(k_heat_tiles<false>, grid, block, 0, st, g.A, g.x, g.part, g.nT);
     hipLaunchKernelGGL(k_heat_finish<EK>, dim3((unsigned)((g.N + 31) / 32)), dim3(256), 0, st, g);
     return hipGetLastError();
 }

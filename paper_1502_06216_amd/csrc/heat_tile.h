@@ -25,11 +25,6 @@ __host__ __device__ __forceinline__ int heat_tile_offset(int r, int c) {
 struct HeatTileRegs {
     f4 v[8];
 };
-__device__ __forceinline__ void heat_load_tile(HeatTileRegs& t, const float* A, int64_t tile, int wave, int lane) {
-    const f4* p = reinterpret_cast<const f4*>(A + tile * kHeatTileFloats) + wave * 512 + lane;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) t.v[k] = p[64 * k];
-}
 
 // rs[q] += this lane's share of row 8 (lane / 4) + q of A x_J, and the lane's
 // share of the four columns of A^T x_I.  get(q): the lane's float4 of row q.

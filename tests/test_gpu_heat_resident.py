@@ -36,6 +36,17 @@ def test_step_matches_the_solves(shape):
     assert err <= TOL
 
 
+@pytest.mark.parametrize("shape", [(108, 107), (121, 118)])
+def test_product_of_an_operator_beyond_the_cache(shape):
+    """Operators of less and more than the last-level cache holds, whose tiles a product streams."""
+    banner(f"heat product {shape}")
+    wl = heat_room(*shape, seed=4)
+    x = dev(np.where(wl.mask, np.random.default_rng(8).uniform(size=shape), 0.0))
+    a, b = [host64(op.apply(x)) for op in _ops(wl)]
+    assert rel_l1(a, b) <= 1e-6      # float32 entries and sums, as in the products against the oracle
+    assert not a[~wl.mask].any()
+
+
 @pytest.mark.parametrize("ce", [1, 2, 7, 200])
 def test_tolerance_mode(ce):
     banner(f"heat resident tolerance ce={ce}")
