@@ -163,8 +163,6 @@ Layout layout_of(const Geo& g, int op, int64_t iters_or_steps) {
     off += align_up(sizeof(Ctl));
     L.sync = off;
     off += align_up(4 * (size_t)resident_sync_words(kFusedMaxBlocks));
-    L.hostout = off;
-    off += align_up(8 * sizeof(double));
     L.part_cap = part_cap_of(g);
     L.part = off;
     off += align_up(4 * (size_t)L.part_cap * sizeof(double));
@@ -190,6 +188,10 @@ Layout layout_of(const Geo& g, int op, int64_t iters_or_steps) {
     L.nfields = nf;
     L.fields = off;
     off += (size_t)nf * align_up((size_t)g.N * sizeof(float));
+    // (behind the fields: a 16-byte copy from a field may start at its last value)
+    static_assert(8 * sizeof(double) >= kFieldSlack, "room past the last field");
+    L.hostout = off;
+    off += align_up(8 * sizeof(double));
     if (op == OP_BACKWARD) {
         L.hist_fields = 2 * std::max<int64_t>(iters_or_steps, 1);
         L.hist = off;
@@ -231,7 +233,7 @@ struct Plan {
     bool plane3d = false;        // 3D applications run as a plane pass and a slow-axis pass
 
     float* F(int i) const { return field[i]; }
-    // x is one of the workspace's fields, each a multiple of 256 bytes long
+    // x is one of the workspace's fields, with kFieldSlack bytes behind each
     bool owns(const float* x) const {
         const char* c = reinterpret_cast<const char*>(x);
         return c >= base && c < base + L.total;

@@ -609,8 +609,7 @@ plane_pass(Plane3D P) {
     // the chunk (layout and swizzle of the panel form).
     {
         const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(P.X), (short)0, RAG && P.padded ? (P.n0 * n1 * n2 * 4 + 15) & ~15 : P.n0 * n1 * n2 * 4,
-            kBufRsrcWord3);
+            const_cast<float*>(P.X), (short)0, P.n0 * n1 * n2 * 4 + (RAG && P.padded ? kFieldSlack : 0), kBufRsrcWord3);
         const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
             SPLIT ? (void*)const_cast<uint16_t*>(P.K2hi) : (void*)const_cast<float*>(P.K2), (short)0,
             SPLIT ? n2 * m2 * 2 : n2 * m2 * 4, kBufRsrcWord3);
@@ -619,8 +618,8 @@ plane_pass(Plane3D P) {
         const int xrow = lane >> 3, xch = lane & 7;
         const int krow = lane >> 2, kch = lane & 3;
         if (RAG && (n2 & 3) != 0 && !P.padded) {
-            // no word past the field may be read: copies of single floats, two
-            // rows each, those past a row's or the plane's end reading as zeros
+            // a caller's field ends with its last value: copies of single floats,
+            // two rows each, those past a row's or the plane's end reading as zeros
             const int XC = m1 / 2;
             for (int j = wave; j < NP * XC; j += kPlaneWaves) {
                 const int pnl = j / XC, row = (j % XC) * 2 + (lane >> 5);
@@ -847,8 +846,8 @@ contract_slow(Pass P, EpiArgs E) {
         // X: 4 rows of 64 r per wave-wide copy; lane L fills position L & 15 of
         // row 4 j + (L >> 4) with the chunk that the swizzle puts there
         // (RAG: the last chunk of a row may hold the next row's first values, which
-        // reach only outputs past r = R; X's allocation is a multiple of 16 bytes)
-        const i4v rx = buffer_desc(P.X, RAG ? (R * n * 4 + 15) & ~15 : R * n * 4);
+        // reach only outputs past r = R; the last row's, the slack past the field)
+        const i4v rx = buffer_desc(P.X, R * n * 4 + (RAG ? kFieldSlack : 0));
         const int krow = lane >> 4, pos = lane & 15;
         for (int j = wave; j < NP * 8; j += kThreads / 64) {
             const int pnl = j / 8, k = (j % 8) * 4 + krow;
@@ -1015,7 +1014,7 @@ int64_t contract_max_blocks(const Pass& pass, int32_t /*precision*/) { return ti
 bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2, int32_t precision) {
     if (!plane3d_pays(n0, n1, n2, W0, W1, W2, precision)) return false;
     if (n0 < kPlaneMinN || n1 < kPlaneMinN || n2 < kPlaneMinN || n1 > kPlaneMaxN1) return false;
-    if ((int64_t)n0 * n1 * n2 * 4 >= kPastEnd) return false;
+    if ((int64_t)n0 * n1 * n2 * 4 + kFieldSlack >= kPastEnd) return false;
     const int np2 = band_panels(n2, W2), np0 = band_panels(n0, W0);
     if (np2 > kPanelMax || np0 > kPanelMax || band_panels(n1, W1) > kPlaneQ) return false;
     // dynamic LDS within 64 KiB with the static arrays beside it

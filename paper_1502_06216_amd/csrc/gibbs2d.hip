@@ -216,8 +216,7 @@ __device__ __forceinline__ void issue_halo(const Band2D& B, const Tile<TT>& T, c
 template <int TT>
 __device__ __forceinline__ void copy_halo(const Band2D& B, const Tile<TT>& T, const int (&off)[halo_copies<TT>()],
                                           uint32_t cut, float* Xs) {
-    // (the field's own allocation is a multiple of 256 bytes long)
-    issue_halo<TT, kCpolCoherent>(B, T, off, Xs, (B.n0 * B.n1 * 4 + 15) & ~15);
+    issue_halo<TT, kCpolCoherent>(B, T, off, Xs, B.n0 * B.n1 * 4 + kFieldSlack);
     wait_vm_n<0>();
     cut_rows<TT>(B, cut, Xs);
 }
@@ -492,20 +491,17 @@ gibbs2d_kernel(Band2D B, EpiArgs E) {
     if (stored) load_bands<TT>(B, T, bands);
     int off[halo_copies<TT>()];
     const uint32_t cut = halo_offsets<TT>(B, T, off);
-    issue_halo<TT, 0>(B, T, off, S.Xs, B.padded ? (B.n0 * B.n1 * 4 + 15) & ~15 : B.n0 * B.n1 * 4);
+    issue_halo<TT, 0>(B, T, off, S.Xs, B.n0 * B.n1 * 4 + (B.padded ? kFieldSlack : 0));
     if (stored) place_bands<TT, SPLIT>(B, T, bands, S);
     else build_bands<TT, SPLIT>(B, T, S);
     wait_vm_n<0>();
     cut_rows<TT>(B, cut, S.Xs);
     const int xs = T.LJp + 4;
-    const int tail = B.n1 & 3;
-    if (!B.padded && tail && T.ib0 + T.LI == B.n0 && T.jb0 + T.LJ == B.n1) {
-        // the chunk across the buffer's end: its values one by one
+    if (!B.padded && (B.n1 & 3) && T.ib0 + T.LI + 2 >= B.n0 && T.jb0 + T.LJ + 2 >= B.n1) {
+        // the field's last three values, which a copy across its end may cover, one by one
         __syncthreads();
-        if (threadIdx.x < tail) {
-            const int c = T.LJ - tail + threadIdx.x;
-            S.Xs[(T.LI - 1) * xs + c] = B.X[(int64_t)(B.n0 - 1) * B.n1 + T.jb0 + c];
-        }
+        const int at = B.n0 * B.n1 - 1 - (int)threadIdx.x, r = at / B.n1 - T.ib0, c = at % B.n1 - T.jb0;
+        if (threadIdx.x < 3 && at >= 0 && r >= 0 && r < T.LI && c >= 0 && c < T.LJ) S.Xs[r * xs + c] = B.X[at];
     }
     if (done) return;   // the step has stopped: nothing to compute (uniform)
     contract_tile<TT, EK, false, SPLIT>(E, T, xs, ein, S, (int)blockIdx.x);

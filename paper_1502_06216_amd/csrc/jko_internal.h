@@ -119,6 +119,13 @@ hipError_t launch_contract(const Pass& pass, int32_t precision, const EpiArgs& e
 // Upper bound of the blocks launch_contract may use for a pass of this shape.
 int64_t contract_max_blocks(const Pass& pass, int32_t precision);
 
+// Bytes past a field of the workspace that a kernel may read (and discards): the
+// rest of a 16-byte copy that starts at the field's last value.  A buffer
+// descriptor that ends with the field would leave such a copy half in range, and
+// nothing here relies on what it then brings: of a caller's field the values
+// that such copies cover are read one by one.
+constexpr int kFieldSlack = 12;
+
 // 3D application in two launches that keep the layout [a][b][c] (c contiguous):
 //   plane pass:  Y[a][b'][c'] = sum_b K1_1[b'][b] sum_c K1_2[c'][c] X[a][b][c]
 //   slow pass:   Y[a'][r] = sum_a K1_0[a'][a] X[a][r]   (r = b n2 + c), + epilogue
@@ -135,13 +142,13 @@ struct Plane3D {
     const float* X;        // input field
     float* Y;              // output field (not X)
     const Ctl* ctl;        // kernels return early when ctl->done
-    bool padded;           // X's allocation is a multiple of 16 bytes long
+    bool padded;           // kFieldSlack bytes past X may be read
 };
 int plane3d_stride(int n);   // the factors' row stride: n in whole panels, the columns past n zero
 bool plane3d_fits(int n0, int n1, int n2, int W0, int W1, int W2, int32_t precision);
 hipError_t launch_plane3d(const Plane3D& p, int32_t precision, int* nblocks, hipStream_t stream);
-// Slow-axis pass: Pass.R = n1 n2 columns, Pass.n = n0, X is n0 x R (rows contiguous in r), in an
-// allocation of a multiple of 16 bytes; the factor's rows are plane3d_stride(n0) long.
+// Slow-axis pass: Pass.R = n1 n2 columns, Pass.n = n0, X is n0 x R (rows contiguous in r), and
+// kFieldSlack bytes past it may be read; the factor's rows are plane3d_stride(n0) long.
 hipError_t launch_contract_slow(const Pass& pass, int32_t precision, const EpiArgs& epi, int* nblocks,
                                 hipStream_t stream);
 int64_t contract_slow_blocks(const Pass& pass);
@@ -157,7 +164,7 @@ struct Band2D {
     int tile;              // output tile edge: 16 or 32
     int batch;             // per-application kernel only: this many n0 x n1 fields stacked in X and in
                            // the epilogue's fields, one block per (field, tile); 0 or 1: one field
-    bool padded;           // per-application kernel only: X's allocation is a multiple of 16 bytes long
+    bool padded;           // per-application kernel only: kFieldSlack bytes past X may be read
     // per-application kernel only: the factors' entries by distance (gibbs_bits of 0 .. n - 1) stored for
     // several applications, or NULL: the blocks compute them
     const uint32_t* tab0;

@@ -4,12 +4,14 @@ lie in the workspace: one iteration under the zero energy from a = 1 is
 b = q / (xi 1), p = xi b, so two products give the step's density bit for bit.
 Grids at the edges of the tiles of both sizes, narrow and wide bands, and bands
 cut by both edges of the grid."""
+import numpy as np
 import pytest
 import torch
 
+import oracle as O
 import paper_1502_06216_amd as jk
 
-from _util import banner, dev
+from _util import banner, dev, f32, host64
 from workloads import small_case
 
 pytestmark = pytest.mark.gpu
@@ -41,3 +43,24 @@ def test_same_bits_as_in_a_step(shape, cells, precision):
         assert not torch.isfinite(y[r, 0])
         if cells * 11 + 20 < shape[1]:
             assert torch.isfinite(y[:, -1]).all()
+
+
+@pytest.mark.parametrize("precision", ["fp32", "split_bf16"])
+@pytest.mark.parametrize("shape", [(64, 1), (65,), (300, 2), (70, 3), (3, 3), (1, 1), (40, 5), (18, 6), (50, 17),
+                                   (33, 34), (80, 47), (20, 18, 21), (17, 16, 33)])
+@pytest.mark.parametrize("cells", [0.4, 1.0, 2.0])
+def test_the_last_values_of_a_callers_field(shape, cells, precision):
+    """The copies that cross the end of a caller's field, whose last three values are read one by one: rows of one
+    to three cells, tiles whose halo ends just before the last cell, every start of the field in its memory; against
+    the oracle's products, with values behind the field that no output may see."""
+    banner(f"field end {shape} {cells} {precision}")
+    gamma = (cells / max(shape)) ** 2
+    rng = np.random.default_rng(9)
+    x = f32(rng.uniform(0.5, 1.5, shape))
+    ref = O.gibbs_apply(x.astype(np.float64), gamma)
+    for off in range(4):
+        buf = torch.full((x.size + 8,), float("nan"), device="cuda")
+        buf[off:off + x.size] = dev(x).reshape(-1)
+        y = host64(jk.gibbs_apply(buf[off:off + x.size].view(*shape), gamma, precision))
+        # sums of positive terms in FP32, two roundings an axis; 16-bit pairs split
+        np.testing.assert_allclose(y, ref, rtol={"fp32": 1e-5, "split_bf16": 1e-4}[precision], atol=0)
