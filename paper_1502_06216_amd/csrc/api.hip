@@ -1878,6 +1878,7 @@ HeatSolve heat_solve_of(const HeatLayout& H, const jko_heat_domain* d, char* bas
     hs.n1 = d->n1;
     hs.L = d->L;
     hs.gamma = gamma;
+    hs.s = heat_series(d->n0, d->n1, gamma, d->L, false);
     hs.Y = sc;
     hs.T0 = sc + H.N;
     hs.T1 = sc + 2 * H.N;
@@ -2115,12 +2116,12 @@ jko_status jko_heat_flow(const jko_heat_domain* domain, const jko_energy* energy
     if (is_congestion(energy) && h[1] < h[0] * (1.0 - 1e-6))
         return fail(JKO_ERR_INFEASIBLE, "capacity sum %.9g < mass %.9g", h[1], h[0]);
     const ProxArgs px = prox_args_fields(energy, sigma, fg, fkf);
+    const HeatSolve hs = heat_solve_of(H, domain, base, params->gamma);
     const float* q = p0;
     jko_status worst = JKO_OK;
     for (int t = 0; t < n_steps; ++t) {
         float* out = (t == n_steps - 1) ? pT : reinterpret_cast<float*>(base + ((t % 2 == 0) ? H.p0 : H.p1));
-        s = heat_step(H, base, nf, heat_solve_of(H, domain, base, params->gamma), params, px, energy->kind, q, out,
-                      stats ? &stats[t] : nullptr, st);
+        s = heat_step(H, base, nf, hs, params, px, energy->kind, q, out, stats ? &stats[t] : nullptr, st);
         if (s == JKO_ERR_NONFINITE) worst = s;
         else if (s) return s;
         q = out;

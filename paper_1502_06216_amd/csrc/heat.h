@@ -70,13 +70,15 @@ hipError_t launch_heat_compact(const uint8_t* mask, int64_t N, int32_t* cidx, in
 hipError_t launch_heat_gather(float* x, const float* src, const int32_t* gidx, int64_t nf, int64_t ld,
                               hipStream_t st);
 
-// x^-L on [1, beta] as a Chebyshev series: x^-L = c_0 / 2 + sum_k c_k T_k(u),
-// x = theta + delta u, theta = (beta + 1) / 2, delta = (beta - 1) / 2, with an
-// error of at most tol (times x^-L's largest value, 1) anywhere on the interval.
+// x^-L on the spectrum [1, beta] of a domain's operator as a Chebyshev series:
+// x^-L = c_0 / 2 + sum_k c_k T_k(u), x = theta + delta u, theta = (beta + 1) / 2,
+// delta = (beta - 1) / 2, cut where heat_series_tol says; for the columns of the
+// stored operator, or for products.  Empty: it has too many terms to be run, or
+// for the host's memory.
 struct HeatSeries {
     std::vector<double> c;
 };
-HeatSeries heat_series(double beta, int L, double tol);
+HeatSeries heat_series(int n0, int n1, double gamma, int L, bool stored);
 
 // Where the series is cut.  The cut is absolute, a fraction of the input's
 // norm, and the iteration divides by a product (b = q / t), so entries far
@@ -106,6 +108,7 @@ struct HeatSolve {
     const int32_t* cidx;     // grid cell -> free index or -1
     int n0, n1, L;
     double gamma;
+    HeatSeries s;            // the same for all products of a call
     double* T0;
     double* T1;
     double* Q0;

@@ -401,19 +401,24 @@ int chunk_log2(int64_t N) {
     return lg;                                    // at most 1024 columns per chunk
 }
 
-// The stencil's constants and the series' coefficients for a domain.
+// The stencil's weights and the spectrum's end for a domain.
+struct Spectrum {
+    double nu0, nu1, beta;
+    Spectrum(int n0, int n1, double gamma, int L)
+        : nu0(n0 > 1 ? gamma * (double)n0 * n0 / L : 0.0), nu1(n1 > 1 ? gamma * (double)n1 * n1 / L : 0.0),
+          beta(1.0 + 4.0 * (nu0 + nu1)) {}
+};
+
+// The stencil's constants for the launches of the series s.
 struct SeriesPlan {
     HeatSeriesArgs a{};
-    HeatSeries s;
+    const HeatSeries& s;
     unsigned tiles = 0;
 };
-SeriesPlan series_plan(int n0, int n1, double gamma, int L, bool stored) {
-    SeriesPlan p;
-    const double nu0 = n0 > 1 ? gamma * (double)n0 * n0 / L : 0.0;
-    const double nu1 = n1 > 1 ? gamma * (double)n1 * n1 / L : 0.0;
-    const double beta = 1.0 + 4.0 * (nu0 + nu1);
-    p.s = heat_series(beta, L, heat_series_tol(L, stored));
-    if (p.s.c.empty()) return p;
+SeriesPlan series_plan(const HeatSeries& s, int n0, int n1, double gamma, int L) {
+    SeriesPlan p{HeatSeriesArgs{}, s};
+    if (s.c.empty()) return p;
+    const auto [nu0, nu1, beta] = Spectrum(n0, n1, gamma, L);
     p.a.n0 = n0;
     p.a.n1 = n1;
     p.a.nu0 = nu0;
@@ -454,7 +459,7 @@ hipError_t run_series(SeriesPlan& p, double* const T[2], double* const Q[2], uns
 template <int EK>
 hipError_t solve_as(const HeatGemv& g, const HeatSolve& h, hipStream_t st) {
     if (g.N <= 0) return hipSuccess;   // no free cell
-    SeriesPlan p = series_plan(h.n0, h.n1, h.gamma, h.L, false);
+    SeriesPlan p = series_plan(h.s, h.n0, h.n1, h.gamma, h.L);
     p.a.mask = h.mask;
     p.a.cidx = h.cidx;
     p.a.x = g.x;
@@ -480,13 +485,14 @@ hipError_t gemv_as(const HeatGemv& g, hipStream_t st) {
 }  // namespace
 
 // The Chebyshev coefficients of x^-L on [1, beta] (x = theta + delta u), down
-// to a tail of `tol` of the largest value f(1) = 1.  f' = -L f / x gives them
+// to a tail of tol of the largest value f(1) = 1.  f' = -L f / x gives them
 // the three-term recurrence
 //   delta (k - 1 + L) c_{k-1} + 2 theta k c_k + delta (k + 1 - L) c_{k+1} = 0,
 // of which they are the decaying solution: they are run backwards from a
 // degree far in the tail (Miller's algorithm) and scaled so that the series
 // is 1 at x = 1, where its terms (-1)^k c_k are all positive.
-HeatSeries heat_series(double beta, int L, double tol) try {
+HeatSeries heat_series(int n0, int n1, double gamma, int L, bool stored) try {
+    const double beta = Spectrum(n0, n1, gamma, L).beta, tol = heat_series_tol(L, stored);
     HeatSeries out;
     if (!(beta > 1.0)) {
         out.c = {2.0};   // M is the identity
@@ -531,7 +537,8 @@ hipError_t heat_build_operator(const uint8_t* mask, int n0, int n1, double gamma
     const int64_t N = (int64_t)n0 * n1;
     hipLaunchKernelGGL(k_heat_zero, dim3(grid_for(heat_operator_floats(nf))), dim3(256), 0, st, A,
                        heat_operator_floats(nf));
-    SeriesPlan p = series_plan(n0, n1, gamma, L, true);
+    const HeatSeries s = heat_series(n0, n1, gamma, L, true);
+    SeriesPlan p = series_plan(s, n0, n1, gamma, L);
     // columns per chunk: T and Q twice each, and Y
     const int64_t C = std::max<int64_t>(1, 4 * ((int64_t)1 << chunk_log2(N)) / 5);
     p.a.mask = mask;
