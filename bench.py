@@ -696,7 +696,7 @@ def main():
                                                                       TRAFFIC_PROFILES.get(("porous512_scaled", prec)))}
         # heat-kernel Gibbs operator (L = 10 implicit steps) on a 100x100 room with obstacles
         extra["heat100_fp32"] = heat_bench(make_workload("heat100"))
-        # beyond the stored operator: a 300 x 300 room by per-product solves
+        # beyond the stored operator: a 300 x 300 room by the per-product series
         from workloads import heat_room
         extra["heat300_per_product_fp32"] = heat_solve_bench(heat_room(300, 300, seed=0))
         extra["adjoint_fp32"] = adjoint_ratio("fp32")

@@ -342,9 +342,9 @@ jko_status jko_time_iteration(const jko_grid* grid, const jko_energy* energy, co
  * product is the Chebyshev series of (Id - (gamma/L) Delta_M)^-L on the grid
  * in FP64 (one five-point stencil sweep per degree, 16 sweeps per launch on
  * tiles with a halo of 16 cells, cut at 1e-85 of the input's norm, for small L
- * at 1e-21 for each of the L; linear in the grid's size), rounded to float32.  The flow uses the iteration and stop test
- * of jko_step with xi replaced by xi~; float32 only, no log domain, no
- * backward.
+ * at 1e-21 for each of the L; linear in the grid's size), rounded to float32.
+ * The flow uses the iteration and stop test of jko_step with xi replaced by
+ * xi~; float32 only, no log domain, no backward.
  * ------------------------------------------------------------------------ */
 typedef struct {
     int32_t n0, n1;          /* grid, n0 x n1 cells (row-major, n1 fastest; n0 = 1: a 1D grid),
@@ -354,7 +354,7 @@ typedef struct {
                                 workspace's operator is in use */
     int32_t L;               /* implicit heat steps, 1..1000 (the paper uses 10) */
     int32_t per_product;     /* 0: the stored dense operator while n0 * n1 <= 65536, the
-                                per-product solves above; 1: the per-product solves always */
+                                per-product series above; 1: the per-product series always */
 } jko_heat_domain;
 
 /* Bytes of device workspace the calls below need for this domain (the dense

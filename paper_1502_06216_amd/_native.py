@@ -413,7 +413,7 @@ class HeatOperator:
     of the grid's shape, True = free; None = no obstacle).  Up to 65536 cells
     construction builds xi~ once on the GPU into a workspace this object owns
     (N^2 * 2 bytes and more); above (or with per_product=True) every product
-    is L solves on the grid instead and nothing is stored.  apply() and
+    is a series of stencil sweeps on the grid instead and nothing is stored.  apply() and
     flow() then use it.  The mask is kept (the library reads it on every
     call)."""
 

@@ -1759,25 +1759,25 @@ namespace {
 
 constexpr int32_t kHeatMagic = 0x48454154;   // "HEAT"
 constexpr int64_t kHeatMaxCells = 65536;         // the stored dense operator
-constexpr int64_t kHeatMaxCellsSolve = 1 << 20;  // the per-product solves
+constexpr int64_t kHeatMaxCellsSolve = 1 << 20;  // the per-product series
 
 struct HeatHdr {
     int32_t magic, n0, n1, L;
-    int32_t solve, pad;      // 1: products by L solves (no stored operator)
+    int32_t solve, pad;      // 1: products by the series (no stored operator)
     double gamma;
     int64_t nf;              // free cells (the operator's order)
 };
 
 struct HeatLayout {
     int64_t N = 0, ld = 0;
-    bool solve = false;      // products by L solves on the grid, no stored operator
+    bool solve = false;      // products by the series on the grid, no stored operator
     size_t hdr = 0, A = 0, part = 0, scratch = 0, cidx = 0, gidx = 0, a = 0, b = 0, x = 0, p0 = 0, p1 = 0, g = 0,
            kf = 0, err = 0, out = 0, sync = 0;
     size_t total = 0;
 };
 
 // The dense stored operator up to 2^16 cells unless the domain asks for the
-// per-product solves; the solves above.
+// per-product series; the series above.
 bool heat_solve_mode(const jko_heat_domain* d) {
     return d->per_product != 0 || (int64_t)d->n0 * d->n1 > kHeatMaxCells;
 }

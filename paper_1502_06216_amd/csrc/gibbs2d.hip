@@ -301,7 +301,8 @@ __device__ __forceinline__ void build_bands(const Band2D& B, const Tile<TT>& T, 
     if (diff < H) tab[ax * H + diff] = gibbs_bits<SPLIT>(diff, ax ? B.n0 : B.n1, B.gamma);
     __syncthreads();
     // axis 1: rows j, then axis 0: rows i
-    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1);
+    const BandUnits<TT> i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
     store_band<TT, SPLIT>(j, [&](int d) { return tab[d]; }, S.Kj, S.Kjh, S.Kjl);
     store_band<TT, SPLIT>(i, [&](int d) { return tab[H + d]; }, S.Ki, S.Kih, S.Kil);
 }
@@ -318,7 +319,8 @@ struct BandRegs {
 };
 template <int TT>
 __device__ __forceinline__ void load_bands(const Band2D& B, const Tile<TT>& T, BandRegs<TT>& r) {
-    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1);
+    const BandUnits<TT> i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
 #pragma unroll
     for (int u = 0; u < band_count<TT>(); ++u) {
         r.j[u] = r.i[u] = u32x4{0, 0, 0, 0};
@@ -333,7 +335,8 @@ __device__ __forceinline__ void load_bands(const Band2D& B, const Tile<TT>& T, B
 template <int TT, bool SPLIT>
 __device__ __forceinline__ void place_bands(const Band2D& B, const Tile<TT>& T, const BandRegs<TT>& r,
                                             Smem<TT, SPLIT>& S) {
-    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1), i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
+    const BandUnits<TT> j = band_units<TT>(T.j0, T.jb0, T.LJ, T.LJp, B.n1);
+    const BandUnits<TT> i = band_units<TT>(T.i0, T.ib0, T.LI, T.LIp, B.n0);
     put_band<TT, SPLIT>(j, r.j, S.Kj, S.Kjh, S.Kjl);
     put_band<TT, SPLIT>(i, r.i, S.Ki, S.Kih, S.Kil);
 }

@@ -23,10 +23,17 @@
 // block starts a phase before all have finished the one before, so nothing is
 // overwritten that another still reads.
 //
-// Bound: streaming of the tiles that are not kept, at 7.3 TB/s (plain loads; with
-// the non-temporal hint 44 us), then the two waits of a product.  An iteration
-// of two products: 100 x 100 room 63.4 -> 39.5 us (86 MB of 187 MB streamed),
-// 80 x 80 (all kept) 16.1 us, 64 x 64 13.8 us.
+// Stop test: the finish of a check's t = A a stores the cells' violations, block
+// 0 sums them once it has seen every block finish, and the word that lets the
+// others go on tells them to stop.  64 x 64, 60 iterations with a check after
+// each: 1180 us; with a launch up to each check, which loaded the kept tiles again
+// and had the host wait twice, 4200; two launches per product 2530.
+//
+// Bound: streaming of the tiles that are not kept, 4.7 TB/s over a whole step of
+// the 100 x 100 room (by plain loads; with the non-temporal hint an iteration took
+// 44 us), then the two waits of a product.  An iteration of two products:
+// 100 x 100 room 63.4 -> 39.5 us (86 MB of 187 MB streamed), 80 x 80 (all kept)
+// 16.1 us, 64 x 64 13.8 us.
 #include <algorithm>
 
 #include "epilogue.h"

@@ -11,9 +11,9 @@
 // chunk order and the epilogue in the tile kernel's lanes, the FP64 partial
 // sums wave by wave and tile by tile.  So the bits are those of the tile
 // kernel and of the launch path, as long as every product is finite: that
-// kernel has zeros past a tile's halo, the rows here go on to the next tile's
-// cells, and a zero of the factor cancels a finite value there, not an infinite
-// one.  A product that isn't finite is therefore reported (kResidentRedo), and the
+// kernel has zeros past a tile's halo (along a row past the group of four it
+// ends in), the rows here go on to the next tile's cells, and a zero of the
+// factor cancels a finite value there, not an infinite one.  A product that isn't finite is therefore reported (kResidentRedo), and the
 // step runs again on the tile kernel.  (Zeros in place of what lies past the
 // halos, selected as the rows are read: 7 to 15 % of an iteration.)
 //
