@@ -118,15 +118,13 @@ def test_checks_cost_little():
     wl = heat_room(64, 64, seed=5)
     en, _ = energies(wl)
     op = _ops(wl)[0]
-    best = []
-    for kw in (dict(), dict(tol=1e-30, check_every=1)):
-        us = []
-        for _ in range(20):
+    best = [np.inf, np.inf]
+    for _ in range(30):
+        for i, kw in enumerate((dict(), dict(tol=1e-30, check_every=1))):
             torch.cuda.synchronize()
             t = time.perf_counter()
             op.step(dev(wl.p0), en, wl.tau, max_iters=60, **kw)
             torch.cuda.synchronize()
-            us.append(1e6 * (time.perf_counter() - t))
-        best.append(min(us))
+            best[i] = min(best[i], 1e6 * (time.perf_counter() - t))
     print(f"[gpu-test] heat resident 64 x 64: {best[0]:.0f} us, with checks {best[1]:.0f}", flush=True)
     assert best[1] <= 2.0 * best[0]
